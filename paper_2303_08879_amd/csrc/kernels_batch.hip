@@ -95,6 +95,7 @@ __global__ __launch_bounds__(kThreads) void k_batch_out(const BatchCirc<R>* __re
 namespace {
 
 struct BatchSched {
+  uint64_t id = 0;                      // unique per built schedule
   int device = -1;
   std::vector<uint64_t> key;
   std::vector<uint64_t> uids;
@@ -122,7 +123,7 @@ std::vector<BatchSched> g_cache;
 fd_batch_tuning g_tuning = {2, 64, 4, 2048, 0};
 
 fd_batch_tuning batch_tuning() { return g_tuning; }
-uint64_t g_clock = 0;
+uint64_t g_clock = 0, g_sched_id = 0;
 constexpr size_t kBatchCache = 8;
 
 void free_sched(BatchSched& s) {
@@ -426,6 +427,42 @@ static bool sweep_takes(const Plan& Pl) {
 
 namespace {
 
+// A batched call captured into a graph: the level launches of the circuits
+// that fill the device, then the persistent sweep's three launches.
+struct BatchGraph {
+  int device = -1;
+  uint64_t sched = 0;                // schedule whose device tables the graph's kernels read (0: none)
+  std::vector<uint64_t> key, uids;
+  hipGraph_t graph = nullptr;
+  hipGraphExec_t exec = nullptr;
+  uint64_t last_use = 0;
+};
+std::vector<BatchGraph> g_graphs;
+hipStream_t g_capture[64] = {};   // private capture stream per device
+bool g_graph_failed = false;      // a capture was refused: batched calls run eagerly
+
+void free_graph(BatchGraph& g) {
+  if (unloading()) return;
+  (void)hipGraphExecDestroy(g.exec);
+  (void)hipGraphDestroy(g.graph);
+  g.exec = nullptr;
+  g.graph = nullptr;
+}
+
+// Drops a schedule and every graph captured over its device tables: a graph
+// replayed after its schedule was evicted would read freed memory.
+void drop_sched(BatchSched& s) {
+  for (size_t i = 0; i < g_graphs.size();) {
+    if (g_graphs[i].sched == s.id) {
+      free_graph(g_graphs[i]);
+      g_graphs.erase(g_graphs.begin() + i);
+    } else {
+      ++i;
+    }
+  }
+  free_sched(s);
+}
+
 // Cache key of a batched call: device, plans, schedules, pointers, knobs.
 std::vector<uint64_t> batch_key(int n, Plan* const* plans, const bool* odd, const void* const* A,
                                 const void* const* b, const void* const* c, void* const* rho, void* const* ws,
@@ -470,34 +507,14 @@ fd_status sweep_sched(int n, Plan* const* plans, const bool* odd, const void* co
   if (g_cache.size() >= kBatchCache) {
     auto it = std::min_element(g_cache.begin(), g_cache.end(),
                                [](const BatchSched& x, const BatchSched& y) { return x.last_use < y.last_use; });
-    free_sched(*it);
+    drop_sched(*it);
     g_cache.erase(it);
   }
+  ns.id = ++g_sched_id;
   g_cache.push_back(std::move(ns));
   *out = &g_cache.back();
   (*out)->last_use = ++g_clock;
   return FD_OK;
-}
-
-// A batched call captured into a graph: the level launches of the circuits
-// that fill the device, then the persistent sweep's three launches.
-struct BatchGraph {
-  int device = -1;
-  std::vector<uint64_t> key, uids;
-  hipGraph_t graph = nullptr;
-  hipGraphExec_t exec = nullptr;
-  uint64_t last_use = 0;
-};
-std::vector<BatchGraph> g_graphs;
-hipStream_t g_capture[64] = {};   // private capture stream per device
-bool g_graph_failed = false;      // a capture was refused: batched calls run eagerly
-
-void free_graph(BatchGraph& g) {
-  if (unloading()) return;
-  (void)hipGraphExecDestroy(g.exec);
-  (void)hipGraphDestroy(g.graph);
-  g.exec = nullptr;
-  g.graph = nullptr;
 }
 
 struct Split {
@@ -630,6 +647,7 @@ fd_status run_forward_batch(int n, Plan* const* plans, const bool* odd, const vo
   }
   BatchGraph g;
   g.device = dev;
+  g.sched = S ? S->id : 0;
   g.key = std::move(key);
   for (int i = 0; i < n; ++i) g.uids.push_back(plans[i]->uid);
   g.graph = graph;
@@ -668,7 +686,7 @@ void batch_forget(uint64_t uid) {
   }
   for (size_t i = 0; i < g_cache.size();) {
     if (std::find(g_cache[i].uids.begin(), g_cache[i].uids.end(), uid) != g_cache[i].uids.end()) {
-      free_sched(g_cache[i]);
+      drop_sched(g_cache[i]);
       g_cache.erase(g_cache.begin() + i);
     } else {
       ++i;

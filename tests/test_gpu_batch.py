@@ -242,6 +242,38 @@ def test_batch_graph_replay_matches_eager_over_repeated_calls():
         F.fd_batch_set_tuning(*old[:4], max(old[4], 0))
 
 
+def test_batch_graph_outlived_by_its_schedule():
+    # a graph captured over a schedule, then enough other calls (new output
+    # buffers) to evict that schedule from the cache, then the first call
+    # again: its graph must have gone with the schedule's device tables
+    circs = small_batch(353, 3)
+    dt = torch.complex128
+    plans = [ops.get_plan(c.cutoffs, c.detected_mask, dt, "zero") for c in circs]
+    ins = [ops._as_inputs(c.A, c.b, c.c, dt, "cuda") for c in circs]
+    ws = [ops._workspace(p.workspace(False)[0], "cuda") for p in plans]
+    sets = [[torch.zeros(p.out_shape, dtype=dt, device="cuda") for p in plans] for _ in range(10)]
+    call = lambda rho: F.fock_diag_fwd_batch(plans, [x[0] for x in ins], [x[1] for x in ins], [x[2] for x in ins],
+                                             rho, ws)
+    old = F.fd_batch_get_tuning()
+    try:
+        F.fd_batch_set_tuning(*old[:4], 1)
+        call(sets[0])                       # captured
+        F.fd_batch_set_tuning(*old[:4], 0)
+        for rho in sets[1:]:                # nine more schedules, no more graphs
+            call(rho)
+        torch.cuda.synchronize()
+        F.fd_batch_set_tuning(*old[:4], 1)
+        for rep in range(2):
+            for r in sets[0]:
+                r.zero_()
+            call(sets[0])
+            torch.cuda.synchronize()
+            for c, r in zip(circs, sets[0]):
+                np.testing.assert_array_equal(r.cpu().numpy(), run_single(c))
+    finally:
+        F.fd_batch_set_tuning(*old[:4], max(old[4], 0))
+
+
 def test_vjp_batch_matches_single_calls():
     circs = small_batch(361, 6, b_general=True)
     dt = torch.complex128
