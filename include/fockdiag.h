@@ -250,28 +250,24 @@ fd_status detection_probs(fd_plan p, const void* A, const void* b, const void* c
                           void* workspace, size_t ws_bytes, hipStream_t stream);
 
 /* Batched forward over n independent circuits, each with its own plan and
- * buffers (arrays of n host-side entries holding device pointers), in one
- * persistent sweep launch.  All pivots of one weight are independent
- * (Sec. 2.2) and circuits are independent of each other: step S of every
- * circuit is swept together, by a cooperative grid that fills the device and
- * takes (circuit, step, tile) work items from a per-step queue, with a grid
- * barrier between steps.  Launches: prep (+ undetected block fill), the
- * sweep, the output permutation.  A circuit whose levels average at least
+ * buffers (arrays of n host-side entries holding device pointers).  All
+ * pivots of one weight are independent (Sec. 2.2) and circuits are
+ * independent of each other: step S of every circuit of one class (Algorithm
+ * 1 or 2, detected-mode count, block coordinates, parity) is one launch, and
+ * the classes run side by side on up to three library-owned streams that are
+ * forked from and joined to `stream` (events; everything is ordered on
+ * `stream` when the call returns).  A circuit whose levels average at least
  * 2048 wavefront-sized units fills the device by itself and runs its own
- * level launches first (as fock_diag_fwd), and so does a circuit the sweep
- * cannot stage (three undetected modes, or rows beyond its LDS); the
- * persistent sweep takes the rest.
+ * level launches (as fock_diag_fwd) meanwhile, and so does a circuit the
+ * batched kernels do not take (three undetected modes, or rows beyond the LDS).
  *   plans      n plans of one dtype, created on the current device
  *   workspace  per circuit, >= fd_plan_workspace(plan, 0) bytes, 256-byte
  *              aligned; the n workspaces must not overlap (FD_ERR_INVALID_ARG)
  *   rho        per circuit, as for fock_diag_fwd
  * Results equal fock_diag_fwd's bit for bit.  The library keeps the work-item
- * table, per-circuit descriptors and the sweep's control words of the last 8
- * (plan set, pointer set) combinations in device memory (freed with the
- * plans); two batched calls with the same plans and pointers must not overlap
- * in time.  A device without cooperative launches gives FD_ERR_UNSUPPORTED.  A
- * barrier wait that exceeds its bound (a few seconds) is reported by
- * fd_device_status of the first plan as FD_ERR_HIP. */
+ * table and per-circuit descriptors of the last 8 (plan set, pointer set)
+ * combinations in device memory (freed with the plans); two batched calls
+ * with the same plans and pointers must not overlap in time. */
 fd_status fock_diag_fwd_batch(int n, const fd_plan* plans, const void* const* A,
                               const void* const* b, const void* const* c, void* const* rho,
                               void* const* workspace, const size_t* ws_bytes, hipStream_t stream);
@@ -293,21 +289,21 @@ fd_status fock_diag_vjp_batch(int n, const fd_plan* plans, const void* const* A,
 /* Scheduling knobs of fock_diag_fwd_batch (process-wide; a schedule built
  * under other knobs is rebuilt on next use):
  *   min_block_units, min_point_units, items_per_wave
- *              every step of a circuit is cut into items of units /
- *              (items_per_wave x resident wavefronts) units, at least
- *              min_block_units (lattice point, row chunk) units (Algorithm 2)
- *              or min_point_units lattice points (Algorithm 1);
+ *              every step of a circuit is cut into workgroups of units /
+ *              (items_per_wave x 2048) units, at least min_block_units / 2
+ *              (lattice point, row chunk) units (Algorithm 2) or
+ *              max(256, min_point_units) lattice points (Algorithm 1);
  *   fill_waves a circuit whose levels average at least fill_waves
  *              wavefront-sized units runs its own level launches instead of
- *              joining the persistent sweep;
+ *              joining the batched ones;
  *   use_graph  1: the first call with a given (plan set, pointer set) is
  *              captured into a HIP graph on a private stream (nothing runs
  *              during capture) and later calls with the same plans, pointers
  *              and knobs replay it on the caller's stream (buffer contents
  *              may change between calls); the last 8 graphs are kept and
  *              freed with their plans.  fd_batch_get_tuning reads -1 if the
- *              runtime refused a capture (a cooperative launch, say): calls
- *              then run their launches directly.  Graphs are not used while
+ *              runtime refused a capture: calls then run their launches
+ *              directly.  Graphs are not used while
  *              a plan of the batch records kernel times.
  * Defaults {2, 64, 4, 2048, 0}; the package's autotuner picks them per batch
  * signature by timing.  Values below 1 (use_graph: other than 0 or 1) give
@@ -340,7 +336,7 @@ fd_status fd_plan_use_graphs(fd_plan p, int enable);
  * 0 input prep, 1 undetected-block fill, 2 forward level sweep, 3 output
  * permutation, 4 cotangent permutation, 5 reverse level sweep, 6 reverse of
  * the undetected-block fill, 7 gradient reduction, 8 accumulator clear,
- * 9 batched prep, 10 batched persistent sweep, 11 batched output permutation
+ * 9 batched prep, 10 batched sweep (all its launches as one record), 11 batched output permutation
  * (batched kinds are recorded on the first plan of the batch). */
 enum { FD_K_PREP = 0, FD_K_UFILL = 1, FD_K_FWD_LEVEL = 2, FD_K_OUT_PERM = 3, FD_K_PERM_IN = 4,
        FD_K_VJP_LEVEL = 5, FD_K_UFILL_VJP = 6, FD_K_VJP_FINAL = 7, FD_K_ZERO = 8,
@@ -353,8 +349,7 @@ const char* fd_last_error(void);
 
 /* Reads and clears the plan's device status word (synchronises `stream`):
  * FD_OK, or FD_ERR_NONFINITE if a non-finite input or output was seen, or
- * FD_ERR_INVALID_ARG if a plan made with FD_B_ZERO received a non-zero b, or
- * FD_ERR_HIP if a batched sweep gave up waiting at a step barrier. */
+ * or FD_ERR_INVALID_ARG if a plan made with FD_B_ZERO received a non-zero b. */
 fd_status fd_device_status(fd_plan p, hipStream_t stream);
 
 /* ---- Total photon cutoff and probability-sum stopping -----------------

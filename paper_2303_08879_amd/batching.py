@@ -3,7 +3,7 @@ memory, and the autotuner of the batched sweep's scheduling knobs.
 
 A batch whose outputs and workspaces exceed the memory budget is packed into
 groups (first-fit decreasing by bytes) that each fit one arena; every group is
-one fock_diag_fwd_batch call, i.e. one persistent sweep launch.  Groups run one
+one fock_diag_fwd_batch call.  Groups run one
 after the other on the current stream and reuse the arena, so the outputs of a
 group are valid until the next group runs (``run(callback)`` hands each
 group's outputs to the caller in between).

@@ -10,7 +10,7 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libfockdiag.so")
 SOURCES = ["planner.cpp", "abi.cpp", "kernels_fwd.hip", "kernels_vjp.hip", "kernels_vjp_block.hip", "kernels_batch.hip", "kernels_state.hip",
-           "kernels_batch_md6.hip", "kernels_batch_md8.hip", "scratch.hip"]
+           "kernels_batch_level.hip", "scratch.hip"]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 # Packed FP32 instructions are disabled for every device pass.

@@ -642,7 +642,6 @@ fd_status fd_device_status(fd_plan p, hipStream_t stream) {
     return fail(FD_ERR_HIP, "reading the device status failed");
   if (h & 1) return fail(FD_ERR_NONFINITE, "non-finite value seen on the device");
   if (h & 2) return fail(FD_ERR_INVALID_ARG, "plan made with FD_B_ZERO received a non-zero b");
-  if (h & 4) return fail(FD_ERR_HIP, "a batched sweep gave up waiting at a step barrier (results invalid)");
   return ok();
 }
 

@@ -1,5 +1,5 @@
 // Per-unit device code of the forward sweep, shared by the per-circuit level
-// kernels and the batched persistent kernel.
+// kernels and the batched level kernels.
 //
 // One sweep step S handles every lattice point m with |m| = S of the detected
 // box.  At m it applies, in this order (Algorithm 1, Sec. 3.1.3; Algorithm 2,

@@ -1,26 +1,25 @@
 // Batched forward: prep and permutation kernels of a batch and the host-side
 // schedule (work items, per-circuit descriptors), cached per plan set and
-// pointer set.  The persistent sweep kernel itself is in batch_sweep.h.
+// pointer set.  The level kernels are in kernels_batch_level.hip.
 //
 // Launch sequence per batch: prep (+ undetected block fill), one workgroup
-// per circuit; the persistent sweep; the F0 -> rho permutation of every
-// circuit in one launch.
+// per circuit; one launch per class and step, the classes on side streams
+// next to the level launches of the circuits that fill the device; the
+// F0 -> rho permutation of every circuit in one launch.
 #include <algorithm>
 #include <cstring>
 #include <memory>
 #include <mutex>
 #include <numeric>
 
-#include "batch_sweep.h"
+#include "batch_level.h"
 
 namespace fd {
 
 // Prep of every circuit (one workgroup each), then step 1 of Algorithm 2 by
-// the first wavefront when the circuit has undetected modes.  Workgroup 0
-// also clears the sweep's control words (queue heads, barrier count).
+// the first wavefront when the circuit has undetected modes.
 template <typename R>
-__global__ __launch_bounds__(kThreads) void k_batch_prep(const BatchCirc<R>* __restrict__ circs, unsigned* ctl,
-                                                         int nctl) {
+__global__ __launch_bounds__(kThreads) void k_batch_prep(const BatchCirc<R>* __restrict__ circs) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
   const BatchCirc<R>* __restrict__ C = circs + blockIdx.x;
   cx<R>* Ai = load_global(&C->Ai);
@@ -28,8 +27,6 @@ __global__ __launch_bounds__(kThreads) void k_batch_prep(const BatchCirc<R>* __r
   const int npos = C->P.npos;
   prep_body<R>(load_global(&C->A), load_global(&C->b), load_global(&C->c), Ai, Ai + npos * npos,
                Ai + npos * npos + npos, f0, C->pa, load_global(&C->status));
-  if (blockIdx.x == 0)
-    for (int i = threadIdx.x; i < nctl; i += blockDim.x) ctl[i] = 0u;
   if (C->P.B == 1) return;
   __syncthreads();
   if (threadIdx.x < 64) {
@@ -94,6 +91,19 @@ __global__ __launch_bounds__(kThreads) void k_batch_out(const BatchCirc<R>* __re
 // ---------------------------------------------------------------------------
 namespace {
 
+// The circuits of one kernel instantiation and their launches, one per step.
+struct BatchClass {
+  int kind = 0, MD = 0, nq = 0, odd = 0;
+  std::vector<int> members;
+  double work = 0.0;
+  struct Step {
+    int i0 = 0, n = 0;                 // its items
+    size_t shm = 0;
+  };
+  std::vector<Step> steps;
+  int lane = 0;                        // stream it runs on
+};
+
 struct BatchSched {
   uint64_t id = 0;                      // unique per built schedule
   int device = -1;
@@ -102,20 +112,14 @@ struct BatchSched {
   void* d_circs = nullptr;
   void* d_items = nullptr;
   void* d_boff = nullptr;
-  void* d_steps = nullptr;             // step offsets into the item table
-  void* d_ctl = nullptr;               // queue heads of every step, then the barrier count
-  int nitems = 0, nsteps = 0;
+  std::vector<BatchClass> classes;     // largest work first
   int64_t out_blocks = 0;
-  BatchLds lds{};
-  size_t shm_prep = 0, shm_sweep = 0, shm_out = 0;
+  size_t shm_prep = 0, shm_out = 0;
   int out_pn_bytes = 0, out_slv_bytes = 0;
-  int grid = 0;
-  int mdmax = 8;
   uint64_t last_use = 0;
   std::vector<unsigned char> h_circs;   // host images kept alive for the asynchronous uploads
   std::vector<BatchItem> h_items;
   std::vector<int64_t> h_boff;
-  std::vector<int> h_steps;
 };
 
 std::mutex g_mu;
@@ -123,6 +127,17 @@ std::vector<BatchSched> g_cache;
 fd_batch_tuning g_tuning = {2, 64, 4, 2048, 0};
 
 fd_batch_tuning batch_tuning() { return g_tuning; }
+// side streams of a batched call (with the caller's, one per hardware queue)
+// and the workgroups that the device holds at once, about
+constexpr int kBatchLanes = 3;
+constexpr int64_t kBatchResident = 2048;
+
+// Whether the batched level kernels run this circuit: at most four block
+// coordinates (two undetected modes), rows and fill staged in LDS.  Others take
+// their own level launches.
+bool level_launch_takes(const Plan& Pl) {
+  return Pl.B == 1 || (Pl.nq <= 4 && !Pl.st_fwd && !Pl.st_ufill);
+}
 uint64_t g_clock = 0, g_sched_id = 0;
 constexpr size_t kBatchCache = 8;
 
@@ -134,10 +149,8 @@ void free_sched(BatchSched& s) {
   (void)hipFree(s.d_circs);
   (void)hipFree(s.d_items);
   (void)hipFree(s.d_boff);
-  (void)hipFree(s.d_steps);
-  (void)hipFree(s.d_ctl);
   (void)hipSetDevice(cur);
-  s.d_circs = s.d_items = s.d_boff = s.d_steps = s.d_ctl = nullptr;
+  s.d_circs = s.d_items = s.d_boff = nullptr;
 }
 
 size_t align16(size_t x) { return (x + 15) & ~size_t(15); }
@@ -148,30 +161,22 @@ fd_status build_sched(int n, Plan* const* plans, const bool* odd, const void* co
                  std::string* err) {
   const size_t eb = sizeof(cx<R>);
   std::vector<BatchCirc<R>> hc(n);
-  BatchLds lds{16, 0, 0, 4};
   int out_pn = 16;
   int64_t out_slv = 8;
   size_t ufill_lds = 0;
-  std::vector<double> work(n, 0.0);
   for (int i = 0; i < n; ++i) {
     const Plan& Pl = *plans[i];
     BatchCirc<R>& C = hc[i];
     std::memset(&C, 0, sizeof(C));
     C.P = make_devplan(Pl, odd[i]);
-    C.kind = Pl.B > 1 ? 1 : 0;
-    if (Pl.nq > 4) {
-      *err = "the batched sweep runs at most two undetected modes";
+    if (!level_launch_takes(Pl)) {
+      *err = "internal error: a circuit that the batched level kernels do not take";
       return FD_ERR_UNSUPPORTED;
-    }
-    if (C.kind) {
-      C.G = chunk_geo(Pl);
-      C.Gh = chunk_geo(Pl, kBT / 2);
     }
     for (int p = 0; p < Pl.npos; ++p) C.pa.pos2blk[p] = Pl.pos2blk[p];
     C.pa.npos = Pl.npos;
     C.pa.M2 = 2 * Pl.M;
     C.pa.check_b_zero = Pl.flags == FD_B_ZERO ? 1 : 0;
-    C.steps = Pl.MD > 0 ? Pl.smax + 1 : 0;
     C.wmax = Pl.wmax;
     const FwdLayout Lw = fwd_layout(Pl, odd[i], false, 0);
     char* w = static_cast<char*>(ws[i]);
@@ -192,123 +197,94 @@ fd_status build_sched(int n, Plan* const* plans, const bool* odd, const void* co
     C.out_elems = Pl.out_elems;
     C.N = Pl.nodes_total;
     const int pnb = (int)align16((size_t)(Pl.MD + 1) * (Pl.smax + 3) * sizeof(int));
-    lds.pn_bytes = std::max(lds.pn_bytes, pnb);
     out_pn = std::max(out_pn, pnb);
     out_slv = std::max<int64_t>(out_slv, (int64_t)(Pl.smax + 2) * 8);
-    if (C.kind) {
-      lds.sa_bytes = std::max(lds.sa_bytes, (int)align16((size_t)Pl.npos * (Pl.npos + 1) * eb));
-      ufill_lds = std::max(ufill_lds, ufill_lds_bytes(Pl, false));
+    if (Pl.B > 1) ufill_lds = std::max(ufill_lds, ufill_lds_bytes(Pl, false));
+    if (Pl.MD == 0) continue;
+    double work = 0.0;
+    for (int s = 0; s <= Pl.smax; ++s) work += (double)Pl.ncnt[s] * Pl.B * Pl.npos * Pl.npos;
+    const int kind = Pl.B > 1 ? 1 : 0, nq = kind ? Pl.nq : 0, od = kind ? 1 : (odd[i] ? 1 : 0);
+    auto it = std::find_if(S->classes.begin(), S->classes.end(), [&](const BatchClass& k) {
+      return k.kind == kind && k.MD == Pl.MD && k.nq == nq && k.odd == od;
+    });
+    if (it == S->classes.end()) {
+      BatchClass k;
+      k.kind = kind;
+      k.MD = Pl.MD;
+      k.nq = nq;
+      k.odd = od;
+      S->classes.push_back(k);
+      it = S->classes.end() - 1;
     }
-    for (int s = 0; s < C.steps; ++s) work[i] += (double)Pl.ncnt[s] * Pl.B;
+    it->members.push_back(i);
+    it->work += work;
   }
-  // per-wave bytes: PN, A/b, then the block unit rows (largest circuit): a
-  // unit of chunk geometry G touches F0 rows [k0-2, k1) and MD bridge pivot
-  // blocks of rows [k0-1, k1) (fwd_block_unit), for either of the circuit's
-  // two geometries (full- and half-height chunks)
-  size_t rows = 0;
-  auto unit_rows = [&](const ChunkGeo& G, int MD) {
-    return ((size_t)(G.RC + 2) + (size_t)MD * (G.RC + 1)) * G.R0 * eb;
-  };
-  for (int i = 0; i < n; ++i)
-    if (hc[i].kind) rows = std::max({rows, unit_rows(hc[i].G, hc[i].P.MD), unit_rows(hc[i].Gh, hc[i].P.MD)});
-  lds.wave_bytes = (int)align16((size_t)lds.pn_bytes + lds.sa_bytes + rows);
-  lds.waves = 4;
-  while (lds.waves > 1 && kTabBytes + (size_t)lds.waves * lds.wave_bytes > kMaxLds) --lds.waves;
-  if (kTabBytes + (size_t)lds.wave_bytes > kMaxLds || ufill_lds > kMaxLds) {
-    *err = "a circuit's undetected block is too large for the batched sweep's LDS staging";
-    return FD_ERR_UNSUPPORTED;
-  }
-  S->lds = lds;
-  S->shm_sweep = kTabBytes + (size_t)lds.waves * lds.wave_bytes;
   S->shm_prep = ufill_lds;
   S->out_pn_bytes = out_pn;
   S->out_slv_bytes = (int)align16((size_t)out_slv);
   S->shm_out = (size_t)out_pn + S->out_slv_bytes + (size_t)kOutTN * (kOutTK + 1) * eb;
 
-  // persistent grid: every workgroup that fits at once
-  bool small = true;   // within the (6, 5, 2) build
-  for (int i = 0; i < n; ++i)
-    small = small && (hc[i].kind ? (hc[i].P.MD <= 5 && hc[i].P.nq <= 2) : hc[i].P.MD <= 6);
-  S->mdmax = small ? 6 : 8;
   if (S->shm_prep > 65536 &&
       hipFuncSetAttribute(reinterpret_cast<const void*>(&k_batch_prep<R>), hipFuncAttributeMaxDynamicSharedMemorySize,
                           (int)S->shm_prep) != hipSuccess) {
     *err = "hipFuncSetAttribute failed";
     return FD_ERR_HIP;
   }
-  int per_cu = 0, cus = 0, dev = 0;
+  int dev = 0;
   (void)hipGetDevice(&dev);
-  BatchSweepArgs qa{};
-  qa.lds = lds;
-  qa.shm = S->shm_sweep;
-  const bool c64 = sizeof(R) == 4;
-  const hipError_t qe = S->mdmax == 6 ? batch_sweep_md6(c64, &qa, &per_cu, nullptr)
-                                      : batch_sweep_md8(c64, &qa, &per_cu, nullptr);
-  if (qe == hipSuccess && per_cu == -1) {
-    *err = "the batched sweep kernel was built with scratch memory; refusing its cooperative launch";
-    return FD_ERR_UNSUPPORTED;
-  }
-  if (qe != hipSuccess || hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
-      per_cu < 1) {
-    *err = "occupancy query for the batched sweep failed (" + std::string(hipGetErrorString(qe)) +
-           ", workgroups per CU " + std::to_string(per_cu) + ", LDS bytes " + std::to_string(S->shm_sweep) +
-           ", wavefronts per workgroup " + std::to_string(lds.waves) + ")";
-    return FD_ERR_HIP;
-  }
-  int coop = 0;
-  if (hipDeviceGetAttribute(&coop, hipDeviceAttributeCooperativeLaunch, dev) != hipSuccess || !coop) {
-    *err = "the device does not support cooperative launches";
-    return FD_ERR_UNSUPPORTED;
-  }
-  S->grid = per_cu * cus;
-  const int64_t waves = (int64_t)S->grid * lds.waves;
-
-  // work items, step-major; within a step larger circuits first, each step
-  // of a circuit cut into items of units / (items_per_wave x wavefronts)
-  // units, at least min_block_units / min_point_units
+  // work items: every step of a circuit in workgroups of whole units, one
+  // (lattice point, chunk) unit or kThreads lattice points each unless the
+  // step has more than items_per_wave x kBatchResident of them
   const fd_batch_tuning T = batch_tuning();
-  std::vector<int> order(n);
-  std::iota(order.begin(), order.end(), 0);
-  std::stable_sort(order.begin(), order.end(), [&](int x, int y) { return work[x] > work[y]; });
-  int max_steps = 0;
-  for (int i = 0; i < n; ++i) max_steps = std::max(max_steps, hc[i].steps);
-  const int64_t div = std::max<int64_t>(1, (int64_t)T.items_per_wave * waves);
+  std::stable_sort(S->classes.begin(), S->classes.end(),
+                   [](const BatchClass& x, const BatchClass& y) { return x.work > y.work; });
   S->h_items.clear();
-  S->h_steps.assign(1, 0);
-  for (int s = 0; s < max_steps; ++s) {
-    for (int i : order) {
-      if (s >= hc[i].steps) continue;
-      const int64_t pts = plans[i]->ncnt[s];
-      if (pts <= 0) continue;
-      const bool half = hc[i].kind && pts * hc[i].G.nchunks < kSmallLevelUnits;
-      const int64_t units = hc[i].kind ? pts * (half ? hc[i].Gh.nchunks : hc[i].G.nchunks) : pts;
-      int64_t per = std::max<int64_t>(hc[i].kind ? T.min_block_units : T.min_point_units, (units + div - 1) / div);
-      if (!hc[i].kind) per = (per + 63) / 64 * 64;   // whole wavefronts of lattice points
-      if (units > 0x7fffffff) {
-        *err = "a step of circuit " + std::to_string(i) + " has too many units for one work item table";
-        return FD_ERR_UNSUPPORTED;
-      }
-      for (int64_t u0 = 0; u0 < units; u0 += per) {
+  for (BatchClass& k : S->classes) {
+    int max_steps = 0;
+    for (int i : k.members) max_steps = std::max(max_steps, plans[i]->smax + 1);
+    k.steps.assign(max_steps, BatchClass::Step());
+    for (int s = 0; s < max_steps; ++s) {
+      BatchClass::Step& st_ = k.steps[s];
+      st_.i0 = (int)S->h_items.size();
+      for (int i : k.members) {
+        const Plan& Pl = *plans[i];
+        if (s > Pl.smax || Pl.ncnt[s] <= 0) continue;
+        const int64_t pts = Pl.ncnt[s];
         BatchItem I;
         std::memset(&I, 0, sizeof(I));
         I.circ = i;
-        I.step = s;
-        I.u0 = (int)u0;
-        I.u1 = (int)std::min(units, u0 + per);
-        I.half = half ? 1 : 0;
-        // an item covers whole units of its own geometry: (lattice point, chunk)
-        // pairs below pts x nchunks, or lattice points below pts
-        if (I.u0 < 0 || I.u1 <= I.u0 || I.u1 > units) {
-          *err = "internal error: batch work item outside its step's units";
-          return FD_ERR_HIP;
+        int64_t units = pts, per;
+        if (k.kind) {
+          const ChunkGeo G = fwd_geo(Pl, pts);
+          I.RC = G.RC;
+          I.nchunks = G.nchunks;
+          units = pts * G.nchunks;
+          per = std::max<int64_t>((T.min_block_units + 1) / 2, units / ((int64_t)T.items_per_wave * kBatchResident));
+          st_.shm = std::max(st_.shm, fwd_lds_bytes_for(Pl, G));
+        } else {
+          per = std::max<int64_t>({kThreads, T.min_point_units, units / ((int64_t)T.items_per_wave * kBatchResident)});
+          per = (per + kThreads - 1) / kThreads * kThreads;
+          st_.shm = std::max(st_.shm, 2 * (kMaxCut + 4) * sizeof(R) + (size_t)(Pl.MD + 1) * (Pl.smax + 3) * sizeof(int));
         }
-        S->h_items.push_back(I);
+        if (units > 0x7fffffff) {
+          *err = "a step of circuit " + std::to_string(i) + " has too many units for one work item table";
+          return FD_ERR_UNSUPPORTED;
+        }
+        for (int64_t u0 = 0; u0 < units; u0 += per) {
+          I.u0 = (int)u0;
+          I.u1 = (int)std::min(units, u0 + per);
+          S->h_items.push_back(I);
+        }
       }
+      st_.n = (int)S->h_items.size() - st_.i0;
     }
-    S->h_steps.push_back((int)S->h_items.size());
   }
-  S->nsteps = max_steps;
-  S->nitems = (int)S->h_items.size();
+  // streams: largest class first, each to the stream with the least work
+  double load[kBatchLanes] = {};
+  for (BatchClass& k : S->classes) {
+    k.lane = (int)(std::min_element(load, load + kBatchLanes) - load);
+    load[k.lane] += k.work;
+  }
   // permutation blocks
   S->h_boff.assign(n + 1, 0);
   for (int i = 0; i < n; ++i) {
@@ -328,20 +304,16 @@ fd_status build_sched(int n, Plan* const* plans, const bool* odd, const void* co
   S->device = dev;
   if (hipMalloc(&S->d_circs, S->h_circs.size()) != hipSuccess ||
       hipMalloc(&S->d_items, std::max<size_t>(1, S->h_items.size()) * sizeof(BatchItem)) != hipSuccess ||
-      hipMalloc(&S->d_boff, S->h_boff.size() * sizeof(int64_t)) != hipSuccess ||
-      hipMalloc(&S->d_steps, S->h_steps.size() * sizeof(int)) != hipSuccess ||
-      hipMalloc(&S->d_ctl, ((size_t)S->nsteps + 1) * sizeof(unsigned)) != hipSuccess) {
+      hipMalloc(&S->d_boff, S->h_boff.size() * sizeof(int64_t)) != hipSuccess) {
     free_sched(*S);
     *err = "device allocation of the batch schedule failed";
     return FD_ERR_OOM;
   }
   if (hipMemcpyAsync(S->d_circs, S->h_circs.data(), S->h_circs.size(), hipMemcpyHostToDevice, st) != hipSuccess ||
-      (S->nitems > 0 && hipMemcpyAsync(S->d_items, S->h_items.data(), S->h_items.size() * sizeof(BatchItem),
+      (!S->h_items.empty() && hipMemcpyAsync(S->d_items, S->h_items.data(), S->h_items.size() * sizeof(BatchItem),
                                        hipMemcpyHostToDevice, st) != hipSuccess) ||
       hipMemcpyAsync(S->d_boff, S->h_boff.data(), S->h_boff.size() * sizeof(int64_t), hipMemcpyHostToDevice,
-                     st) != hipSuccess ||
-      hipMemcpyAsync(S->d_steps, S->h_steps.data(), S->h_steps.size() * sizeof(int), hipMemcpyHostToDevice, st) !=
-          hipSuccess) {
+                     st) != hipSuccess) {
     free_sched(*S);
     *err = "upload of the batch schedule failed";
     return FD_ERR_HIP;
@@ -349,37 +321,66 @@ fd_status build_sched(int n, Plan* const* plans, const bool* odd, const void* co
   return FD_OK;
 }
 
+// Side streams of a batched call and the events that order them after the
+// caller's stream and it after them, per device, kept until the process ends.
+// Used under g_mu; a call that finds earlier work on a side stream queues
+// behind it.
+struct BatchLanes {
+  hipStream_t s[kBatchLanes] = {};
+  hipEvent_t fork = nullptr, join[kBatchLanes] = {};
+};
+BatchLanes g_lanes[64];
+
+hipError_t batch_lanes(int dev, BatchLanes** out) {
+  BatchLanes& L = g_lanes[dev];
+  hipError_t e = hipSuccess;
+  if (!L.fork) e = hipEventCreateWithFlags(&L.fork, hipEventDisableTiming);
+  for (int k = 0; k < kBatchLanes && e == hipSuccess; ++k) {
+    if (!L.s[k]) e = hipStreamCreateWithFlags(&L.s[k], hipStreamNonBlocking);
+    if (e == hipSuccess && !L.join[k]) e = hipEventCreateWithFlags(&L.join[k], hipEventDisableTiming);
+  }
+  *out = &L;
+  return e;
+}
+
+// The steps of the classes of one stream, class by class.
 template <typename R>
-hipError_t launch_batch(const BatchSched& S, int n, const Plan& P0, hipStream_t st) {
-  const BatchCirc<R>* circs = static_cast<const BatchCirc<R>*>(S.d_circs);
-  unsigned* ctl = static_cast<unsigned*>(S.d_ctl);
-  {
-    KTimer kt(P0, KK_BATCH_PREP, st);
-    hipLaunchKernelGGL((k_batch_prep<R>), dim3(n), dim3(kThreads), S.shm_prep, st, circs, ctl, S.nsteps + 1);
+hipError_t launch_lane(const BatchSched& S, int lane, hipStream_t st) {
+  for (const BatchClass& k : S.classes) {
+    if (k.lane != lane) continue;
+    for (size_t s = 0; s < k.steps.size(); ++s) {
+      if (k.steps[s].n == 0) continue;
+      BatchLaunch a{};
+      a.kind = k.kind;
+      a.MD = k.MD;
+      a.nq = k.nq;
+      a.odd = k.odd;
+      a.circs = S.d_circs;
+      a.items = static_cast<const BatchItem*>(S.d_items) + k.steps[s].i0;
+      a.nitems = k.steps[s].n;
+      a.S = (int)s;
+      a.shm = k.steps[s].shm;
+      const hipError_t e = launch_batch_level<R>(a, st);
+      if (e != hipSuccess) return e;
+    }
   }
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  if (S.nitems > 0) {
-    KTimer kt(P0, KK_BATCH_SWEEP, st);
-    BatchSweepArgs a{};
-    a.circs = circs;
-    a.items = S.d_items;
-    a.step_off = static_cast<const int*>(S.d_steps);
-    a.nsteps = S.nsteps;
-    a.ctl = ctl;
-    a.status = P0.d_status;
-    a.lds = S.lds;
-    a.grid = S.grid;
-    a.shm = S.shm_sweep;
-    const bool c64 = sizeof(R) == 4;
-    e = S.mdmax == 6 ? batch_sweep_md6(c64, &a, nullptr, st) : batch_sweep_md8(c64, &a, nullptr, st);
-    if (e != hipSuccess) return e;
-  }
-  {
-    KTimer kt(P0, KK_BATCH_OUT, st);
-    hipLaunchKernelGGL((k_batch_out<R>), dim3((unsigned)S.out_blocks), dim3(kThreads), S.shm_out, st, circs,
-                       static_cast<const int64_t*>(S.d_boff), n, S.out_pn_bytes, S.out_slv_bytes);
-  }
+  return hipSuccess;
+}
+
+template <typename R>
+hipError_t launch_batch_prep(const BatchSched& S, int n, const Plan& P0, hipStream_t st) {
+  KTimer kt(P0, KK_BATCH_PREP, st);
+  hipLaunchKernelGGL((k_batch_prep<R>), dim3(n), dim3(kThreads), S.shm_prep, st,
+                     static_cast<const BatchCirc<R>*>(S.d_circs));
+  return hipGetLastError();
+}
+
+template <typename R>
+hipError_t launch_batch_out(const BatchSched& S, int n, const Plan& P0, hipStream_t st) {
+  KTimer kt(P0, KK_BATCH_OUT, st);
+  hipLaunchKernelGGL((k_batch_out<R>), dim3((unsigned)S.out_blocks), dim3(kThreads), S.shm_out, st,
+                     static_cast<const BatchCirc<R>*>(S.d_circs), static_cast<const int64_t*>(S.d_boff), n,
+                     S.out_pn_bytes, S.out_slv_bytes);
   return hipGetLastError();
 }
 
@@ -399,36 +400,9 @@ static bool fills_device(const Plan& Pl, double fill_waves) {
   return units / (Pl.smax + 1) >= fill_waves;
 }
 
-// The persistent sweep runs blocks of at most four coordinates (two
-// undetected modes) whose unit rows and fill fit its LDS staging; other
-// circuits take their own level launches.
-// Per-wave LDS parts of a circuit in the sweep (as build_sched lays them
-// out): its PN table, A and b, its block unit rows.
-struct WaveParts {
-  size_t pn = 0, sa = 0, rows = 0;
-};
-static WaveParts wave_parts(const Plan& Pl) {
-  const size_t eb = elem_bytes(Pl.dt);
-  WaveParts w;
-  w.pn = align16((size_t)(Pl.MD + 1) * (Pl.smax + 3) * sizeof(int));
-  if (Pl.B > 1) {
-    w.sa = align16((size_t)Pl.npos * (Pl.npos + 1) * eb);
-    for (const ChunkGeo& G : {chunk_geo(Pl), chunk_geo(Pl, kBT / 2)})
-      w.rows = std::max(w.rows, ((size_t)(G.RC + 2) + (size_t)Pl.MD * (G.RC + 1)) * G.R0 * eb);
-  }
-  return w;
-}
-static bool sweep_takes(const Plan& Pl) {
-  if (Pl.B == 1) return true;
-  if (Pl.nq > 4) return false;
-  const WaveParts w = wave_parts(Pl);
-  return kTabBytes + align16(w.pn + w.sa + w.rows) <= kMaxLds && ufill_lds_bytes(Pl, false) <= kMaxLds;
-}
-
 namespace {
 
-// A batched call captured into a graph: the level launches of the circuits
-// that fill the device, then the persistent sweep's three launches.
+// A batched call captured into a graph.
 struct BatchGraph {
   int device = -1;
   uint64_t sched = 0;                // schedule whose device tables the graph's kernels read (0: none)
@@ -486,7 +460,7 @@ std::vector<uint64_t> batch_key(int n, Plan* const* plans, const bool* odd, cons
   return key;
 }
 
-// The schedule of the persistent sweep over these circuits, built and
+// The schedule of the level launches over these circuits, built and
 // uploaded on `st` on first use.  Caller holds g_mu.
 fd_status sweep_sched(int n, Plan* const* plans, const bool* odd, const void* const* A, const void* const* b,
                       const void* const* c, void* const* rho, void* const* ws, const fd_batch_tuning& T,
@@ -524,45 +498,65 @@ struct Split {
 Split split_batch(int n, Plan* const* plans, const fd_batch_tuning& T) {
   Split sp;
   for (int i = 0; i < n; ++i)
-    (fills_device(*plans[i], (double)T.fill_waves) || !sweep_takes(*plans[i]) ? sp.big : sp.small).push_back(i);
-  // one wave's LDS holds the largest PN table, A/b and unit rows of all
-  // members together: while they do not fit, the member with the most unit
-  // rows leaves the sweep
-  for (;;) {
-    WaveParts mx;
-    int worst = -1;
-    size_t worst_rows = 0;
-    for (size_t k = 0; k < sp.small.size(); ++k) {
-      const WaveParts w = wave_parts(*plans[sp.small[k]]);
-      mx.pn = std::max(mx.pn, w.pn);
-      mx.sa = std::max(mx.sa, w.sa);
-      mx.rows = std::max(mx.rows, w.rows);
-      if (worst < 0 || w.rows + w.sa > worst_rows) {
-        worst = (int)k;
-        worst_rows = w.rows + w.sa;
-      }
-    }
-    if (worst < 0 || kTabBytes + align16(mx.pn + mx.sa + mx.rows) <= kMaxLds) break;
-    sp.big.push_back(sp.small[worst]);
-    sp.small.erase(sp.small.begin() + worst);
-  }
+    (fills_device(*plans[i], (double)T.fill_waves) || !level_launch_takes(*plans[i]) ? sp.big : sp.small).push_back(i);
   return sp;
 }
 
-// Enqueues the whole batched call on `st`: the circuits that fill the device
-// (or that the sweep cannot stage) with their own level launches, then the
-// sweep over the others (its schedule `S`, built beforehand).
+// Enqueues the whole batched call on `st`: prep of the batched circuits, then
+// their classes on the side streams while `st` runs the level launches of the
+// circuits that fill the device (or that the batched kernels do not take), then
+// the permutation.  `st` waits for the side streams before it goes on, so
+// everything the call touches is ordered on `st`.
+template <typename R>
+hipError_t enqueue_batch_t(const Split& sp, Plan* const* plans, const bool* odd, const void* const* A,
+                           const void* const* b, const void* const* c, void* const* rho, void* const* ws,
+                           const BatchSched* S, hipStream_t st) {
+  hipError_t e = hipSuccess;
+  auto big = [&]() -> hipError_t {
+    for (int i : sp.big) {
+      const hipError_t x = run_forward(*plans[i], odd[i], A[i], b[i], c[i], rho[i], ws[i], nullptr, st);
+      if (x != hipSuccess) return x;
+    }
+    return hipSuccess;
+  };
+  if (!S) return big();
+  const int n = (int)sp.small.size();
+  const Plan& P0 = *plans[sp.small[0]];
+  if ((e = launch_batch_prep<R>(*S, n, P0, st)) != hipSuccess) return e;
+  BatchLanes* L = nullptr;
+  if ((e = batch_lanes(S->device, &L)) != hipSuccess) return e;
+  bool used[kBatchLanes] = {};
+  for (const BatchClass& k : S->classes) used[k.lane] = true;
+  {
+    KTimer kt(P0, KK_BATCH_SWEEP, st);
+    if ((e = hipEventRecord(L->fork, st)) != hipSuccess) return e;
+    hipError_t bad = hipSuccess;
+    for (int k = 0; k < kBatchLanes; ++k)
+      if (used[k] && bad == hipSuccess) bad = hipStreamWaitEvent(L->s[k], L->fork, 0);
+      else used[k] = false;
+    // the large circuits first: the device works on them while the host
+    // enqueues the others
+    if (bad == hipSuccess) bad = big();
+    for (int k = 0; k < kBatchLanes; ++k)
+      if (used[k] && bad == hipSuccess) bad = launch_lane<R>(*S, k, L->s[k]);
+    // every stream that was forked is joined, also after an error
+    for (int k = 0; k < kBatchLanes; ++k)
+      if (used[k]) {
+        e = hipEventRecord(L->join[k], L->s[k]);
+        if (e == hipSuccess) e = hipStreamWaitEvent(st, L->join[k], 0);
+        if (bad == hipSuccess) bad = e;
+      }
+    if (bad != hipSuccess) return bad;
+  }
+  return launch_batch_out<R>(*S, n, P0, st);
+}
+
 hipError_t enqueue_batch(const Split& sp, Plan* const* plans, const bool* odd, const void* const* A,
                          const void* const* b, const void* const* c, void* const* rho, void* const* ws,
                          const BatchSched* S, hipStream_t st) {
-  for (int i : sp.big) {
-    const hipError_t e = run_forward(*plans[i], odd[i], A[i], b[i], c[i], rho[i], ws[i], nullptr, st);
-    if (e != hipSuccess) return e;
-  }
-  if (!S) return hipSuccess;
-  const Plan& P0 = *plans[sp.small[0]];
-  return P0.dt == FD_C64 ? launch_batch<float>(*S, (int)sp.small.size(), P0, st)
-                         : launch_batch<double>(*S, (int)sp.small.size(), P0, st);
+  const bool c64 = !sp.small.empty() && plans[sp.small[0]]->dt == FD_C64;
+  return c64 ? enqueue_batch_t<float>(sp, plans, odd, A, b, c, rho, ws, S, st)
+             : enqueue_batch_t<double>(sp, plans, odd, A, b, c, rho, ws, S, st);
 }
 
 }  // namespace
@@ -574,7 +568,7 @@ fd_status run_forward_batch(int n, Plan* const* plans, const bool* odd, const vo
   std::lock_guard<std::mutex> lock(g_mu);
   const fd_batch_tuning T = g_tuning;
   const Split sp = split_batch(n, plans, T);
-  // the sweep's members, as arrays of their own
+  // the batched members, as arrays of their own
   const size_t m = sp.small.size();
   std::vector<Plan*> p2(m);
   std::unique_ptr<bool[]> o2(new bool[m > 0 ? m : 1]);
@@ -602,12 +596,13 @@ fd_status run_forward_batch(int n, Plan* const* plans, const bool* odd, const vo
     *err = std::string("kernel launch failed: ") + hipGetErrorString(e);
     return FD_ERR_HIP;
   };
+  int dev = 0;
+  (void)hipGetDevice(&dev);
+  if (dev < 0 || dev >= 64) return fail_hip(hipErrorInvalidDevice);
   if (T.use_graph <= 0 || g_graph_failed || timing) {
     const hipError_t e = enqueue_batch(sp, plans, odd, A, b, c, rho, ws, S, st);
     return e == hipSuccess ? FD_OK : fail_hip(e);
   }
-  int dev = 0;
-  (void)hipGetDevice(&dev);
   std::vector<uint64_t> key = batch_key(n, plans, odd, A, b, c, rho, ws, T);
   for (BatchGraph& g : g_graphs)
     if (g.key == key) {
@@ -616,7 +611,6 @@ fd_status run_forward_batch(int n, Plan* const* plans, const bool* odd, const vo
       return e == hipSuccess ? FD_OK : fail_hip(e);
     }
   hipError_t e;
-  if (dev < 0 || dev >= 64) return fail_hip(hipErrorInvalidDevice);
   if (!g_capture[dev] && (e = hipStreamCreateWithFlags(&g_capture[dev], hipStreamNonBlocking)) != hipSuccess)
     return fail_hip(e);
   hipStream_t cs = g_capture[dev];
@@ -631,8 +625,7 @@ fd_status run_forward_batch(int n, Plan* const* plans, const bool* odd, const vo
   }
   (void)hipGetLastError();
   if (!captured) {
-    // the runtime would not capture (cooperative launches, for one): run
-    // this and later calls eagerly
+    // the runtime would not capture: run this and later calls eagerly
     if (exec) (void)hipGraphExecDestroy(exec);
     if (graph) (void)hipGraphDestroy(graph);
     g_graph_failed = true;
