@@ -292,7 +292,7 @@ fd_status fock_diag_vjp_batch(int n, const fd_plan* plans, const void* const* A,
  *              every step of a circuit is cut into workgroups of units /
  *              (items_per_wave x 2048) units, at least min_block_units / 2
  *              (lattice point, row chunk) units (Algorithm 2) or
- *              max(256, min_point_units) lattice points (Algorithm 1);
+ *              max(64, min_point_units) lattice points (Algorithm 1);
  *   fill_waves a circuit whose levels average at least fill_waves
  *              wavefront-sized units runs its own level launches instead of
  *              joining the batched ones;

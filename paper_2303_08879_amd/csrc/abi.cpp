@@ -169,6 +169,8 @@ fd_status fd_plan_destroy(fd_plan p) {
     (void)hipFree(P.d_elist);
     (void)hipFree(P.d_woff);
     (void)hipFree(P.d_node);
+    (void)hipFree(P.d_sqt);
+    (void)hipFree(P.d_mtab);
     (void)hipFree(P.d_mass);
     (void)hipSetDevice(cur);
   }

@@ -35,6 +35,7 @@ struct BatchCirc {
   const cx<R>* b;
   const cx<R>* c;
   cx<R>* rho;
+  const uint64_t* mtab;        // digits of the lattice points (Algorithm 1), may be null
   const int* elist;
   const int* woff;
   int* status;

@@ -149,6 +149,12 @@ struct LevelPtrs {
   const int* node;
 };
 
+// One forward level of a plan with every mode detected (kernels_point.hip); dT
+// != 0: with tangents, dT bytes after the values (odd levels swept).
+template <typename R>
+hipError_t launch_fwd_point_level(const Plan& Pl, const DevPlan& P, bool odd, int S, const LevelPtrs<R>& L,
+                                  const cx<R>* A, const cx<R>* b, int nwork, hipStream_t st, int64_t dT = 0);
+
 // Node record of lattice point r of the level: m, the ranks of m - 1_j at
 // level S-1 and of m + 1_j at level S+1 (one scalar load per unit).
 template <int MD>

@@ -55,8 +55,11 @@ constexpr int kFwdWaves = 4;             // wavefronts per workgroup of the bloc
 constexpr int kFwdChunk = 448;           // own entries of one of its (lattice point, row chunk) units,
 constexpr int kFwdChunkSmall = 192;      // on levels with fewer than kSmallLevelUnits units
 constexpr int kNodeStride = 3 * kMaxD;   // ints per node record: m, rank(m - 1_j), rank(m + 1_j)
-constexpr int kPointBatch = 32;          // Abar records per LDS staging batch, point reverse kernel
-constexpr int kBlockBatch = 32;          // the same, block reverse kernel
+constexpr int64_t kMaxDigitTable = 1 << 20;   // lattice points: 8 MB of digits, a few ms of host work
+// Points of a level from which the point kernels rank 64 points per wavefront
+// (a quarter of the rank work) instead of 16 (four times the wavefronts).
+constexpr int kPointTileMin = 65536;
+constexpr int kBlockBatch = 32;          // Abar records per LDS staging batch, block reverse kernel
 constexpr int kVjpSlots = 16384;         // reduction slots of the state-vector cotangents
 
 enum FamType { F_F0 = 0, F_F1K, F_F1B, F_F2, F_1010, F_1001 };
@@ -83,6 +86,7 @@ struct DevPlan {
   int ustride[kMaxUq];
   double uinv[kMaxUq];       // 1 / ustride (exact coordinate split, see ucoord)
   double cinv[kMaxD];        // 1 / CD (exact digit split of C-order indices, see node_of_cindex)
+  const void* sqt;           // sqrt(v), then 1 / sqrt(v), v = 0..kMaxCut + 3, in the plan's precision
   const int* pn;             // [(MD+1) x pnw]: PN[d][s+1] = #points of sub-box d with sum <= s
   const int64_t* lvl;        // [(MD) x (smax+2)]: node offset of level S for group g (store-all)
   const int* node;           // Algorithm 2 plans: node records in level-major order (else null)
@@ -156,6 +160,8 @@ struct Plan {
   int* d_pn = nullptr;
   int64_t* d_lvl = nullptr;
   int* d_node = nullptr;             // node records (Algorithm 2 plans)
+  void* d_sqt = nullptr;             // square-root tables
+  uint64_t* d_mtab = nullptr;        // digits of every lattice point in node order (Algorithm 1 plans of at most kMaxDigitTable points)
   double* d_mass = nullptr;          // per-level probability masses (stopping rule)
   int* d_status = nullptr;
   // undetected-block fill order (step 1 of Algorithm 2): entries sorted by weight

@@ -185,123 +185,6 @@ __device__ __forceinline__ void load_tables(const DevPlan& P, int* spn, R* sq, R
 }
 
 // ---------------------------------------------------------------------------
-// Algorithm 1 (every mode detected): one thread per lattice point.
-// ---------------------------------------------------------------------------
-template <int MD, bool ODD, typename R, typename LP>
-__device__ __forceinline__ void fwd_point_unit(const DevPlan& P, const LP& L, const cx<R>* __restrict__ Ai,
-                                               const cx<R>* __restrict__ bi, const int* spn, const R* sq,
-                                               const R* isq, int S, int r) {
-  constexpr int NP = 2 * MD;
-  const int pnw = P.pnw;
-  int m[MD], s[MD + 1], rdn[MD], rup[MD];
-  unrank<MD>(spn, pnw, P.CD, S, r, m, s);
-  neighbour_ranks<MD>(spn, pnw, s, rdn, rup);
-
-  // the point's own F0 entry: always valid, the address that neighbour loads
-  // of absent neighbours read instead (their value is then discarded), so
-  // every load is issued unconditionally and a pivot's loads share one wait
-  const cx<R>* own = at32(L.f0cur, (uint32_t)r);
-  const cx<R> g0 = ld(own);
-  cx<R> yk[MD];
-#pragma unroll
-  for (int K = 0; K < MD; ++K) yk[K] = czero<R>();
-
-  if (ODD && m[0] <= P.CD[0] - 2) {
-    // diagonal pivot d(m): reads d(m) - 1_l, writes d(m) + 1_i (type-1 offsets)
-    cx<R> x[NP];
-#pragma unroll
-    for (int j = 0; j < MD; ++j) {
-      const bool h = m[j] > 0;
-      const cx<R> vb = ld(h ? at32(L.rd[fam_f1b(MD, j)], (uint32_t)rdn[j]) : own);   // d(m)-1_ket(j) = F1b(j)(m-1_j)
-      const cx<R> vk = ld(h ? at32(L.rd[fam_f1k(j)], (uint32_t)rdn[j]) : own);      // d(m)-1_bra(j) = F1k(j)(m-1_j)
-      x[2 * j] = cscale(h ? vb : czero<R>(), sq[m[j]]);
-      x[2 * j + 1] = cscale(h ? vk : czero<R>(), sq[m[j]]);
-    }
-#pragma unroll
-    for (int j = 0; j < MD; ++j) {
-#pragma unroll
-      for (int side = 0; side < 2; ++side) {
-        const int i = 2 * j + side;
-        cx<R> acc = czero<R>();
-        cfma(acc, ld(bi + i), g0);
-#pragma unroll
-        for (int l = 0; l < NP; ++l) cfma(acc, ld(Ai + i * NP + l), x[l]);
-        acc = cscale(acc, isq[m[j] + 1]);
-        if (side == 0) {
-          yk[j] = acc;
-          if (j == 0 || m[j] <= P.CD[j] - 2) {
-            cx<R>* dst = at32(L.wr[fam_f1k(j)], (uint32_t)r);
-            st(dst, acc);
-            count_write(P, dst);
-          }
-        } else {
-          const bool ok = (j == 0) ? (m[0] <= P.CD[0] - 3) : (m[j] <= P.CD[j] - 2);
-          if (ok) {
-            cx<R>* dst = at32(L.wr[fam_f1b(MD, j)], (uint32_t)r);
-            st(dst, acc);
-            count_write(P, dst);
-          }
-        }
-      }
-    }
-  }
-
-  int K0 = MD;
-#pragma unroll
-  for (int d = MD - 1; d >= 0; --d)
-    if (m[d] > 0) K0 = d;
-#pragma unroll
-  for (int K = 0; K < MD; ++K) {
-    if (K > K0) break;
-    if (m[K] > P.CD[K] - 2) continue;
-    // pivot p = d(m) + 1_ket(K): reads p - 1_l for l >= ket(K)
-    cx<R> x[NP];
-    x[2 * K] = cscale(g0, sq[m[K] + 1]);                                    // p - 1_ket(K) = d(m)
-    {
-      const bool h = m[K] > 0;
-      const cx<R> v = ld(h ? at32(L.rd[fam_f2(MD, K)], (uint32_t)rdn[K]) : own);
-      x[2 * K + 1] = cscale(h ? v : czero<R>(), sq[m[K]]);
-    }
-#pragma unroll
-    for (int j = K + 1; j < MD; ++j) {
-      const bool h = m[j] > 0;
-      const cx<R> v0 = ld(h ? at32(L.rd[fam_1001(MD, K, j)], (uint32_t)rdn[j]) : own);
-      const cx<R> v1 = ld(h ? at32(L.rd[fam_1010(MD, K, j)], (uint32_t)rdn[j]) : own);
-      x[2 * j] = cscale(h ? v0 : czero<R>(), sq[m[j]]);
-      x[2 * j + 1] = cscale(h ? v1 : czero<R>(), sq[m[j]]);
-    }
-    // writes p + 1_i
-#pragma unroll
-    for (int i = 2 * K; i < NP; ++i) {
-      const int j = i >> 1;
-      bool ok;
-      R scale;
-      cx<R>* dst;
-      if (i == 2 * K + 1) {                 // d(m + 1_K): output amplitude
-        ok = L.f0nxt != nullptr;            // none above the last level (a total photon cutoff)
-        scale = isq[m[K] + 1];
-        dst = at32(L.f0nxt, (uint32_t)rup[K]);
-      } else if (i == 2 * K) {              // F2(K)(m)
-        ok = (m[K] <= P.CD[K] - 3);
-        scale = isq[m[K] + 2];
-        dst = at32(L.wr[fam_f2(MD, K)], (uint32_t)r);
-      } else {                              // F1010(K,j)(m) / F1001(K,j)(m)
-        ok = (m[j] <= P.CD[j] - 2);
-        scale = isq[m[j] + 1];
-        dst = at32(L.wr[(i & 1) ? fam_1001(MD, K, j) : fam_1010(MD, K, j)], (uint32_t)r);
-      }
-      if (!ok) continue;
-      cx<R> acc = czero<R>();
-      if (ODD) cfma(acc, ld(bi + i), yk[K]);
-#pragma unroll
-      for (int l = 2 * K; l < NP; ++l) cfma(acc, ld(Ai + i * NP + l), x[l]);
-      st(dst, cscale(acc, scale));
-      count_write(P, dst);
-    }
-  }
-}
-
-// ---------------------------------------------------------------------------
 // Algorithm 2 (undetected modes present).  A node's block of B entries is
 // split into chunks of whole rows of the first undetected coordinate (rows of
 // R0 = B / C0 entries); the WV wavefronts of one workgroup handle one

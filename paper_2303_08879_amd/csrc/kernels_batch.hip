@@ -13,6 +13,7 @@
 #include <numeric>
 
 #include "batch_level.h"
+#include "pt_units.h"
 
 namespace fd {
 
@@ -191,6 +192,7 @@ fd_status build_sched(int n, Plan* const* plans, const bool* odd, const void* co
     C.b = static_cast<const cx<R>*>(b[i]);
     C.c = static_cast<const cx<R>*>(c[i]);
     C.rho = static_cast<cx<R>*>(rho[i]);
+    C.mtab = Pl.d_mtab;
     C.elist = Pl.d_elist;
     C.woff = Pl.d_woff;
     C.status = Pl.d_status;
@@ -233,7 +235,7 @@ fd_status build_sched(int n, Plan* const* plans, const bool* odd, const void* co
   int dev = 0;
   (void)hipGetDevice(&dev);
   // work items: every step of a circuit in workgroups of whole units, one
-  // (lattice point, chunk) unit or kThreads lattice points each unless the
+  // (lattice point, chunk) unit or one 16-column pass each unless the
   // step has more than items_per_wave x kBatchResident of them
   const fd_batch_tuning T = batch_tuning();
   std::stable_sort(S->classes.begin(), S->classes.end(),
@@ -262,9 +264,11 @@ fd_status build_sched(int n, Plan* const* plans, const bool* odd, const void* co
           per = std::max<int64_t>((T.min_block_units + 1) / 2, units / ((int64_t)T.items_per_wave * kBatchResident));
           st_.shm = std::max(st_.shm, fwd_lds_bytes_for(Pl, G));
         } else {
-          per = std::max<int64_t>({kThreads, T.min_point_units, units / ((int64_t)T.items_per_wave * kBatchResident)});
-          per = (per + kThreads - 1) / kThreads * kThreads;
-          st_.shm = std::max(st_.shm, 2 * (kMaxCut + 4) * sizeof(R) + (size_t)(Pl.MD + 1) * (Pl.smax + 3) * sizeof(int));
+          // a pass of the workgroup's wavefronts takes 16 points each
+          constexpr int64_t pass = 16 * (kThreads / 64);
+          per = std::max<int64_t>({pass, T.min_point_units, units / ((int64_t)T.items_per_wave * kBatchResident)});
+          per = (per + pass - 1) / pass * pass;
+          st_.shm = std::max(st_.shm, pt_lds_bytes(Pl, 1, kThreads / 64, 2));
         }
         if (units > 0x7fffffff) {
           *err = "a step of circuit " + std::to_string(i) + " has too many units for one work item table";

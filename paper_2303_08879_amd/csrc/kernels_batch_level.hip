@@ -1,29 +1,37 @@
 // Level kernels of the batched forward: one step of every circuit of a class.
 #include "batch_level.h"
+#include "pt_units.h"
 
 namespace fd {
 
 template <int MD, bool ODD, typename R>
-__global__ __launch_bounds__(kThreads) void k_batch_point(const BatchCirc<R>* __restrict__ circs,
+__global__ __launch_bounds__(kThreads, 2) void k_batch_point(const BatchCirc<R>* __restrict__ circs,
                                                           const BatchItem* __restrict__ items, int S) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
   const BatchItem I = items[blockIdx.x];
   const BatchCirc<R>* __restrict__ C = circs + I.circ;
   R* sq = reinterpret_cast<R*>(smem_raw);
-  R* isq = sq + (kMaxCut + 4);
-  int* spn = reinterpret_cast<int*>(isq + (kMaxCut + 4));
-  const int npn = (MD + 1) * C->P.pnw;
-  const int* pn = load_global(&C->P.pn);
-  for (int i = threadIdx.x; i < npn; i += blockDim.x) spn[i] = pn[i];
-  for (int v = threadIdx.x; v < kMaxCut + 4; v += blockDim.x) {
-    sq[v] = sqrt(R(v));
-    isq[v] = v ? R(1) / sqrt(R(v)) : R(0);
-  }
-  __syncthreads();
+  uint64_t* rd = reinterpret_cast<uint64_t*>(sq + 2 * (kMaxCut + 4));
+  uint64_t* wr = rd + pt_table_entries(MD);
+  int* rows = reinterpret_cast<int*>(wr + pt_table_entries(MD));
+  int* spn = rows + (kThreads / 64) * pt_row_ints(MD, 1);
+  rows += (threadIdx.x >> 6) * pt_row_ints(MD, 1);
+  const DevPlan& P = C->P;
+  const R* sqt = static_cast<const R*>(load_global(&P.sqt));
+  const int* pn = load_global(&P.pn);
+  for (int i = threadIdx.x; i < 2 * (kMaxCut + 4); i += blockDim.x) sq[i] = sqt[i];
+  for (int i = threadIdx.x; i < (MD + 1) * P.pnw; i += blockDim.x) spn[i] = pn[i];
   const BatchLevel<R> L = batch_level(C, S);
+  pt_fill_pointers<MD, ODD, R>(L, rd, wr);
   const cx<R>* Ai = load_global(&C->Ai);
-  for (int r = I.u0 + (int)threadIdx.x; r < I.u1; r += blockDim.x)
-    fwd_point_unit<MD, ODD, R>(C->P, L, Ai, Ai + 4 * MD * MD, spn, sq, isq, S, r);
+  PtConst<MD, ODD, false, R> Q;
+  Q.load(P, Ai, Ai + 4 * MD * MD, 0);
+  __syncthreads();
+  const PtLds<R> Y{sq, sq + (kMaxCut + 4), spn, rd, wr};
+  const uint64_t* mt = load_global(&C->mtab);
+  if (mt) mt += load_global(&P.lvl)[S];
+  for (int base = I.u0 + 16 * (int)(threadIdx.x >> 6); base < I.u1; base += 16 * (kThreads / 64))
+    fwd_point_tile<MD, ODD, false, 1, R>(P, Y, Q, L.f0cur, L.f0nxt != nullptr, mt, S, base, I.u1, rows);
 }
 
 template <int MD, int NQ, typename R>

@@ -95,244 +95,6 @@ __global__ __launch_bounds__(kThreads) void k_perm_in(DevPlan P, const cx<R>* __
     st(g0 + node_of_cindex(P, spn, slv, (int)idx), ld(drho + idx));
 }
 
-template <typename R>
-__device__ __forceinline__ void load_tables_v(const DevPlan& P, int* spn, R* sq, R* isq) {
-  const int n = (P.MD + 1) * P.pnw;
-  for (int i = threadIdx.x; i < n; i += blockDim.x) spn[i] = P.pn[i];
-  for (int v = threadIdx.x; v < kMaxCut + 4; v += blockDim.x) {
-    sq[v] = sqrt(R(v));
-    isq[v] = v ? R(1) / sqrt(R(v)) : R(0);
-  }
-}
-
-// ---------------------------------------------------------------------------
-// Algorithm 1 reverse step: one thread per lattice point.
-// For each pivot the lane gathers the cotangents h of its targets, forms the
-// adjoint of the reads (u = A^H h, with A and b read through uniform loads,
-// so they live in scalar registers instead of LDS or vector registers) and
-// writes the read cotangents.  The Abar / bbar records (h and the read
-// values x, which only the reduction needs) are staged NB lanes at a time in
-// the wave's LDS area and reduced on the matrix cores: a smaller batch keeps
-// the staging area, and so the LDS per wave, small enough for several waves
-// per SIMD; the read values of a lane are loaded when its batch is staged.
-// ---------------------------------------------------------------------------
-template <int MD, bool ODD, typename R, int NB>
-__global__ __launch_bounds__(kThreads) void k_vjp_point(DevPlan P, VjpPtrs<R> V, const cx<R>* __restrict__ Ai,
-                                                        const cx<R>* __restrict__ bi, int S, int nwork,
-                                                        double2* __restrict__ partial) {
-  constexpr int NP = 2 * MD;
-  constexpr int NR = NP + 1;
-  constexpr int NPAIR = NP * NR;
-  constexpr int RS = NB + 1;   // padded row stride of the staging area
-  static_assert(NB % 4 == 0 && 64 % NB == 0, "batches of whole MFMA steps that tile the wavefront");
-  extern __shared__ __align__(16) unsigned char smem_raw[];
-  cx<R>* rec = reinterpret_cast<cx<R>*>(smem_raw);                 // waves x RS x (NP + NR)
-  R* sq = reinterpret_cast<R*>(rec + (size_t)(kThreads / 64) * RS * (NP + NR));
-  R* isq = sq + (kMaxCut + 4);
-  int* spn = reinterpret_cast<int*>(isq + (kMaxCut + 4));
-  load_tables_v(P, spn, sq, isq);
-  __syncthreads();
-  cx<R>* recw = rec + (size_t)(threadIdx.x >> 6) * RS * (NP + NR);
-  const int lane = threadIdx.x & 63;
-  // columns of X that can be non-zero: the pivot value (bbar) only when odd
-  // levels are swept
-  constexpr int NCOL = ODD ? NR : NP;
-  MfmaAcc<(NCOL + 15) / 16> acc;
-  mfma_acc_zero(acc);
-  const int pnw = P.pnw;
-
-  for (int base = blockIdx.x * kThreads; base < nwork; base += gridDim.x * kThreads) {
-    const int r = base + threadIdx.x;
-    const bool live = r < nwork;
-    int m[MD], s[MD + 1], rdn[MD], rup[MD];
-#pragma unroll
-    for (int d = 0; d < MD; ++d) m[d] = 0;
-    int K0 = MD;
-    cx<R> g0acc = czero<R>(), G0 = czero<R>();
-    // the point's own F0 entry: always valid for a live lane, the address that
-    // loads of absent neighbours or unset cotangent slots read instead (their
-    // value is then discarded), so a pivot's loads are issued unconditionally
-    // and share one wait
-    const cx<R>* own = at32(V.fcur[0], (uint32_t)(live ? r : 0));
-    if (live) {
-      unrank<MD>(spn, pnw, P.CD, S, r, m, s);
-      neighbour_ranks<MD>(spn, pnw, s, rdn, rup);
-#pragma unroll
-      for (int d = MD - 1; d >= 0; --d)
-        if (m[d] > 0) K0 = d;
-      g0acc = ld(at32(V.d0cur, (uint32_t)r));
-      G0 = ld(own);
-    }
-    cx<R> ykg[MD];
-#pragma unroll
-    for (int K = 0; K < MD; ++K) ykg[K] = czero<R>();
-
-#pragma unroll
-    for (int K = 0; K < MD; ++K) {
-      const bool valid = live && K <= K0 && m[K] <= P.CD[K] - 2;
-      if (__ballot(valid) == 0ull) continue;   // uniform over the wave (each wave stages its own records)
-      // the record's read values, loaded by every lane with the cotangents
-      // (one memory round trip for both, and for both record batches)
-      cx<R> xr[NCOL];
-#pragma unroll
-      for (int l = 0; l < NCOL; ++l) xr[l] = czero<R>();
-      cx<R> h[NP];
-#pragma unroll
-      for (int i = 0; i < NP; ++i) h[i] = czero<R>();
-      if (valid) {
-        xr[2 * K] = cscale(G0, sq[m[K] + 1]);
-        {
-          const bool hk = m[K] > 0;
-          const cx<R> v = ld(hk ? at32(V.fprev[fam_f2(MD, K)], (uint32_t)rdn[K]) : own);
-          xr[2 * K + 1] = cscale(hk ? v : czero<R>(), sq[m[K]]);
-        }
-#pragma unroll
-        for (int j = K + 1; j < MD; ++j) {
-          const bool hj = m[j] > 0;
-          const cx<R> v0 = ld(hj ? at32(V.fprev[fam_1001(MD, K, j)], (uint32_t)rdn[j]) : own);
-          const cx<R> v1 = ld(hj ? at32(V.fprev[fam_1010(MD, K, j)], (uint32_t)rdn[j]) : own);
-          xr[2 * j] = cscale(hj ? v0 : czero<R>(), sq[m[j]]);
-          xr[2 * j + 1] = cscale(hj ? v1 : czero<R>(), sq[m[j]]);
-        }
-        if (ODD) xr[NP] = ld(at32(V.fcur[fam_f1k(K)], (uint32_t)r));
-        // (no level above the last one under a total photon cutoff)
-        if (V.gf0nxt) h[2 * K + 1] = cscale(ld(at32(V.gf0nxt, (uint32_t)rup[K])), isq[m[K] + 1]);
-        {
-          const bool t2 = m[K] <= P.CD[K] - 3;
-          const cx<R> v = ld(t2 ? at32(V.gcur[fam_f2(MD, K)], (uint32_t)r) : own);
-          h[2 * K] = cscale(t2 ? v : czero<R>(), isq[m[K] + 2]);
-        }
-#pragma unroll
-        for (int j = K + 1; j < MD; ++j) {
-          const bool tj = m[j] <= P.CD[j] - 2;
-          const cx<R> v0 = ld(tj ? at32(V.gcur[fam_1010(MD, K, j)], (uint32_t)r) : own);
-          const cx<R> v1 = ld(tj ? at32(V.gcur[fam_1001(MD, K, j)], (uint32_t)r) : own);
-          h[2 * j] = cscale(tj ? v0 : czero<R>(), isq[m[j] + 1]);
-          h[2 * j + 1] = cscale(tj ? v1 : czero<R>(), isq[m[j] + 1]);
-        }
-        // adjoint of the reads
-#pragma unroll
-        for (int l = 2 * K; l < NP; ++l) {
-          cx<R> u = czero<R>();
-#pragma unroll
-          for (int i = 2 * K; i < NP; ++i) cfma_conj(u, ld(Ai + i * NP + l), h[i]);
-          const int j = l >> 1;
-          if (l == 2 * K) {
-            g0acc = cadd(g0acc, cscale(u, sq[m[K] + 1]));
-          } else if (l == 2 * K + 1) {
-            if (m[K] > 0) st(at32(V.gprev[fam_f2(MD, K)], (uint32_t)rdn[K]), cscale(u, sq[m[K]]));
-          } else if (m[j] > 0) {
-            st(at32(V.gprev[(l & 1) ? fam_1010(MD, K, j) : fam_1001(MD, K, j)], (uint32_t)rdn[j]), cscale(u, sq[m[j]]));
-          }
-        }
-        if (ODD) {
-          cx<R> gp = czero<R>();
-#pragma unroll
-          for (int i = 2 * K; i < NP; ++i) cfma_conj(gp, ld(bi + i), h[i]);
-          const bool has_diag_reader = (K > 0) || (m[0] + 1 <= P.CD[0] - 2);
-          ykg[K] = has_diag_reader ? cadd(ld(at32(V.gcur[fam_f1k(K)], (uint32_t)r)), gp) : gp;
-        }
-      }
-      // Abar records of this pivot, NB lanes at a time
-#pragma unroll 1
-      for (int q = 0; q < 64 / NB; ++q) {
-        const bool grp = (lane / NB) == q;
-        if (__ballot(valid && grp) == 0ull) continue;   // uniform over the wave
-        if (grp) {
-          const int col = lane - q * NB;
-#pragma unroll
-          for (int l = 0; l < NCOL; ++l) recw[(NP + l) * RS + col] = xr[l];
-#pragma unroll
-          for (int i = 0; i < NP; ++i) recw[i * RS + col] = h[i];
-        }
-        wave_sync();
-        wave_accum_mfma<R, NP, NCOL, NB>(recw, acc);
-        wave_sync();
-      }
-    }
-
-    if (ODD) {
-      const bool valid = live && m[0] <= P.CD[0] - 2;
-      if (__ballot(valid) != 0ull) {
-        cx<R> xr[NCOL];
-#pragma unroll
-        for (int l = 0; l < NCOL; ++l) xr[l] = czero<R>();
-        if (valid) {
-#pragma unroll
-          for (int j = 0; j < MD; ++j) {
-            const bool hj = m[j] > 0;
-            const cx<R> v0 = ld(hj ? at32(V.fprev[fam_f1b(MD, j)], (uint32_t)rdn[j]) : own);
-            const cx<R> v1 = ld(hj ? at32(V.fprev[fam_f1k(j)], (uint32_t)rdn[j]) : own);
-            xr[2 * j] = cscale(hj ? v0 : czero<R>(), sq[m[j]]);
-            xr[2 * j + 1] = cscale(hj ? v1 : czero<R>(), sq[m[j]]);
-          }
-          xr[NP] = G0;
-        }
-        cx<R> h[NP];
-#pragma unroll
-        for (int i = 0; i < NP; ++i) h[i] = czero<R>();
-        if (valid) {
-#pragma unroll
-          for (int j = 0; j < MD; ++j) {
-            const bool okk = j == 0 || m[j] <= P.CD[j] - 2;
-            const bool kpiv = (j <= K0) && (m[j] <= P.CD[j] - 2);
-            const bool okb = (j == 0) ? (m[0] <= P.CD[0] - 3) : (m[j] <= P.CD[j] - 2);
-            const cx<R> vk = ld(okk && !kpiv ? at32(V.gcur[fam_f1k(j)], (uint32_t)r) : own);
-            const cx<R> vb = ld(okb ? at32(V.gcur[fam_f1b(MD, j)], (uint32_t)r) : own);
-            h[2 * j] = okk ? cscale(kpiv ? ykg[j] : vk, isq[m[j] + 1]) : czero<R>();
-            h[2 * j + 1] = cscale(okb ? vb : czero<R>(), isq[m[j] + 1]);
-          }
-#pragma unroll
-          for (int l = 0; l < NP; ++l) {
-            const int j = l >> 1;
-            if (m[j] == 0) continue;
-            cx<R> u = czero<R>();
-#pragma unroll
-            for (int i = 0; i < NP; ++i) cfma_conj(u, ld(Ai + i * NP + l), h[i]);
-            st(at32(V.gprev[(l & 1) ? fam_f1k(j) : fam_f1b(MD, j)], (uint32_t)rdn[j]), cscale(u, sq[m[j]]));
-          }
-          cx<R> gp = czero<R>();
-#pragma unroll
-          for (int i = 0; i < NP; ++i) cfma_conj(gp, ld(bi + i), h[i]);
-          g0acc = cadd(g0acc, gp);
-        }
-#pragma unroll 1
-        for (int q = 0; q < 64 / NB; ++q) {
-          const bool grp = (lane / NB) == q;
-          if (__ballot(valid && grp) == 0ull) continue;
-          if (grp) {
-            const int col = lane - q * NB;
-#pragma unroll
-            for (int l = 0; l < NCOL; ++l) recw[(NP + l) * RS + col] = xr[l];
-#pragma unroll
-            for (int i = 0; i < NP; ++i) recw[i * RS + col] = h[i];
-          }
-          wave_sync();
-          wave_accum_mfma<R, NP, NCOL, NB>(recw, acc);
-          wave_sync();
-        }
-      }
-    }
-    if (live) st(at32(V.gcur[0], (uint32_t)r), g0acc);
-  }
-  // fold the per-wave pair tables (fixed order) into this block's slot
-  cx<double>* red = reinterpret_cast<cx<double>*>(smem_raw);
-  __syncthreads();
-  mfma_acc_store<NP, NR, NCOL>(acc, red + (size_t)(threadIdx.x >> 6) * NPAIR);
-  __syncthreads();
-  double2* slot = partial + (size_t)blockIdx.x * NPAIR;
-  for (int p = threadIdx.x; p < NPAIR; p += blockDim.x) {
-    if (p - (p / NR) * NR >= NCOL) continue;   // the bbar column without odd levels: zero
-    double sx = 0.0, sy = 0.0;
-    for (int wv = 0; wv < kThreads / 64; ++wv) {
-      sx += red[(size_t)wv * NPAIR + p].x;
-      sy += red[(size_t)wv * NPAIR + p].y;
-    }
-    const double2 v = slot[p];
-    slot[p] = make_double2(v.x + sx, v.y + sy);
-  }
-}
-
 // ---------------------------------------------------------------------------
 // Reverse of step 1 of Algorithm 2 (undetected block at zero detections), by
 // weight from the top, one wavefront with the block's forward values and
@@ -495,7 +257,7 @@ struct FinalArgs {
 };
 
 template <typename R>
-__global__ __launch_bounds__(kThreads) void k_vjp_final(const double2* __restrict__ partial, FinalArgs a,
+__global__ __launch_bounds__(kThreads) void k_vjp_final(const double2* __restrict__ partial, int nslots, FinalArgs a,
                                                         const cx<R>* __restrict__ cbar, cx<R>* dA, cx<R>* db,
                                                         cx<R>* dc) {
   __shared__ double2 red[kThreads];
@@ -513,25 +275,23 @@ __global__ __launch_bounds__(kThreads) void k_vjp_final(const double2* __restric
     if (p >= 0) c1 = p * NR + a.npos;
   }
   double sx = 0.0, sy = 0.0;
-  // slots threadIdx.x, + kThreads, ... in order; a fixed trip count lets the
-  // loads of all of them go out before the first add
-  static_assert(kPartialSlots % kThreads == 0, "slot count");
-  constexpr int KS = kPartialSlots / kThreads;
+  // slots threadIdx.x, + kThreads, ... in order, KS of them per pass: their
+  // loads go out before the first add
+  constexpr int KS = 8;
   if (c1 >= 0) {
-    double2 v[KS], w[KS];
+    for (int s0 = threadIdx.x; s0 < nslots; s0 += KS * kThreads) {
+      double2 v[KS], w[KS];
 #pragma unroll
-    for (int k = 0; k < KS; ++k) {
-      const size_t s = threadIdx.x + (size_t)k * kThreads;
-      v[k] = partial[s * P + c1];
-      w[k] = c2 >= 0 ? partial[s * P + c2] : make_double2(0.0, 0.0);
-    }
+      for (int k = 0; k < KS; ++k) {
+        const size_t s = s0 + k * kThreads;
+        const bool in = (int)s < nslots;
+        v[k] = in ? partial[s * P + c1] : make_double2(0.0, 0.0);
+        w[k] = in && c2 >= 0 ? partial[s * P + c2] : make_double2(0.0, 0.0);
+      }
 #pragma unroll
-    for (int k = 0; k < KS; ++k) {
-      sx += v[k].x;
-      sy += v[k].y;
-      if (c2 >= 0) {
-        sx += w[k].x;
-        sy += w[k].y;
+      for (int k = 0; k < KS; ++k) {
+        sx += v[k].x + w[k].x;
+        sy += v[k].y + w[k].y;
       }
     }
   }
@@ -552,6 +312,25 @@ __global__ __launch_bounds__(kThreads) void k_vjp_final(const double2* __restric
     st(db + (idx - a.M2 * a.M2), cmake<R>((R)t.x, (R)t.y));
   else
     st(dc, ld(cbar));
+}
+
+// ---------------------------------------------------------------------------
+// Block levels: the translation unit for the plan's detected modes.
+// ---------------------------------------------------------------------------
+template <typename R, int LO>
+hipError_t launch_vjp_block_range(const Plan& Pl, const DevPlan& P, const VjpPtrs<R>& Vp, const cx<R>* Ai,
+                                  const cx<R>* bi, int S, int nwork, double2* partial, hipStream_t st);
+template <typename R>
+hipError_t launch_vjp_block_level(const Plan& Pl, const DevPlan& P, const VjpPtrs<R>& Vp, const cx<R>* Ai,
+                                  const cx<R>* bi, int S, int nwork, double2* partial, hipStream_t st) {
+  return Pl.MD <= 4 ? launch_vjp_block_range<R, 1>(Pl, P, Vp, Ai, bi, S, nwork, partial, st)
+                    : launch_vjp_block_range<R, 5>(Pl, P, Vp, Ai, bi, S, nwork, partial, st);
+}
+
+// Workgroups of a block level (streamed rows: private slots for at most kStreamSlots workgroups)
+int vjp_block_grid(const Plan& Pl, int nwork) {
+  return (int)std::min<int64_t>((int64_t)nwork * vjp_geo(Pl, nwork).nchunks,
+                                Pl.st_vjp ? kStreamSlots : kPartialSlots - 1);
 }
 
 // ---------------------------------------------------------------------------
@@ -587,11 +366,17 @@ static hipError_t run_vjp_t(const Plan& Pl, bool odd, const void* A, const void*
   }
   if (e != hipSuccess) return e;
   const int PP = Pl.npos * (Pl.npos + 1);
-  const int64_t npart = (int64_t)kPartialSlots * PP;
+  // reduction slots in use: one per workgroup of the largest level, and the
+  // undetected-block fill's (the last one)
+  int nslots = Pl.B > 1 ? 1 : 0;
+  for (int S = 0; S <= Pl.smax && Pl.MD > 0; ++S)
+    nslots = std::max(nslots, (Pl.B > 1 ? 1 + vjp_block_grid(Pl, (int)Pl.ncnt[S]) : vjp_point_grid((int)Pl.ncnt[S])));
+  const int64_t npart = (int64_t)nslots * PP;
   {
     KTimer kt(Pl, KK_ZERO, st);
-    hipLaunchKernelGGL(k_zero_d2, dim3((unsigned)std::min<int64_t>((npart + 255) / 256, 4096)), dim3(256), 0, st,
+    hipLaunchKernelGGL(k_zero_d2, dim3((unsigned)std::min<int64_t>(std::max<int64_t>(1, (npart + 255) / 256), 4096)), dim3(256), 0, st,
                        partial, npart);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
   }
   DevPlan P = make_devplan(Pl, odd);
   cx<R>* g0 = reinterpret_cast<cx<R>*>(ws + V.g0);
@@ -626,7 +411,6 @@ static hipError_t run_vjp_t(const Plan& Pl, bool odd, const void* A, const void*
       if ((e = hipGetLastError()) != hipSuccess) return e;
     }
   }
-  const size_t tab = 2 * (kMaxCut + 4) * sizeof(R) + (size_t)(MD + 1) * (Pl.smax + 3) * sizeof(int);
   // Checkpointed plans: the forward values of one segment of levels at a
   // time, recomputed from the segment's checkpoint into the segment buffer
   // (slot k holds level seg_lo - 1 + k); F0 of every level is in `saved`.
@@ -700,39 +484,7 @@ static hipError_t run_vjp_t(const Plan& Pl, bool odd, const void* A, const void*
     const int nwork = (int)Pl.ncnt[S];
     KTimer kt(Pl, KK_VJP_LEVEL, st);
     if (Pl.B == 1) {
-      const int NP = 2 * MD;
-      const size_t shm = std::max((size_t)(kThreads / 64) * (kPointBatch + 1) * (2 * NP + 1) * sizeof(cx<R>),
-                                  (size_t)(kThreads / 64) * NP * (NP + 1) * sizeof(cx<double>)) + tab;
-      const int grid = (int)std::min<int64_t>((nwork + kThreads - 1) / kThreads, kPartialSlots - 1);
-#define FD_VJP_POINT(MDV)                                                                                        \
-  case MDV:                                                                                                      \
-    if (odd) {                                                                                                   \
-      if (shm > 65536)                                                                                           \
-        (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&k_vjp_point<MDV, true, R, kPointBatch>),       \
-                                  hipFuncAttributeMaxDynamicSharedMemorySize, (int)shm);                         \
-      hipLaunchKernelGGL((k_vjp_point<MDV, true, R, kPointBatch>), dim3(grid), dim3(kThreads), shm, st, P, Vp, \
-                         Ai, bi, S, nwork, partial);                                                             \
-    } else {                                                                                                     \
-      if (shm > 65536)                                                                                           \
-        (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&k_vjp_point<MDV, false, R, kPointBatch>),      \
-                                  hipFuncAttributeMaxDynamicSharedMemorySize, (int)shm);                         \
-      hipLaunchKernelGGL((k_vjp_point<MDV, false, R, kPointBatch>), dim3(grid), dim3(kThreads), shm, st, P,    \
-                         Vp, Ai, bi, S, nwork, partial);                                                         \
-    }                                                                                                            \
-    break;
-      switch (MD) {
-        FD_VJP_POINT(1)
-        FD_VJP_POINT(2)
-        FD_VJP_POINT(3)
-        FD_VJP_POINT(4)
-        FD_VJP_POINT(5)
-        FD_VJP_POINT(6)
-        FD_VJP_POINT(7)
-        FD_VJP_POINT(8)
-        default:
-          return hipErrorInvalidValue;
-      }
-#undef FD_VJP_POINT
+      if ((e = launch_vjp_point_level<R>(Pl, P, odd, S, Vp, Ai, bi, nwork, partial, st)) != hipSuccess) return e;
     } else {
       if ((e = launch_vjp_block_level<R>(Pl, P, Vp, Ai, bi, S, nwork, partial, st)) != hipSuccess) return e;
     }
@@ -759,7 +511,7 @@ static hipError_t run_vjp_t(const Plan& Pl, bool odd, const void* A, const void*
       (void)hipFuncSetAttribute(reinterpret_cast<const void*>(kfn), hipFuncAttributeMaxDynamicSharedMemorySize,
                                 (int)shm);
     hipLaunchKernelGGL(kfn, dim3(1), dim3(64), shm, st, P, Ai, bi, G0blk, gseed, Pl.d_elist, Pl.d_woff, Pl.wmax,
-                       partial + (size_t)(kPartialSlots - 1) * PP, cb, gbuf);
+                       partial + (size_t)(nslots - 1) * PP, cb, gbuf);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     cbar_src = cb;
   }
@@ -771,7 +523,7 @@ static hipError_t run_vjp_t(const Plan& Pl, bool odd, const void* A, const void*
   fa.npos = Pl.npos;
   const int nout = fa.M2 * fa.M2 + fa.M2 + 1;
   KTimer kt(Pl, KK_VJP_FINAL, st);
-  hipLaunchKernelGGL((k_vjp_final<R>), dim3(nout), dim3(kThreads), 0, st, partial, fa, cbar_src,
+  hipLaunchKernelGGL((k_vjp_final<R>), dim3(nout), dim3(kThreads), 0, st, partial, nslots, fa, cbar_src,
                      reinterpret_cast<cx<R>*>(dA), reinterpret_cast<cx<R>*>(db), reinterpret_cast<cx<R>*>(dc));
   return hipGetLastError();
 }

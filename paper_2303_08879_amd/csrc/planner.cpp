@@ -3,6 +3,7 @@
 // the undetected block of Algorithm 2).  Host-only: no device call here
 // except in ensure_device(), which uploads the tables on first use.
 #include <algorithm>
+#include <cmath>
 #include <cstdlib>
 #include <atomic>
 #include <cstring>
@@ -335,6 +336,7 @@ DevPlan make_devplan(const Plan& P, bool odd) {
     d.uinv[q] = 1.0 / P.ustride[q];
   }
   for (int j = 0; j < P.MD; ++j) d.cinv[j] = 1.0 / P.CD[j];
+  d.sqt = P.d_sqt;
   d.pn = P.d_pn;
   d.lvl = P.d_lvl;
   d.node = P.d_node;
@@ -624,6 +626,28 @@ static bool build_node_table(const Plan& P, std::vector<int>* out, std::string* 
   return true;
 }
 
+// Digits of every lattice point in node order, mode j at bits 8 j..8 j + 7:
+// C order visits the points of one level in lexicographic order, so each
+// point takes the next place of its level.
+static void build_digit_table(const Plan& P, std::vector<uint64_t>* out) {
+  out->assign((size_t)P.nodes_total, 0);
+  std::vector<int64_t> next(P.lvl.begin(), P.lvl.begin() + P.smax + 1);
+  int m[kMaxD] = {};
+  int S = 0;
+  for (int64_t it = 0; it < P.nodes_total; ++it) {
+    uint64_t pk = 0;
+    for (int j = 0; j < P.MD; ++j) pk |= (uint64_t)m[j] << (8 * j);
+    (*out)[(size_t)next[S]++] = pk;
+    for (int j = P.MD - 1; j >= 0; --j) {
+      ++m[j];
+      ++S;
+      if (m[j] < P.CD[j] && S <= P.smax) break;   // (the cap of a total photon cutoff)
+      S -= m[j];
+      m[j] = 0;
+    }
+  }
+}
+
 fd_status ensure_device(Plan* P, std::string* err) {
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess) {
@@ -651,6 +675,40 @@ fd_status ensure_device(Plan* P, std::string* err) {
       hipMemset(P->d_status, 0, 256) != hipSuccess) {
     *err = "upload of plan tables failed";
     return FD_ERR_HIP;
+  }
+  {
+    // square-root tables (correctly rounded on the host as on the device)
+    const int n = kMaxCut + 4;
+    std::vector<double> t(2 * n);
+    std::vector<float> tf(2 * n);
+    for (int v = 0; v < n; ++v) {
+      t[v] = std::sqrt((double)v);
+      t[n + v] = v ? 1.0 / t[v] : 0.0;
+      tf[v] = std::sqrt((float)v);
+      tf[n + v] = v ? 1.0f / tf[v] : 0.0f;
+    }
+    const size_t nb = 2 * n * (elem_bytes(P->dt) / 2);
+    const void* src = P->dt == FD_C64 ? (const void*)tf.data() : (const void*)t.data();
+    if (hipMalloc(&P->d_sqt, nb) != hipSuccess) {
+      *err = "hipMalloc of plan tables failed";
+      return FD_ERR_OOM;
+    }
+    if (hipMemcpy(P->d_sqt, src, nb, hipMemcpyHostToDevice) != hipSuccess) {
+      *err = "upload of plan tables failed";
+      return FD_ERR_HIP;
+    }
+  }
+  if (P->MD > 0 && P->B == 1 && P->nodes_total <= kMaxDigitTable) {
+    std::vector<uint64_t> mt;
+    build_digit_table(*P, &mt);
+    if (hipMalloc((void**)&P->d_mtab, mt.size() * 8) != hipSuccess) {
+      *err = "hipMalloc of the digit table failed";
+      return FD_ERR_OOM;
+    }
+    if (hipMemcpy(P->d_mtab, mt.data(), mt.size() * 8, hipMemcpyHostToDevice) != hipSuccess) {
+      *err = "upload of the digit table failed";
+      return FD_ERR_HIP;
+    }
   }
   if (P->MD > 0 && P->B == 1 &&
       hipMalloc((void**)&P->d_mass, (size_t)(P->smax + 1) * kMassParts * sizeof(double)) != hipSuccess) {

@@ -1,6 +1,8 @@
 // Reverse sweep of Algorithm 2 plans: the block kernel and its per-level
-// launch (the point kernels, the fills and the sweep driver are in
-// kernels_vjp.hip).
+// launch, compiled in four translation units (precision, detected modes 1-4
+// and 5-8); the fills and the sweep driver are in kernels_vjp.hip.
+#pragma once
+
 #include <algorithm>
 
 #include "vjp_common.h"
@@ -354,41 +356,36 @@ static void launch_vjp_block_k(int waves, size_t shm, int grid, hipStream_t st, 
   launch_vjp_block_w<MD, NQ, R, ST, kVjpWavesLds>(shm, grid, st, P, Vp, Ai, bi, S, nwork, G, partial);
 }
 
-template <typename R>
-hipError_t launch_vjp_block_level(const Plan& Pl, const DevPlan& P, const VjpPtrs<R>& Vp, const cx<R>* Ai,
+// Detected modes LO..LO + 3.
+template <typename R, int LO>
+hipError_t launch_vjp_block_range(const Plan& Pl, const DevPlan& P, const VjpPtrs<R>& Vp, const cx<R>* Ai,
                                   const cx<R>* bi, int S, int nwork, double2* partial, hipStream_t st) {
   const int MD = Pl.MD;
   // as in the forward sweep: shorter row chunks on levels with few units
   const ChunkGeo G = vjp_geo(Pl, nwork);
   const size_t shm = vjp_lds_bytes_for(Pl, G);
   if (shm > kMaxLds) return hipErrorInvalidConfiguration;   // rejected before the sweep
-  // streamed rows: private slots for at most kStreamSlots workgroups
-  const int grid = (int)std::min<int64_t>((int64_t)nwork * G.nchunks,
-                                          Pl.st_vjp ? kStreamSlots : kPartialSlots - 1);
-#define FD_VJP_BLOCK_NQ(MDV, NQV)                                                                  \
+  const int grid = vjp_block_grid(Pl, nwork);
+#define FD_VJP_BLOCK_NQ(MDV, NQV)                                                                       \
   if (Pl.st_vjp)                                                                                   \
     launch_vjp_block_k<MDV, NQV, R, true>(Pl.vjp_waves, shm, grid, st, P, Vp, Ai, bi, S, nwork, G, partial); \
   else                                                                                             \
     launch_vjp_block_k<MDV, NQV, R, false>(Pl.vjp_waves, shm, grid, st, P, Vp, Ai, bi, S, nwork, G, partial);
 #define FD_VJP_BLOCK(MDV)        \
-  case MDV:                      \
+  case LO + MDV:                 \
     if (Pl.nq == 2) {            \
-      FD_VJP_BLOCK_NQ(MDV, 2)    \
+      FD_VJP_BLOCK_NQ(LO + MDV, 2)    \
     } else if (Pl.nq == 4) {     \
-      FD_VJP_BLOCK_NQ(MDV, 4)    \
+      FD_VJP_BLOCK_NQ(LO + MDV, 4)    \
     } else {                     \
-      FD_VJP_BLOCK_NQ(MDV, 6)    \
+      FD_VJP_BLOCK_NQ(LO + MDV, 6)    \
     }                            \
     break;
   switch (MD) {
+    FD_VJP_BLOCK(0)
     FD_VJP_BLOCK(1)
     FD_VJP_BLOCK(2)
     FD_VJP_BLOCK(3)
-    FD_VJP_BLOCK(4)
-    FD_VJP_BLOCK(5)
-    FD_VJP_BLOCK(6)
-    FD_VJP_BLOCK(7)
-    FD_VJP_BLOCK(8)
     default:
       return hipErrorInvalidValue;
   }
@@ -396,12 +393,5 @@ hipError_t launch_vjp_block_level(const Plan& Pl, const DevPlan& P, const VjpPtr
 #undef FD_VJP_BLOCK_NQ
   return hipSuccess;
 }
-
-template hipError_t launch_vjp_block_level<float>(const Plan&, const DevPlan&, const VjpPtrs<float>&,
-                                                  const cx<float>*, const cx<float>*, int, int, double2*,
-                                                  hipStream_t);
-template hipError_t launch_vjp_block_level<double>(const Plan&, const DevPlan&, const VjpPtrs<double>&,
-                                                   const cx<double>*, const cx<double>*, int, int, double2*,
-                                                   hipStream_t);
 
 }  // namespace fd

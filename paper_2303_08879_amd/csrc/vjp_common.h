@@ -106,4 +106,13 @@ template <typename R>
 hipError_t launch_vjp_block_level(const Plan& Pl, const DevPlan& P, const VjpPtrs<R>& Vp, const cx<R>* Ai,
                                   const cx<R>* bi, int S, int nwork, double2* partial, hipStream_t st);
 
+// Its workgroups, each with a reduction slot of its own.
+int vjp_block_grid(const Plan& Pl, int nwork);
+
+// The same for a plan with every mode detected (kernels_vjp_point.hip).
+template <typename R>
+hipError_t launch_vjp_point_level(const Plan& Pl, const DevPlan& P, bool odd, int S, const VjpPtrs<R>& V,
+                                  const cx<R>* A, const cx<R>* b, int nwork, double2* partial, hipStream_t st);
+int vjp_point_grid(int nwork);
+
 }  // namespace fd
