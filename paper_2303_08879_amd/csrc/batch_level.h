@@ -43,8 +43,8 @@ struct BatchCirc {
 };
 
 // One workgroup's share of a launch: units [u0, u1) of circuit `circ` at the
-// launch's step (lattice points; (lattice point, row chunk) pairs of geometry
-// (RC, nchunks) for Algorithm 2).
+// launch's step ((bridge, 16-point tile) items of Algorithm 1; (lattice point,
+// row chunk) pairs of geometry (RC, nchunks) for Algorithm 2).
 struct BatchItem {
   int circ, u0, u1, RC, nchunks, pad[3];
 };

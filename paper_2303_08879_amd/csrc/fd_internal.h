@@ -56,9 +56,11 @@ constexpr int kFwdChunk = 448;           // own entries of one of its (lattice p
 constexpr int kFwdChunkSmall = 192;      // on levels with fewer than kSmallLevelUnits units
 constexpr int kNodeStride = 3 * kMaxD;   // ints per node record: m, rank(m - 1_j), rank(m + 1_j)
 constexpr int64_t kMaxDigitTable = 1 << 20;   // lattice points: 8 MB of digits, a few ms of host work
-// Points of a level from which the point kernels rank 64 points per wavefront
-// (a quarter of the rank work) instead of 16 (four times the wavefronts).
-constexpr int kPointTileMin = 65536;
+// Points of a level from which the reverse point kernel ranks 64 points per
+// wavefront (a quarter of the rank work) instead of 16 (four times the
+// wavefronts).  Eight modes: 71 thousand points 30 against 28 us, 143 thousand 41
+// against 48, a million 218 against 236.
+constexpr int kPointTileMin = 1 << 17;
 constexpr int kBlockBatch = 32;          // Abar records per LDS staging batch, block reverse kernel
 constexpr int kVjpSlots = 16384;         // reduction slots of the state-vector cotangents
 

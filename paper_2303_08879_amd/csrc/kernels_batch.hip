@@ -264,10 +264,12 @@ fd_status build_sched(int n, Plan* const* plans, const bool* odd, const void* co
           per = std::max<int64_t>((T.min_block_units + 1) / 2, units / ((int64_t)T.items_per_wave * kBatchResident));
           st_.shm = std::max(st_.shm, fwd_lds_bytes_for(Pl, G));
         } else {
-          // a pass of the workgroup's wavefronts takes 16 points each
-          constexpr int64_t pass = 16 * (kThreads / 64);
-          per = std::max<int64_t>({pass, T.min_point_units, units / ((int64_t)T.items_per_wave * kBatchResident)});
-          per = (per + pass - 1) / pass * pass;
+          const PtItems N = pt_items(Pl, s);
+          units = 0;
+          for (int K = 0; K < Pl.MD; ++K) units += N.tiles(K);
+          // min_point_units counts lattice points, 16 per item
+          per = std::max<int64_t>({kThreads / 64, T.min_point_units / 16,
+                                   units / ((int64_t)T.items_per_wave * kBatchResident)});
           st_.shm = std::max(st_.shm, pt_lds_bytes(Pl, 1, kThreads / 64, 2));
         }
         if (units > 0x7fffffff) {

@@ -29,9 +29,15 @@ __global__ __launch_bounds__(kThreads, 2) void k_batch_point(const BatchCirc<R>*
   __syncthreads();
   const PtLds<R> Y{sq, sq + (kMaxCut + 4), spn, rd, wr};
   const uint64_t* mt = load_global(&C->mtab);
-  if (mt) mt += load_global(&P.lvl)[S];
-  for (int base = I.u0 + 16 * (int)(threadIdx.x >> 6); base < I.u1; base += 16 * (kThreads / 64))
-    fwd_point_tile<MD, ODD, false, 1, R>(P, Y, Q, L.f0cur, L.f0nxt != nullptr, mt, S, base, I.u1, rows);
+  const int64_t* lvl = load_global(&P.lvl);
+  if (mt) mt += lvl[S];
+  PtItems N;
+  for (int K = 0; K < MD; ++K) N.n[K] = (int)(lvl[K * (P.smax + 2) + S + 1] - lvl[K * (P.smax + 2) + S]);
+  for (int u = I.u0 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6); u < I.u1; u += kThreads / 64) {
+    int K, base;
+    if (!pt_item(N, MD, u, &K, &base)) break;
+    fwd_point_item<MD, ODD, false, R>(P, Y, Q, L.f0cur, L.f0nxt != nullptr, mt, S, K, base, N.n[K], rows);
+  }
 }
 
 template <int MD, int NQ, typename R>

@@ -7,37 +7,41 @@
 
 namespace fd {
 
-template <int MD, bool ODD, bool DUAL, int T, typename R>
+template <int MD, bool ODD, bool DUAL, typename R>
 __global__ __launch_bounds__(kThreads, 2) void k_fwd_point(DevPlan P, LevelPtrs<R> L, const uint64_t* __restrict__ mt,
-                                                        const cx<R>* __restrict__ Ai, const cx<R>* __restrict__ bi,
-                                                        int S, int nwork, int64_t dT) {
+                                                           const cx<R>* __restrict__ Ai, const cx<R>* __restrict__ bi,
+                                                           int S, PtItems I, int64_t dT) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
   R* sq = reinterpret_cast<R*>(smem_raw);
   uint64_t* rd = reinterpret_cast<uint64_t*>(sq + 2 * (kMaxCut + 4));
   uint64_t* wr = rd + pt_table_entries(MD);
   int* rows = reinterpret_cast<int*>(wr + pt_table_entries(MD));
-  int* spn = rows + (kThreads / 64) * pt_row_ints(MD, T);
-  rows += (threadIdx.x >> 6) * pt_row_ints(MD, T);
+  int* spn = rows + (kThreads / 64) * pt_row_ints(MD, 1);
+  rows += (threadIdx.x >> 6) * pt_row_ints(MD, 1);
   pt_load_tables<R>(P, MD, sq, spn);
   pt_fill_pointers<MD, ODD, R>(L, rd, wr);
   PtConst<MD, ODD, DUAL, R> C;
   C.load(P, Ai, bi, dT);
   __syncthreads();
   const PtLds<R> Y{sq, sq + (kMaxCut + 4), spn, rd, wr};
-  const int base = (blockIdx.x * (kThreads / 64) + (threadIdx.x >> 6)) * 16 * T;
-  if (base >= nwork) return;
-  fwd_point_tile<MD, ODD, DUAL, T, R>(P, Y, C, L.f0cur, L.f0nxt != nullptr, mt, S, base, nwork, rows, dT);
+  int K, base;
+  if (!pt_item(I, MD, blockIdx.x * (kThreads / 64) + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), &K, &base))
+    return;
+  fwd_point_item<MD, ODD, DUAL, R>(P, Y, C, L.f0cur, L.f0nxt != nullptr, mt, S, K, base, I.n[K], rows, dT);
 }
 
-template <int T, typename R>
-static hipError_t launch_t(const Plan& Pl, const DevPlan& P, bool odd, int S, const LevelPtrs<R>& L, const cx<R>* A,
-                           const cx<R>* b, int nwork, int64_t dT, hipStream_t st) {
-  const int per = kThreads / 64 * 16 * T, grid = (nwork + per - 1) / per;
-  const size_t shm = pt_lds_bytes(Pl, T, kThreads / 64, 2);
+template <typename R>
+hipError_t launch_fwd_point_level(const Plan& Pl, const DevPlan& P, bool odd, int S, const LevelPtrs<R>& L,
+                                  const cx<R>* A, const cx<R>* b, int nwork, hipStream_t st, int64_t dT) {
+  const PtItems I = pt_items(Pl, S);
+  int units = 0;
+  for (int K = 0; K < Pl.MD; ++K) units += I.tiles(K);
+  const int grid = (units + kThreads / 64 - 1) / (kThreads / 64);
+  const size_t shm = pt_lds_bytes(Pl, 1, kThreads / 64, 2);
   const uint64_t* mt = Pl.d_mtab ? Pl.d_mtab + Pl.lvl[S] : nullptr;
-#define FD_LAUNCH(MDV, ODD, DUAL)                                                                                   \
-  hipLaunchKernelGGL((k_fwd_point<MDV, ODD, DUAL, T, R>), dim3(grid), dim3(kThreads), shm, st, P, L, mt, A, b, S,   \
-                     nwork, dT)
+#define FD_LAUNCH(MDV, ODD, DUAL)                                                                                  \
+  hipLaunchKernelGGL((k_fwd_point<MDV, ODD, DUAL, R>), dim3(grid), dim3(kThreads), shm, st, P, L, mt, A, b, S, I,  \
+                     dT)
 #define FD_LAUNCH_POINT(MDV)           \
   case MDV:                            \
     if (dT)                            \
@@ -62,13 +66,6 @@ static hipError_t launch_t(const Plan& Pl, const DevPlan& P, bool odd, int S, co
 #undef FD_LAUNCH_POINT
 #undef FD_LAUNCH
   return hipGetLastError();
-}
-
-template <typename R>
-hipError_t launch_fwd_point_level(const Plan& Pl, const DevPlan& P, bool odd, int S, const LevelPtrs<R>& L,
-                                  const cx<R>* A, const cx<R>* b, int nwork, hipStream_t st, int64_t dT) {
-  return nwork >= kPointTileMin ? launch_t<4, R>(Pl, P, odd, S, L, A, b, nwork, dT, st)
-                                : launch_t<1, R>(Pl, P, odd, S, L, A, b, nwork, dT, st);
 }
 template hipError_t launch_fwd_point_level<float>(const Plan&, const DevPlan&, bool, int, const LevelPtrs<float>&,
                                                   const cx<float>*, const cx<float>*, int, hipStream_t, int64_t);

@@ -13,10 +13,10 @@
 // complex registers of reads and targets live and fetched A through scalar
 // loads, ceil(NP^2 / 4) cache lines per wavefront and pivot with a wait each.
 //
-// Ranks: one point per lane and 64-point tile (T = 4) or, on levels with few
-// points, 16-point tile (T = 1); the ranks of the neighbours and the digits
-// of m go through LDS rows, from which the four lanes of a point take the
-// modes of their positions.
+// Ranks: the ranks of the neighbours and the digits of m go through LDS rows,
+// from which the four lanes of a point take the modes of their positions; one
+// point per lane and 64-point tile (T = 4, large levels of the reverse sweep) or
+// the four lanes of a 16-point tile's point alike (T = 1).
 #pragma once
 
 #include "fwd_units.h"
@@ -191,40 +191,55 @@ struct PtConst {
   }
 };
 
-// One tile of 16 T lattice points base.. of level S (n points), one
+// The work of a forward level: items (K, tile of 16 points) for every bridge K,
+// whose points are the first n[K] of the level (n_<K = 0).  One item applies
+// bridge K; the K = 0 items also apply the diagonal pivot, the others only
+// form its value at position 2 K (ODD).  A tile whose points take every bridge
+// would otherwise run them one after the other: on the first level of eight
+// modes 14 us against 6.
+struct PtItems {
+  int n[kMaxD];
+  __host__ __device__ __forceinline__ int tiles(int K) const { return (n[K] + 15) >> 4; }
+};
+__device__ __forceinline__ bool pt_item(const PtItems& I, int MD, int u, int* K, int* base) {
+  for (int k = 0; k < MD; ++k) {
+    const int t = I.tiles(k);
+    if (u < t) {
+      *K = k;
+      *base = 16 * u;
+      return true;
+    }
+    u -= t;
+  }
+  return false;
+}
+
+// One item: 16 lattice points base.. of level S (the n points of bridge K), one
 // wavefront.  DUAL carries every amplitude's tangent along (Sec. 2.5, the
 // tangent recurrences summed along one direction): with x, y the values and
-// their tangents x', y',
+// x', y' their tangents,
 //   y' ~ A x' + dA x + b p' + db p
 // for the same reads, targets and scales (p the pivot's value).
-template <int MD, bool ODD, bool DUAL, int T, typename R>
-__device__ __forceinline__ void fwd_point_tile(const DevPlan& P, const PtLds<R>& Y, const PtConst<MD, ODD, DUAL, R>& C,
-                                               const cx<R>* f0cur, bool has_next, const uint64_t* mt, int S, int base,
-                                               int n, int* rows, int64_t dT = 0) {
-  constexpr int NP = 2 * MD, KS = PtMat<MD, R>::KS, SL = 16 * T;
+template <int MD, bool ODD, bool DUAL, typename R>
+__device__ __forceinline__ void fwd_point_item(const DevPlan& P, const PtLds<R>& Y, const PtConst<MD, ODD, DUAL, R>& C,
+                                               const cx<R>* f0cur, bool has_next, const uint64_t* mt, int S, int K,
+                                               int base, int n, int* rows, int64_t dT = 0) {
+  constexpr int NP = 2 * MD, KS = PtMat<MD, R>::KS;
   typedef typename Mma<R>::v4 v4;
   const int lane = threadIdx.x & 63, c = lane & 15, kq = lane >> 4, hk = kq >> 1, side = kq & 1;
-  {
-    const int q = T == 4 ? lane : c;
-    pt_rank_rows<MD, T>(P, Y.spn, mt, S, min(base + q, n - 1), q, rows);
-  }
+  const bool live = base + c < n;
+  const int r = min(base + c, n - 1);
+  pt_rank_rows<MD, 1>(P, Y.spn, mt, S, r, c, rows);
   wave_sync();
-#pragma unroll 1
-  for (int t = 0; t < T; ++t) {
-    const int r0 = base + 16 * t;
-    if (r0 >= n) break;
-    const int slot = 16 * t + c;
-    const bool live = r0 + c < n;
-    const int r = min(r0 + c, n - 1);
-    const uint64_t pk = pt_digits<MD, T>(rows, slot);
+  {
+    const uint64_t pk = pt_digits<MD, 1>(rows, c);
     int mj[KS], dn[KS];
 #pragma unroll
     for (int s = 0; s < KS; ++s) {
       const int j = 2 * s + hk;
       mj[s] = (int)((pk >> (8 * j)) & 255);
-      dn[s] = rows[min(j, MD - 1) * SL + slot];
+      dn[s] = rows[min(j, MD - 1) * 16 + c];
     }
-    const int K0 = pk ? (__ffsll((unsigned long long)pk) - 1) >> 3 : MD;
     const cx<R> g0 = ld(f0cur + r);
     cx<R> t0 = czero<R>();
     if (DUAL) t0 = ld(tangent_of(f0cur, dT) + r);
@@ -296,19 +311,16 @@ __device__ __forceinline__ void fwd_point_tile(const DevPlan& P, const PtLds<R>&
         y[s] = cscale(cmake<R>(re[s], im[s]), w);
         if (DUAL) ty[s] = cscale(cmake<R>(tre[s], tim[s]), w);
         const int room = (j == 0 ? C.cj[s] - 2 - side : C.cj[s] - 2) - mj[s];
-        if (valid && p < NP && room >= 0) write(MD, s, r, y[s], ty[s]);
+        if (K == 0 && valid && p < NP && room >= 0) write(MD, s, r, y[s], ty[s]);
       }
     }
-#pragma unroll 1
-    for (int K = 0; K < MD; ++K) {
-      if (__ballot(live && K <= K0) == 0ull) break;
-      const int mK = (int)((pk >> (8 * K)) & 255);
-      const bool valid = live && K <= K0 && mK <= P.CD[K] - 2;
-      if (__ballot(valid) == 0ull) continue;
+    const int mK = (int)((pk >> (8 * K)) & 255);
+    const bool valid = live && mK <= P.CD[K] - 2;
+    if (__ballot(valid) != 0ull) {
       // pivot d(m) + 1_ket(K)
       cx<R> x[KS], tx[KS];
       reads(K, valid, x, tx);
-      const int up = rows[(MD + K) * SL + slot];
+      const int up = rows[(MD + K) * 16 + c];
       cx<R> yk = czero<R>(), tyk = czero<R>();
       if (ODD) {
         // the pivot value: target 2 K of the diagonal pivot, held by lane
@@ -340,7 +352,14 @@ __device__ __forceinline__ void fwd_point_tile(const DevPlan& P, const PtLds<R>&
       }
     }
   }
-  wave_sync();   // the rows are rewritten by the next tile
+  wave_sync();   // the rows are rewritten by the next item
+}
+
+// The items of level S (group K's points of a level are those with n_<K = 0).
+inline PtItems pt_items(const Plan& Pl, int S) {
+  PtItems I = {};
+  for (int K = 0; K < Pl.MD; ++K) I.n[K] = (int)Pl.ncnt[(size_t)K * (Pl.smax + 1) + S];
+  return I;
 }
 
 // LDS bytes of the point kernels' tables and rank rows (`waves` wavefronts).
