@@ -52,6 +52,13 @@ __device__ __forceinline__ cx<R> cadd(const cx<R>& a, const cx<R>& b) {
   return cmake<R>(a.x + b.x, a.y + b.y);
 }
 
+// c ? a : b, component by component (a conditional between two objects selects
+// between their addresses, which puts them in scratch memory)
+template <typename R>
+__device__ __forceinline__ cx<R> csel(bool c, cx<R> a, cx<R> b) {
+  return cmake<R>(c ? a.x : b.x, c ? a.y : b.y);
+}
+
 // Value and tangent of one amplitude (forward mode, Sec. 2.5): the tangent
 // of an element stored at p lives dT bytes after it.
 template <typename R>

@@ -49,8 +49,7 @@ constexpr int kPartialSlots = 4096;      // deterministic VJP partial accumulato
 constexpr int kStreamSlots = 1024;       // workgroups of a block kernel whose rows stream from HBM
 constexpr int kThreads = 256;
 constexpr int kBT = 64;                  // threads of the block (Algorithm 2) kernels: one wavefront
-constexpr int kVjpWaves = 4;             // wavefronts per workgroup of the block reverse kernel,
-constexpr int kVjpWavesLds = 2;          // or this many where four wavefronts' staging does not fit the LDS
+constexpr int kVjpWaves = 4;             // wavefronts per workgroup of the block reverse kernel
 constexpr int kFwdWaves = 4;             // wavefronts per workgroup of the block forward kernel
 constexpr int kFwdChunk = 448;           // own entries of one of its (lattice point, row chunk) units,
 constexpr int kFwdChunkSmall = 192;      // on levels with fewer than kSmallLevelUnits units
@@ -61,7 +60,6 @@ constexpr int64_t kMaxDigitTable = 1 << 20;   // lattice points: 8 MB of digits,
 // wavefronts).  Eight modes: 71 thousand points 30 against 28 us, 143 thousand 41
 // against 48, a million 218 against 236.
 constexpr int kPointTileMin = 1 << 17;
-constexpr int kBlockBatch = 32;          // Abar records per LDS staging batch, block reverse kernel
 constexpr int kVjpSlots = 16384;         // reduction slots of the state-vector cotangents
 
 enum FamType { F_F0 = 0, F_F1K, F_F1B, F_F2, F_1010, F_1001 };
@@ -185,9 +183,7 @@ struct Plan {
   // blocks whose rows do not fit the LDS staging stream them from HBM, per
   // kernel: forward block units, block fill, reverse block units, reverse fill
   bool st_fwd = false, st_ufill = false, st_vjp = false, st_ufill_vjp = false;
-  // wavefronts per workgroup of the block reverse kernel (kVjpWaves, or
-  // kVjpWavesLds where the rows and staging of kVjpWaves do not fit the LDS)
-  int vjp_waves = kVjpWavesLds;
+  bool vjp_short = false;            // shorter row chunks of the block reverse kernel (LDS)
   bool odd_for(bool b_zero) const { return !b_zero || MU > 0; }
 };
 
@@ -244,9 +240,8 @@ struct VjpLayout {
   size_t total = 0;
 };
 // Entries of one workgroup's private slot of the block reverse kernel: the
-// pivot cotangent blocks (MD rows sets), their b-terms and the own F0
-// cotangent rows, each read only by the lane that wrote it; streamed rows add
-// the undetected-neighbour terms (NQ x (RC + 2) rows).
+// pivot cotangent blocks (MD rows sets), and with streamed rows their b-terms,
+// the own F0 cotangent rows and the undetected-neighbour terms.
 size_t vjp_private_entries(const Plan& P);
 size_t vjp_lds_bytes(const Plan& P);   // dynamic LDS of the block reverse kernel (largest geometry used)
 // Dynamic LDS of the forward block kernel for one chunk geometry: F0 rows

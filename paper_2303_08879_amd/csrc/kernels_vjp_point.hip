@@ -25,40 +25,6 @@
 
 namespace fd {
 
-// Pointer tables of the reverse step: cotangents of the targets (hp), cotangent
-// slots of the reads (gp), forward values of the reads (xp).
-template <int MD, bool ODD, typename R>
-__device__ __forceinline__ void pt_fill_vjp_pointers(const VjpPtrs<R>& V, uint64_t* hp, uint64_t* gp, uint64_t* xp) {
-  constexpr int NP = 2 * MD;
-  for (int t = threadIdx.x; t < pt_table_entries(MD); t += blockDim.x) {
-    const int K = t / kPtPos, p = t % kPtPos, j = p >> 1, b = p & 1;
-    int ft = -1, fr = -1;   // target (level S, F0: S + 1) and read (level S - 1, F0: S) families
-    if (p < NP) {
-      if (K == MD) {
-        if (ODD) {
-          ft = b ? fam_f1b(MD, j) : fam_f1k(j);
-          fr = b ? fam_f1k(j) : fam_f1b(MD, j);
-        }
-      } else if (p == 2 * K) {
-        ft = fam_f2(MD, K);
-        fr = 0;
-      } else if (p == 2 * K + 1) {
-        ft = 0;
-        fr = fam_f2(MD, K);
-      } else if (j > K) {
-        ft = b ? fam_1001(MD, K, j) : fam_1010(MD, K, j);
-        fr = b ? fam_1010(MD, K, j) : fam_1001(MD, K, j);
-      }
-    }
-    hp[t] = ft < 0 ? 0 : reinterpret_cast<uint64_t>(ft ? V.gcur[ft] : const_cast<cx<R>*>(V.gf0nxt));
-    gp[t] = fr < 1 ? 0 : reinterpret_cast<uint64_t>(V.gprev[fr]);
-    xp[t] = fr < 0 ? 0 : reinterpret_cast<uint64_t>(fr ? V.fprev[fr] : V.fcur[0]);
-    if (ODD && p == NP) xp[t] = reinterpret_cast<uint64_t>(V.fcur[K < MD ? fam_f1k(K) : 0]);   // the pivot's value
-  }
-}
-
-constexpr int kTurn = 17;   // row stride of the LDS tile that turns h
-
 // Two wavefronts per SIMD asked for: the compiler then keeps the MFMA operands
 // and results out of the accumulation registers (8 modes, b = 0: 200 -> 184).
 template <int MD, bool ODD, int T, typename R>
@@ -151,7 +117,7 @@ __global__ __launch_bounds__(kThreads, 2) void k_vjp_point(DevPlan P, VjpPtrs<R>
           const bool ok = ((vm >> (4 * s + kq)) & 1) && pr < NCOL &&
                           (first || ((pr > 2 * K || K == MD) && m > 0));
           const cx<R> v = ld(ok ? global_at<const cx<R>>(b) + (first ? r0 + 4 * s + kq : rows[jr * SL + q]) : f0);
-          x[s] = cscale(ok ? v : czero<R>(), piv ? R(1) : sq[m + (first ? 1 : 0)]);
+          x[s] = cscale(csel(ok, v, czero<R>()), piv ? R(1) : sq[m + (first ? 1 : 0)]);
         }
       };
       // D += h conj(x)^T over the tile's 16 points
@@ -162,10 +128,7 @@ __global__ __launch_bounds__(kThreads, 2) void k_vjp_point(DevPlan P, VjpPtrs<R>
 #pragma unroll
         for (int s = 0; s < 4; ++s) {
           const cx<R> v = turn[pr * kTurn + 4 * s + kq];
-          const double hx = v.x, hy = v.y, xx = x[s].x, xy = x[s].y;
-          acc.p1[0] = __builtin_amdgcn_mfma_f64_16x16x4f64(hx, xx, acc.p1[0], 0, 0, 0);
-          acc.p2[0] = __builtin_amdgcn_mfma_f64_16x16x4f64(hy, xy, acc.p2[0], 0, 0, 0);
-          acc.p3[0] = __builtin_amdgcn_mfma_f64_16x16x4f64(hx + hy, xx - xy, acc.p3[0], 0, 0, 0);
+          mfma_acc_add<1, R>(acc, 0, v, x[s]);
         }
         wave_sync();
       };
@@ -204,7 +167,7 @@ __global__ __launch_bounds__(kThreads, 2) void k_vjp_point(DevPlan P, VjpPtrs<R>
           const bool nxt = p == 2 * K + 1;
           const bool ok = valid && p < NP && p >= 2 * K && digit(s) + two <= cj[s] - 2 && (!nxt || has_next);
           const cx<R> v = ld(ok ? global_at<const cx<R>>(hp[K * kPtPos + p]) + (nxt ? up : r) : f0);
-          h[s] = cscale(ok ? v : czero<R>(), isq[digit(s) + 1 + two]);
+          h[s] = cscale(csel(ok, v, czero<R>()), isq[digit(s) + 1 + two]);
         }
         load_x(K, (uint32_t)vb & 0xffffu, x);
         cx<R> pv = czero<R>(), gc = czero<R>();
@@ -212,10 +175,10 @@ __global__ __launch_bounds__(kThreads, 2) void k_vjp_point(DevPlan P, VjpPtrs<R>
           const bool has_diag_reader = (K > 0) || (mK + 1 <= P.CD[0] - 2);
           const bool lv = valid && has_diag_reader;
           const cx<R> g = ld(lv ? V.gcur[fam_f1k(K)] + r : f0);
-          gc = lv ? g : czero<R>();
+          gc = csel(lv, g, czero<R>());
           if (!kCol) {
             const cx<R> v = ld(valid ? V.fcur[fam_f1k(K)] + r : f0);
-            pv = valid ? v : czero<R>();
+            pv = csel(valid, v, czero<R>());
           }
         }
         v4 re, im;
@@ -229,7 +192,7 @@ __global__ __launch_bounds__(kThreads, 2) void k_vjp_point(DevPlan P, VjpPtrs<R>
           const bool first = p == 2 * K;
           const cx<R> u = cscale(cmake<R>(re[s], im[s]), sq[digit(s) + (first ? 1 : 0)]);
           if (first)
-            g0 = cadd(g0, valid ? u : czero<R>());
+            g0 = cadd(g0, csel(valid, u, czero<R>()));
           else if (valid && p < NP && p > 2 * K && digit(s) > 0)
             st(global_at<cx<R>>(gp[K * kPtPos + p]) + down(s), u);
         }
@@ -255,7 +218,7 @@ __global__ __launch_bounds__(kThreads, 2) void k_vjp_point(DevPlan P, VjpPtrs<R>
             const bool ok = valid && p < NP && room >= 0;
             const bool bridge = side == 0 && j <= K0 && digit(s) <= cj[s] - 2;   // its cotangent is at hand
             const cx<R> v = ld(ok && !bridge ? global_at<const cx<R>>(hp[MD * kPtPos + p]) + r : f0);
-            h[s] = cscale(ok ? (bridge ? yk[s] : v) : czero<R>(), isq[digit(s) + 1]);
+            h[s] = cscale(csel(ok, csel(bridge, yk[s], v), czero<R>()), isq[digit(s) + 1]);
           }
           load_x(MD, (uint32_t)vb & 0xffffu, x);
           v4 re, im;
@@ -271,7 +234,7 @@ __global__ __launch_bounds__(kThreads, 2) void k_vjp_point(DevPlan P, VjpPtrs<R>
           cx<R> G0 = czero<R>();
           if (!kCol) {
             const cx<R> v = ld(f0 + r);
-            G0 = valid ? v : G0;
+            G0 = csel(valid, v, G0);
           }
           gdiag = dot_b(h, G0, re, im);
           reduce(h, x);

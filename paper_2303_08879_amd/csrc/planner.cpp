@@ -308,8 +308,8 @@ fd_status build_plan(int M, const int* cutoffs, uint32_t mask, fd_dtype dt, uint
     const size_t rows = std::max(fwd_lds_bytes_for(*P, chunk_geo(*P)), fwd_lds_bytes_for(*P, chunk_geo(*P, kBT / 2)));
     P->st_fwd = P->MD > 0 && rows > kMaxLds;
     P->st_ufill = ufill_lds_bytes(*P, false) > kMaxLds;
-    P->vjp_waves = kVjpWaves;
-    if (vjp_lds_bytes(*P) > kMaxLds) P->vjp_waves = kVjpWavesLds;
+    P->vjp_short = false;
+    if (vjp_lds_bytes(*P) > kMaxLds) P->vjp_short = true;
     P->st_vjp = P->MD > 0 && vjp_lds_bytes(*P) > kMaxLds;
     P->st_ufill_vjp = ufill_lds_bytes(*P, true) > kMaxLds;
   }
@@ -399,17 +399,18 @@ ChunkGeo chunk_geo(const Plan& Pl, int target) {
   return G;
 }
 
-// Dynamic LDS of the block reverse kernel for a chunk geometry: the forward
-// pivot rows, the undetected-neighbour terms, each wavefront's record
-// staging batch and A, b (or the pair table of the final fold, if larger), then the
-// square-root tables.
+// Dynamic LDS of the block reverse kernel for a chunk geometry: the square-root
+// tables, the three pointer tables, each wavefront's tile that turns h, then
+// (unless streamed) the b terms, own rows and undetected-neighbour terms; or the
+// pair tables of the final fold, if larger.
 size_t vjp_lds_bytes_for(const Plan& Pl, const ChunkGeo& G) {
-  const size_t eb = elem_bytes(Pl.dt), rb = eb / 2;
-  const int MD = Pl.MD, NPD = 2 * MD, NR = Pl.npos + 1, WV = Pl.vjp_waves;
-  const size_t rows = Pl.st_vjp ? 0 : (size_t)(G.RC + 1) * G.R0 + (size_t)Pl.nq * (G.RC + 2) * G.R0;
-  const size_t ents = rows + (size_t)WV * (kBlockBatch + 1) * (NPD + NR);
-  return std::max((ents + (size_t)Pl.npos * (Pl.npos + 1)) * eb, (size_t)WV * NPD * NR * 16) +
-         2 * (kMaxCut + 4) * rb;
+  const size_t eb = elem_bytes(Pl.dt);
+  const int MD = Pl.MD, NPD = 2 * MD, NR = Pl.npos + 1;
+  const size_t rows =
+      Pl.st_vjp ? 0 : ((size_t)(G.RC + 1) + G.RC + (size_t)Pl.nq * (G.RC + 2)) * G.R0;
+  return std::max(2 * (kMaxCut + 4) * (eb / 2) + 3 * (size_t)(MD + 1) * 16 * 8 +
+                      ((size_t)kVjpWaves * NPD * 17 + rows) * eb,
+                  (size_t)kVjpWaves * NPD * NR * 16);
 }
 
 // Chunk geometry of a forward level with nwork lattice points (its units
@@ -427,13 +428,12 @@ ChunkGeo fwd_geo(const Plan& Pl, int64_t nwork) {
 }
 
 // Row chunks of the reverse block kernel: own entries per unit on large
-// levels, on levels with fewer than `small_units` units, and that threshold.
-// Four wavefronts take 128 entries each (48 on small levels): a chunk's two
-// halo rows then cost less of its time (5-mode conditional reverse 6.2 -> 5.7
-// ms, 6-mode gradient circuit 12.9 -> 10.4 ms); two wavefronts keep 64 (32).
+// levels, on levels with fewer than `small_units` units, and that threshold: 512
+// (192 on small levels), so that a chunk's two halo rows are a small part of its
+// time; 128 (64) where the taller rows do not fit the LDS.
 VjpChunking vjp_chunking(const Plan& Pl) {
-  if (Pl.vjp_waves == kVjpWaves) return {128 * kVjpWaves, 48 * kVjpWaves, 1024};
-  return {64 * Pl.vjp_waves, 32 * Pl.vjp_waves, kSmallLevelUnits};
+  if (!Pl.vjp_short) return {128 * kVjpWaves, 48 * kVjpWaves, 1024};
+  return {32 * kVjpWaves, 16 * kVjpWaves, kSmallLevelUnits};
 }
 
 // Chunk geometry of a reverse level with nwork lattice points.

@@ -258,9 +258,9 @@ __device__ __forceinline__ void fwd_point_item(const DevPlan& P, const PtLds<R>&
         const cx<R> v = ld(a);
         if (DUAL) {
           const cx<R> u = ld(tangent_of(a, dT));
-          tx[s] = cscale(ok ? u : czero<R>(), w);
+          tx[s] = cscale(csel(ok, u, czero<R>()), w);
         }
-        x[s] = cscale(ok ? v : czero<R>(), w);
+        x[s] = cscale(csel(ok, v, czero<R>()), w);
       }
     };
     // targets of a pivot of value p (tangent tp) with reads x (tx)

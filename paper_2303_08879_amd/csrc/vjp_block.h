@@ -10,317 +10,299 @@
 namespace fd {
 
 // ---------------------------------------------------------------------------
-// Algorithm 2 reverse step.  One workgroup of WV wavefronts per (lattice
+// Algorithm 2 reverse step.  One workgroup of four wavefronts per (lattice
 // point, chunk of rows of the first undetected coordinate).  The undetected
 // neighbour terms make the cotangent of a pivot entry pull from the entry one
 // row below, so a chunk recomputes the target cotangents of two rows past its
 // own (bridge pivots: the rows its diagonal pivot needs; diagonal pivot: one
-// row), without storing them.  Four wavefronts with chunks of about 128
-// entries each (48 on levels with few units) make that recomputation a small
-// part of a chunk; plans whose four-wavefront staging does not fit the LDS,
-// and streamed rows, run two wavefronts with 64-entry chunks (the chunk
-// heights are set by the planner).
-// Abar records are folded per wavefront: each wave stages NB records at a
-// time in its own LDS region and reduces them on the matrix cores into its
-// own accumulators; the waves' tables are added in wave order at the end.
+// row), without storing them.
+// The entries of a chunk are the columns of the products, 16 per wavefront and
+// step as in the point kernel: u = [A b]^H h gives the cotangents of the undetected
+// neighbours (rows 0..NQ-1, kept in LDS: the entry below picks them up), of the
+// detected reads (stored to their only reader's slot) and of the pivot (the last
+// row); D += h conj(x)^T over the chunk's own entries gives Abar and bbar.  The read
+// values come from memory in the operand's layout, the undetected neighbours' from
+// the pivot's own row (a cache hit).  Everything but the entry's index is
+// uniform over a (lattice point, bridge), so a lane keeps one pointer per position.
+// What bounds it: 48 bytes per computed amplitude.  One entry per lane held two
+// full vectors and staged them in LDS, 76 KB per workgroup; it moved 1.9 TB/s.
+// ST: the neighbour terms, b terms and own rows in the workgroup's private
+// slot in global memory (blocks whose rows do not fit the LDS); the
+// __syncthreads between phases are workgroup-scope fences.
 // ---------------------------------------------------------------------------
-template <int MD, int NQ, typename R, int NB, bool ST, int WV>
-__global__ __launch_bounds__(64 * WV) void k_vjp_block(DevPlan P, VjpPtrs<R> V, const cx<R>* __restrict__ Ai,
-                                                        const cx<R>* __restrict__ bi, int S, int nwork,
-                                                        ChunkGeo G, double2* __restrict__ partial) {
-  constexpr int NPD = 2 * MD;
-  constexpr int NPOS = NQ + NPD;
-  constexpr int NR = NPOS + 1;
-  constexpr int NPAIR = NPD * NR;
-  // Abar / bbar records (the target cotangents h and the read values x of
-  // one entry) are staged NB lanes at a time and reduced on the matrix cores,
-  // as in the point kernel; the read values of a lane are formed when its
-  // batch is staged.
-  constexpr int RS = NB + 1;
-  static_assert(NB % 4 == 0 && 64 % NB == 0, "batches of whole MFMA steps that tile the wavefront");
+template <int MD, int NQ, typename R, bool ST>
+__global__ __launch_bounds__(64 * kVjpWaves, 2) void k_vjp_block(DevPlan P, VjpPtrs<R> V, const cx<R>* __restrict__ Ai,
+                                                                 const cx<R>* __restrict__ bi, int S, int nwork,
+                                                                 ChunkGeo G, double2* __restrict__ partial) {
+  constexpr int NPD = 2 * MD, NPOS = NQ + NPD, NR = NPOS + 1, NPAIR = NPD * NR;
+  constexpr int KS = (NPD + 3) / 4;      // steps over the targets
+  constexpr int NT = (NR + 15) / 16;     // tiles of rows of u, and of columns of D
+  constexpr int WV = kVjpWaves;
+  typedef typename Mma<R>::v4 v4;
   extern __shared__ __align__(16) unsigned char smem_raw[];
   const int B = P.B, R0 = G.R0, RC = G.RC;
   const int nrow1 = (RC + 1) * R0, nrow2 = (RC + 2) * R0;
-  // entries each lane reads back only itself (same entry-to-lane map in every
-  // loop of a unit): the workgroup's private slot in global memory, which
-  // leaves the LDS to the shared rows and raises the wavefronts per CU
-  cx<R>* gpk = V.priv + (size_t)blockIdx.x * V.priv_stride;   // MD x rows [k0, k1+1)
-  cx<R>* gbv = gpk + (size_t)MD * nrow1;                       // rows [k0, k1+1)
-  cx<R>* g0a = gbv + nrow1;                                    // own rows
-  // the forward pivot rows [k0-1, k1) and the undetected-neighbour terms of
-  // NQ x rows [k0, k1+2): in LDS, or (ST, blocks whose rows do not fit) the
-  // pivot rows read from HBM where they lie and the terms in the private
-  // slot after the own rows (the __syncthreads between phases are
-  // workgroup-scope fences)
-  cx<R>* lfw = reinterpret_cast<cx<R>*>(smem_raw);
-  cx<R>* qv = ST ? g0a + (size_t)RC * R0 : lfw + nrow1;
-  cx<R>* rec = ST ? lfw : qv + (size_t)NQ * nrow2;   // waves x RS x (NPD + NR)
-  cx<R>* sA = rec + (size_t)WV * RS * (NPD + NR);   // A (NPOS x NPOS) then b (NPOS)
-  const cx<R>* sb = sA + NPOS * NPOS;
-  R* sq = reinterpret_cast<R*>(sA + NPOS * NPOS + NPOS);
-  R* isq = sq + (kMaxCut + 4);
-  for (int v = threadIdx.x; v < kMaxCut + 4; v += blockDim.x) {
-    sq[v] = sqrt(R(v));
-    isq[v] = v ? R(1) / sqrt(R(v)) : R(0);
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, c = lane & 15, kq = lane >> 4;
+  R* sq = reinterpret_cast<R*>(smem_raw);
+  const R* isq = sq + (kMaxCut + 4);
+  uint64_t* hp = reinterpret_cast<uint64_t*>(sq + 2 * (kMaxCut + 4));
+  uint64_t* gp = hp + pt_table_entries(MD);
+  uint64_t* xp = gp + pt_table_entries(MD);
+  cx<R>* turn = reinterpret_cast<cx<R>*>(xp + pt_table_entries(MD));   // waves x NPD x kTurn
+  cx<R>* rows = turn + WV * NPD * kTurn;
+  turn += wave * NPD * kTurn;
+  cx<R>* gpk = V.priv + (size_t)blockIdx.x * V.priv_stride;   // bridge pivots' cotangents, MD x rows [k0, k1+1)
+  cx<R>* gbv = ST ? gpk + (size_t)MD * nrow1 : rows;          // b^H h of the bridge, rows [k0, k1+1)
+  cx<R>* g0a = gbv + nrow1;                                   // F0 cotangent, own rows
+  cx<R>* qv = g0a + RC * R0;                                  // neighbour terms, NQ x rows [k0, k1+2)
+  {
+    const R* t = reinterpret_cast<const R*>(P.sqt);
+    for (int i = threadIdx.x; i < 2 * (kMaxCut + 4); i += blockDim.x) sq[i] = t[i];
   }
-  for (int i = threadIdx.x; i < NPOS * NPOS + NPOS; i += blockDim.x) sA[i] = ld(Ai + i);
-  // (one wavefront per workgroup: every phase of a unit starts with a staging
-  // loop and a barrier before it reads these tables)
-  cx<R>* recw = rec + (size_t)(threadIdx.x >> 6) * RS * (NPD + NR);
-  const int lane = threadIdx.x & 63;
-  MfmaAcc<(NR + 15) / 16> acc;
+  pt_fill_vjp_pointers<MD, true, R>(V, hp, gp, xp);
+  // [A b]^H: row l = 16 t + row, column i = 4 s + kq
+  R ar[NT][KS], ai[NT][KS];
+#pragma unroll
+  for (int t = 0; t < NT; ++t)
+#pragma unroll
+    for (int s = 0; s < KS; ++s) {
+      const int l = 16 * t + Mma<R>::row_pos(c), i = 4 * s + kq;
+      const bool in = l < NR && i < NPD;
+      const cx<R> v = ld(!in ? Ai : l < NPOS ? Ai + (NQ + i) * NPOS + l : bi + NQ + i);
+      ar[t][s] = in ? v.x : R(0);
+      ai[t][s] = in ? -v.y : R(0);
+    }
+  // the undetected coordinate of a lane whose read is a neighbour (columns l < NQ)
+  const int ql = min(c, NQ - 1);
+  const int us = P.ustride[ql], ud = P.udims[ql];
+  // single precision splits entries below 65536 exactly: (e + 1/2) / us lies at
+  // least 1 / (2 us) from an integer, the product is off by less than e 2^-23 / us
+  const float ui = 1.0f / (float)us, di = 1.0f / (float)ud;
+  int cj[KS];
+#pragma unroll
+  for (int s = 0; s < KS; ++s) cj[s] = P.CD[min((4 * s + kq) >> 1, MD - 1)];
+  MfmaAcc<NT> acc;
   mfma_acc_zero(acc);
+  __syncthreads();
 
   for (int w = blockIdx.x; w < nwork * G.nchunks; w += gridDim.x) {
-    const int r = w / G.nchunks, c = w - r * G.nchunks;
-    const int k0 = c * RC, k1 = min(G.C0, k0 + RC);
-    const int e_own0 = k0 * R0, e_own1 = k1 * R0;
-    int m[MD], rdn[MD], rup[MD];
-    node_record<MD>(V.node, r, m, rdn, rup);
+    const int r = w / G.nchunks, ch = w - r * G.nchunks;
+    const int k0 = ch * RC, k1 = min(G.C0, k0 + RC);
+    const int e0 = k0 * R0, e1 = k1 * R0;                          // own entries
+    const int eb1 = min(G.C0, k1 + 1) * R0, eq1 = min(G.C0, k1 + 2) * R0;
+    const int nrec = V.node[(size_t)r * kNodeStride + min(lane, kNodeStride - 1)];
+    auto m_of = [&](int j) { return __shfl(nrec, j); };
+    auto down = [&](int j) { return __shfl(nrec, MD + j); };
+    const int m0 = __builtin_amdgcn_readlane(nrec, 0);
+    const size_t rB = (size_t)r * B;
+    if (m0 > P.CD[0] - 2) {   // no pivot here (uniform)
+      for (int e = e0 + threadIdx.x; e < e1; e += blockDim.x) st(V.gcur[0] + rB + e, ld(V.d0cur + rB + e));
+      continue;
+    }
     int K0 = MD;
 #pragma unroll
     for (int d = MD - 1; d >= 0; --d)
-      if (m[d] > 0) K0 = d;
-    const size_t rB = (size_t)r * B;
-    // forward pivot row entry e of the current phase's pivot block
-    const cx<R>* fsrc = nullptr;
-    auto LF = [&](int e) -> cx<R> {
-      if constexpr (ST)
-        return ld(at32(fsrc, (uint32_t)e));
-      else
-        return lfw[e - (k0 - 1) * R0];
+      if (__builtin_amdgcn_readlane(nrec, d) > 0) K0 = d;
+
+    // sum over the undetected neighbours above entry e of their terms
+    auto neighbours = [&](int e, cx<R> v) -> cx<R> {
+      int rem = e;
+#pragma unroll
+      for (int q = 0; q < NQ; ++q) {
+        const int k = ucoord(P, rem, q);
+        rem -= k * P.ustride[q];
+        if (k + 1 < P.udims[q]) v = cadd(v, cscale(qv[(size_t)q * nrow2 + (e - e0) + P.ustride[q]], sq[k + 1]));
+      }
+      return v;
     };
-    for (int e = e_own0 + threadIdx.x; e < e_own1; e += blockDim.x) g0a[e - e_own0] = ld(at32(V.d0cur, (uint32_t)(r * B + e)));
 
-#pragma unroll
-    for (int K = 0; K < MD; ++K) {
-      if (K > K0 || m[K] > P.CD[K] - 2) continue;   // uniform
-      fsrc = V.fcur[fam_f1k(K)] + rB;
-      if constexpr (!ST) {
-        const int e0 = max(0, k0 - 1) * R0;
-        for (int e = e0 + threadIdx.x; e < e_own1; e += blockDim.x) lfw[e - (k0 - 1) * R0] = ld(fsrc + e);
-      }
-      __syncthreads();
-      const int eq1 = min(G.C0, k1 + 2) * R0, eb1 = min(G.C0, k1 + 1) * R0;
-      const bool has_diag_reader = (K > 0) || (m[0] + 1 <= P.CD[0] - 2);
-      for (int base = e_own0; base < eq1; base += blockDim.x) {
-        const int e = base + threadIdx.x;
-        const bool live = e < eq1, own = e < e_own1;
-        // the record's read values, loaded by every lane with the cotangents
-        // (one memory round trip for both, and for both record batches)
-        const bool rec_ok = live && own;
-        cx<R> xr[NR];
-#pragma unroll
-        for (int l = 0; l < NR; ++l) xr[l] = czero<R>();
-        if (rec_ok) {
-          int rem = e;
-#pragma unroll
-          for (int q = 0; q < NQ; ++q) {
-            const int kq = ucoord(P, rem, q);
-            rem -= kq * P.ustride[q];
-            if (kq > 0) xr[q] = cscale(LF(e - P.ustride[q]), sq[kq]);
-          }
-          xr[NPOS] = LF(e);
-          xr[NQ + 2 * K] = cscale(ld(at32(V.fcur[0], (uint32_t)(r * B + e))), sq[m[K] + 1]);
-          if (m[K] > 0)
-            xr[NQ + 2 * K + 1] = cscale(ld(at32(V.fprev[fam_f2(MD, K)], (uint32_t)(rdn[K] * B + e))), sq[m[K]]);
-#pragma unroll
-          for (int j = K + 1; j < MD; ++j) {
-            if (m[j] > 0) {
-              xr[NQ + 2 * j] = cscale(ld(at32(V.fprev[fam_1001(MD, K, j)], (uint32_t)(rdn[j] * B + e))), sq[m[j]]);
-              xr[NQ + 2 * j + 1] = cscale(ld(at32(V.fprev[fam_1010(MD, K, j)], (uint32_t)(rdn[j] * B + e))), sq[m[j]]);
-            }
-          }
-        }
-        cx<R> h[NPD];
-#pragma unroll
-        for (int i = 0; i < NPD; ++i) h[i] = czero<R>();
-        if (live) {
-          h[2 * K + 1] = cscale(ld(at32(V.gf0nxt, (uint32_t)(rup[K] * B + e))), isq[m[K] + 1]);
-          if (m[K] <= P.CD[K] - 3) h[2 * K] = cscale(ld(at32(V.gcur[fam_f2(MD, K)], (uint32_t)(r * B + e))), isq[m[K] + 2]);
-#pragma unroll
-          for (int j = K + 1; j < MD; ++j) {
-            if (m[j] <= P.CD[j] - 2) {
-              h[2 * j] = cscale(ld(at32(V.gcur[fam_1010(MD, K, j)], (uint32_t)(r * B + e))), isq[m[j] + 1]);
-              h[2 * j + 1] = cscale(ld(at32(V.gcur[fam_1001(MD, K, j)], (uint32_t)(r * B + e))), isq[m[j] + 1]);
-            }
-          }
-#pragma unroll
-          for (int q = 0; q < NQ; ++q) {
-            cx<R> u = czero<R>();
-#pragma unroll
-            for (int i = 2 * K; i < NPD; ++i) cfma_conj(u, sA[(NQ + i) * NPOS + q], h[i]);
-            qv[(size_t)q * nrow2 + (e - e_own0)] = u;
-          }
-          if (e < eb1) {
-            cx<R> gb = czero<R>();
-#pragma unroll
-            for (int i = 2 * K; i < NPD; ++i) cfma_conj(gb, sb[NQ + i], h[i]);
-            gbv[e - e_own0] = gb;
-          }
-          if (own) {
-#pragma unroll
-            for (int l = 2 * K; l < NPD; ++l) {
-              const int j = l >> 1;
-              if (l != 2 * K && m[j] == 0) continue;
-              cx<R> u = czero<R>();
-#pragma unroll
-              for (int i = 2 * K; i < NPD; ++i) cfma_conj(u, sA[(NQ + i) * NPOS + NQ + l], h[i]);
-              if (l == 2 * K) {
-                g0a[e - e_own0] = cadd(g0a[e - e_own0], cscale(u, sq[m[K] + 1]));
-              } else if (l == 2 * K + 1) {
-                st(at32(V.gprev[fam_f2(MD, K)], (uint32_t)(rdn[K] * B + e)), cscale(u, sq[m[K]]));
-              } else {
-                st(at32(V.gprev[(l & 1) ? fam_1010(MD, K, j) : fam_1001(MD, K, j)], (uint32_t)(rdn[j] * B + e)),
-                   cscale(u, sq[m[j]]));
-              }
-            }
-          }
-        }
-        // Abar records of the own entries, NB lanes at a time
+    // the pivots: K < MD the bridges d(m) + 1_ket(K), then (K = MD) the diagonal
 #pragma unroll 1
-        for (int qb = 0; qb < 64 / NB; ++qb) {
-          const bool grp = (lane / NB) == qb;
-          if (__ballot(rec_ok && grp) == 0ull) continue;   // uniform over the wave
-          if (grp) {
-            const int col = lane - qb * NB;
+    for (int K = 0; K <= MD; ++K) {
+      const bool diag = K == MD;
+      if (!diag && K > K0) continue;
+      const int mK = diag ? 0 : __builtin_amdgcn_readlane(nrec, K);
+      if (!diag && mK > P.CD[K] - 2) continue;   // uniform
+      const int up = diag ? 0 : __builtin_amdgcn_readlane(nrec, 2 * MD + K);
+      const int ee = diag ? eb1 : eq1;                        // entries [e0, ee) of the targets
+      const cx<R>* pv = V.fcur[diag ? 0 : fam_f1k(K)] + rB;   // the pivot's values
+      // targets: pointer and scale of each of the lane's positions
+      const cx<R>* hptr[KS];
+      R hw[KS];
+      uint32_t hv = 0;
 #pragma unroll
-            for (int l = 0; l < NR; ++l) recw[(NPD + l) * RS + col] = xr[l];
-#pragma unroll
-            for (int i = 0; i < NPD; ++i) recw[i * RS + col] = rec_ok ? h[i] : czero<R>();
-          }
-          wave_sync();
-          wave_accum_mfma<R, NPD, NR, NB>(recw, acc);
-          wave_sync();
-        }
+      for (int s = 0; s < KS; ++s) {
+        const int p = 4 * s + kq, j = min(p >> 1, MD - 1), side = p & 1;
+        const int mj = m_of(j);
+        const int two = p == 2 * K ? 1 : 0;
+        const int room = cj[s] - 2 - mj - (diag && j == 0 ? side : two);
+        const bool ok = p < NPD && room >= 0 && (diag || p >= 2 * K);
+        const bool bridge = diag && side == 0 && j <= K0 && mj <= cj[s] - 2;   // its cotangent is at hand
+        const cx<R>* t = global_at<const cx<R>>(hp[K * kPtPos + p]) + (p == 2 * K + 1 ? (size_t)up * B : rB);
+        t = bridge ? gpk + (size_t)j * nrow1 - e0 : t;
+        hptr[s] = ok ? t : pv;
+        hw[s] = isq[mj + 1 + two];
+        hv |= (ok ? 1u : 0u) << s;
       }
-      __syncthreads();
-      // total cotangent of the bridge pivot block F1k(K)(m), rows [k0, k1+1)
-      for (int e = e_own0 + threadIdx.x; e < eb1; e += blockDim.x) {
-        int rem = e;
-        const int le = e - e_own0;
-        cx<R> v = gbv[le];
-        if (has_diag_reader) v = cadd(v, ld(at32(V.gcur[fam_f1k(K)], (uint32_t)(r * B + e))));
+      // read values: columns l = 16 t + c
+      const cx<R>* xptr[NT];
+      R xw[NT];
+      uint32_t xv = 0;
 #pragma unroll
-        for (int q = 0; q < NQ; ++q) {
-          const int kq = ucoord(P, rem, q);
-          rem -= kq * P.ustride[q];
-          if (kq + 1 < P.udims[q]) v = cadd(v, cscale(qv[(size_t)q * nrow2 + le + P.ustride[q]], sq[kq + 1]));
-        }
-        gpk[(size_t)K * nrow1 + le] = v;
+      for (int t = 0; t < NT; ++t) {
+        const int l = 16 * t + c, p = l - NQ, pc = min(max(p, 0), NPD - 1), j = pc >> 1;
+        const int mj = m_of(j), dn = down(j);
+        const bool first = p == 2 * K, det = p >= 0 && p < NPD;
+        const bool ok = l < NR && (!det || first || ((diag || p > 2 * K) && mj > 0));
+        xptr[t] = !ok || !det ? pv : global_at<const cx<R>>(xp[K * kPtPos + pc]) + (first ? rB : (size_t)dn * B);
+        xw[t] = det ? sq[mj + (first ? 1 : 0)] : R(1);
+        xv |= (ok ? 1u : 0u) << t;
       }
-      __syncthreads();
-    }
-
-    if (m[0] <= P.CD[0] - 2) {
-      fsrc = V.fcur[0] + rB;
-      if constexpr (!ST) {
-        const int e0 = max(0, k0 - 1) * R0;
-        for (int e = e0 + threadIdx.x; e < e_own1; e += blockDim.x) lfw[e - (k0 - 1) * R0] = ld(fsrc + e);
+      // where the rows of u go: the cotangents of the detected reads to their
+      // slots in memory; the neighbour terms, the b terms and the F0 cotangent
+      // (added to) to the unit's rows, at offset loff, entries below lend
+      cx<R>* gptr[NT * 4];
+      R gw[NT * 4];
+      int loff[NT * 4], lend[NT * 4];
+      uint32_t gv = 0, lsum = 0;
+#pragma unroll
+      for (int t = 0; t < NT * 4; ++t) {
+        const int l = 4 * t + kq, p = l - NQ, pc = min(max(p, 0), NPD - 1), j = pc >> 1;
+        const int mj = m_of(j), dn = down(j);
+        const bool det = p >= 0 && p < NPD, first = p == 2 * K;
+        const bool ok = det && (diag || p > 2 * K) && mj > 0;
+        gptr[t] = global_at<cx<R>>(gp[K * kPtPos + pc]) + (ok ? (size_t)dn * B : 0);
+        gw[t] = det ? sq[first ? mK + 1 : mj] : R(1);
+        gv |= (ok ? 1u : 0u) << t;
+        const bool nb = l < NQ, piv = l == NPOS;
+        loff[t] = nb ? (2 * RC + 1) * R0 + l * nrow2 : piv && !diag ? 0 : nrow1;
+        lend[t] = nb ? ee : piv && !diag ? eb1 : piv || (det && first) ? e1 : e0;
+        lsum |= (piv ? diag : first) ? 1u << t : 0u;
       }
-      __syncthreads();
-      const int eq1 = min(G.C0, k1 + 1) * R0;
-      for (int base = e_own0; base < eq1; base += blockDim.x) {
-        const int e = base + threadIdx.x;
-        const bool live = e < eq1, own = e < e_own1;
-        // the record's read values, loaded with the cotangents
-        const bool rec_ok = live && own;
-        cx<R> xr[NR];
-#pragma unroll
-        for (int l = 0; l < NR; ++l) xr[l] = czero<R>();
-        if (rec_ok) {
-          int rem = e;
-#pragma unroll
-          for (int q = 0; q < NQ; ++q) {
-            const int kq = ucoord(P, rem, q);
-            rem -= kq * P.ustride[q];
-            if (kq > 0) xr[q] = cscale(LF(e - P.ustride[q]), sq[kq]);
-          }
-          xr[NPOS] = LF(e);
-#pragma unroll
-          for (int j = 0; j < MD; ++j) {
-            if (m[j] > 0) {
-              xr[NQ + 2 * j] = cscale(ld(at32(V.fprev[fam_f1b(MD, j)], (uint32_t)(rdn[j] * B + e))), sq[m[j]]);
-              xr[NQ + 2 * j + 1] = cscale(ld(at32(V.fprev[fam_f1k(j)], (uint32_t)(rdn[j] * B + e))), sq[m[j]]);
-            }
-          }
+      // read column t of entry ex: neighbour columns read the entry one step
+      // down in their coordinate, with its square root as weight
+      auto xcol = [&](int t, int ex, int* at, R* wt) -> bool {
+        bool ok = ex < e1 && ((xv >> t) & 1);
+        *at = ex;
+        *wt = xw[t];
+        if (t == 0) {
+          const int q = (int)(((float)ex + 0.5f) * ui);
+          const int kc = q - ud * (int)(((float)q + 0.5f) * di);
+          const bool nb = c < NQ;
+          const R wq = sq[kc];
+          ok = ok && (!nb || kc > 0);
+          *at = nb ? ex - us : ex;
+          *wt = nb ? wq : *wt;
         }
-        cx<R> h[NPD];
+        *at = ok ? *at : e0;
+        return ok;
+      };
+      // the tile's loads, unconditional and unscaled: issued one tile ahead
+      // (a load waited on within the tile's work would wait for them all)
+      auto issue = [&](int eb, cx<R>(&h)[KS], cx<R>(&x)[NT][4], cx<R>& d0) {
+        const int e = eb + c;
+        if (K == 0) d0 = ld(V.d0cur + rB + min(e, e1 - 1));
 #pragma unroll
-        for (int i = 0; i < NPD; ++i) h[i] = czero<R>();
-        if (live) {
-          const int le = e - e_own0;
+        for (int s = 0; s < KS; ++s) h[s] = ld(hptr[s] + (e < ee ? e : e0));
+        if (eb < e1) {
 #pragma unroll
-          for (int j = 0; j < MD; ++j) {
-            if (j == 0 || m[j] <= P.CD[j] - 2) {
-              const bool bridge = j <= K0 && m[j] <= P.CD[j] - 2;
-              const cx<R> gt = bridge ? gpk[(size_t)j * nrow1 + le] : ld(at32(V.gcur[fam_f1k(j)], (uint32_t)(r * B + e)));
-              h[2 * j] = cscale(gt, isq[m[j] + 1]);
+          for (int t = 0; t < NT; ++t)
+#pragma unroll
+            for (int s = 0; s < 4; ++s) {
+              int at;
+              R wt;
+              (void)xcol(t, eb + 4 * s + kq, &at, &wt);
+              x[t][s] = ld(xptr[t] + at);
             }
-            const bool okb = (j == 0) ? (m[0] <= P.CD[0] - 3) : (m[j] <= P.CD[j] - 2);
-            if (okb) h[2 * j + 1] = cscale(ld(at32(V.gcur[fam_f1b(MD, j)], (uint32_t)(r * B + e))), isq[m[j] + 1]);
-          }
-#pragma unroll
-          for (int q = 0; q < NQ; ++q) {
-            cx<R> u = czero<R>();
-#pragma unroll
-            for (int i = 0; i < NPD; ++i) cfma_conj(u, sA[(NQ + i) * NPOS + q], h[i]);
-            qv[(size_t)q * nrow2 + le] = u;
-          }
-          if (own) {
-#pragma unroll
-            for (int l = 0; l < NPD; ++l) {
-              const int j = l >> 1;
-              if (m[j] == 0) continue;
-              cx<R> u = czero<R>();
-#pragma unroll
-              for (int i = 0; i < NPD; ++i) cfma_conj(u, sA[(NQ + i) * NPOS + NQ + l], h[i]);
-              st(at32(V.gprev[(l & 1) ? fam_f1k(j) : fam_f1b(MD, j)], (uint32_t)(rdn[j] * B + e)), cscale(u, sq[m[j]]));
-            }
-            cx<R> gb = czero<R>();
-#pragma unroll
-            for (int i = 0; i < NPD; ++i) cfma_conj(gb, sb[NQ + i], h[i]);
-            g0a[le] = cadd(g0a[le], gb);
-          }
         }
-        // Abar records of the own entries, NB lanes at a time
+      };
+      cx<R> hn[KS], xn[NT][4], dn = czero<R>();
+      if (e0 + 16 * wave < ee) issue(e0 + 16 * wave, hn, xn, dn);
 #pragma unroll 1
-        for (int qb = 0; qb < 64 / NB; ++qb) {
-          const bool grp = (lane / NB) == qb;
-          if (__ballot(rec_ok && grp) == 0ull) continue;   // uniform over the wave
-          if (grp) {
-            const int col = lane - qb * NB;
+      for (int eb = e0 + 16 * wave; eb < ee; eb += 16 * WV) {
+        const int e = eb + c, le = e - e0;
+        const bool live = e < ee, own = e < e1;
+        const bool any_own = eb < e1;   // uniform
+        cx<R> h[KS], x[NT][4];
 #pragma unroll
-            for (int l = 0; l < NR; ++l) recw[(NPD + l) * RS + col] = xr[l];
+        for (int s = 0; s < KS; ++s) h[s] = hn[s];
 #pragma unroll
-            for (int i = 0; i < NPD; ++i) recw[i * RS + col] = rec_ok ? h[i] : czero<R>();
+        for (int t = 0; t < NT; ++t)
+#pragma unroll
+          for (int s = 0; s < 4; ++s) x[t][s] = xn[t][s];
+        const cx<R> d0 = dn;
+        if (eb + 16 * WV < ee) issue(eb + 16 * WV, hn, xn, dn);
+#pragma unroll
+        for (int s = 0; s < KS; ++s) {
+          const bool ok = live && ((hv >> s) & 1);
+          h[s] = cscale(csel(ok, h[s], czero<R>()), hw[s]);
+        }
+#pragma unroll
+        for (int t = 0; t < NT; ++t) {
+          v4 re, im;
+#pragma unroll
+          for (int s = 0; s < 4; ++s) re[s] = im[s] = R(0);
+#pragma unroll
+          for (int s = 0; s < KS; ++s) {
+            re = Mma<R>::mma(ar[t][s], h[s].x, re);
+            im = Mma<R>::mma(ar[t][s], h[s].y, im);
+            re = Mma<R>::mma(ai[t][s], -h[s].y, re);
+            im = Mma<R>::mma(ai[t][s], h[s].x, im);
           }
+#pragma unroll
+          for (int s = 0; s < 4; ++s) {
+            const int i = 4 * t + s;
+            if (4 * i >= NR) continue;   // no such rows
+            const cx<R> u = cscale(cmake<R>(re[s], im[s]), gw[i]);
+            cx<R>* slot = gbv + loff[i] + le;
+            if (e < lend[i]) {
+              cx<R> was = *slot;
+              was = csel(K == 0, d0, was);
+              *slot = cadd(u, csel((lsum >> i) & 1, was, czero<R>()));
+            }
+            if (own && ((gv >> i) & 1)) st(gptr[i] + e, u);
+          }
+        }
+        if (any_own) {
+          // D over the own entries (h of the others as zero)
+#pragma unroll
+          for (int s = 0; s < KS; ++s)
+            if (4 * s + kq < NPD) turn[(4 * s + kq) * kTurn + c] = csel(own, h[s], czero<R>());
           wave_sync();
-          wave_accum_mfma<R, NPD, NR, NB>(recw, acc);
+#pragma unroll
+          for (int s = 0; s < 4; ++s) {
+            const cx<R> ht = turn[min(c, NPD - 1) * kTurn + 4 * s + kq];
+#pragma unroll
+            for (int t = 0; t < NT; ++t) {
+              int at;
+              R wt;
+              const bool ok = xcol(t, eb + 4 * s + kq, &at, &wt);
+              mfma_acc_add<NT, R>(acc, t, ht, cscale(csel(ok, x[t][s], czero<R>()), wt));
+            }
+          }
           wave_sync();
         }
       }
       __syncthreads();
-      for (int e = e_own0 + threadIdx.x; e < e_own1; e += blockDim.x) {
-        int rem = e;
-        const int le = e - e_own0;
-        cx<R> v = g0a[le];
-#pragma unroll
-        for (int q = 0; q < NQ; ++q) {
-          const int kq = ucoord(P, rem, q);
-          rem -= kq * P.ustride[q];
-          if (kq + 1 < P.udims[q]) v = cadd(v, cscale(qv[(size_t)q * nrow2 + le + P.ustride[q]], sq[kq + 1]));
+      if (!diag) {
+        // total cotangent of the bridge pivot block F1k(K)(m), rows [k0, k1+1)
+        const bool has_diag_reader = (K > 0) || (m0 + 1 <= P.CD[0] - 2);
+        const cx<R>* gc = V.gcur[fam_f1k(K)] + rB;
+        for (int e = e0 + threadIdx.x; e < eb1; e += blockDim.x) {
+          cx<R> v = gbv[e - e0];
+          if (has_diag_reader) v = cadd(v, ld(gc + e));
+          gpk[(size_t)K * nrow1 + (e - e0)] = neighbours(e, v);
         }
-        g0a[le] = v;
+        __syncthreads();
       }
     }
-    for (int e = e_own0 + threadIdx.x; e < e_own1; e += blockDim.x) st(at32(V.gcur[0], (uint32_t)(r * B + e)), g0a[e - e_own0]);
+    for (int e = e0 + threadIdx.x; e < e1; e += blockDim.x) st(V.gcur[0] + rB + e, neighbours(e, g0a[e - e0]));
     __syncthreads();
   }
   // fold the waves' pair tables (in wave order) into this block's slot
   cx<double>* red = reinterpret_cast<cx<double>*>(smem_raw);
   __syncthreads();
-  mfma_acc_store<NPD, NR, NR>(acc, red + (size_t)(threadIdx.x >> 6) * NPAIR);
+  mfma_acc_store<NPD, NR, NR>(acc, red + (size_t)wave * NPAIR);
   __syncthreads();
   double2* slot = partial + (size_t)blockIdx.x * (NPOS * NR);
   for (int p = threadIdx.x; p < NPAIR; p += blockDim.x) {
@@ -336,24 +318,15 @@ __global__ __launch_bounds__(64 * WV) void k_vjp_block(DevPlan P, VjpPtrs<R> V, 
   }
 }
 
-template <int MD, int NQ, typename R, bool ST, int WV>
-static void launch_vjp_block_w(size_t shm, int grid, hipStream_t st, const DevPlan& P, const VjpPtrs<R>& Vp,
+template <int MD, int NQ, typename R, bool ST>
+static void launch_vjp_block_k(size_t shm, int grid, hipStream_t st, const DevPlan& P, const VjpPtrs<R>& Vp,
                                const cx<R>* Ai, const cx<R>* bi, int S, int nwork, const ChunkGeo& G,
                                double2* partial) {
   if (shm > 65536)
-    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&k_vjp_block<MD, NQ, R, kBlockBatch, ST, WV>),
+    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&k_vjp_block<MD, NQ, R, ST>),
                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)shm);
-  hipLaunchKernelGGL((k_vjp_block<MD, NQ, R, kBlockBatch, ST, WV>), dim3(grid), dim3(64 * WV), shm, st, P, Vp, Ai,
-                     bi, S, nwork, G, partial);
-}
-template <int MD, int NQ, typename R, bool ST>
-static void launch_vjp_block_k(int waves, size_t shm, int grid, hipStream_t st, const DevPlan& P,
-                               const VjpPtrs<R>& Vp, const cx<R>* Ai, const cx<R>* bi, int S, int nwork,
-                               const ChunkGeo& G, double2* partial) {
-  if constexpr (!ST)
-    if (waves == kVjpWaves)
-      return launch_vjp_block_w<MD, NQ, R, ST, kVjpWaves>(shm, grid, st, P, Vp, Ai, bi, S, nwork, G, partial);
-  launch_vjp_block_w<MD, NQ, R, ST, kVjpWavesLds>(shm, grid, st, P, Vp, Ai, bi, S, nwork, G, partial);
+  hipLaunchKernelGGL((k_vjp_block<MD, NQ, R, ST>), dim3(grid), dim3(64 * kVjpWaves), shm, st, P, Vp, Ai, bi, S, nwork,
+                     G, partial);
 }
 
 // Detected modes LO..LO + 3.
@@ -368,9 +341,9 @@ hipError_t launch_vjp_block_range(const Plan& Pl, const DevPlan& P, const VjpPtr
   const int grid = vjp_block_grid(Pl, nwork);
 #define FD_VJP_BLOCK_NQ(MDV, NQV)                                                                       \
   if (Pl.st_vjp)                                                                                   \
-    launch_vjp_block_k<MDV, NQV, R, true>(Pl.vjp_waves, shm, grid, st, P, Vp, Ai, bi, S, nwork, G, partial); \
+    launch_vjp_block_k<MDV, NQV, R, true>(shm, grid, st, P, Vp, Ai, bi, S, nwork, G, partial); \
   else                                                                                             \
-    launch_vjp_block_k<MDV, NQV, R, false>(Pl.vjp_waves, shm, grid, st, P, Vp, Ai, bi, S, nwork, G, partial);
+    launch_vjp_block_k<MDV, NQV, R, false>(shm, grid, st, P, Vp, Ai, bi, S, nwork, G, partial);
 #define FD_VJP_BLOCK(MDV)        \
   case LO + MDV:                 \
     if (Pl.nq == 2) {            \

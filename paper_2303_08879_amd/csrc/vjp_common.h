@@ -3,7 +3,7 @@
 // reverse sweep and the matrix-core reduction of the Abar / bbar records.
 #pragma once
 
-#include "fd_device.h"
+#include "pt_units.h"
 
 namespace fd {
 
@@ -22,21 +22,17 @@ struct VjpPtrs {
 
 // Abar / bbar: every reverse step reduces outer products of per-target
 // records (the target cotangents h and the read values x of one pivot
-// application) over all targets: D[i][l] = sum_rec h_i conj(x_l), i.e.
-// (H^T X-bar)[i][l], a dense contraction over the records.  A wavefront
-// stages NB records in LDS (row r of H or X holds value r of every record,
-// rows NB + 1 apart so the rows read together fall in different banks) and
-// runs NB / 4 FP64 MFMA 16x16x4 steps of four records: lane t feeds value
-// t % 16 of record k0 + t / 16 to both operands (one 16-byte LDS read each)
-// and keeps D[4 j + t / 16][16 c + t % 16], j = 0..3, of column tile c in its
-// accumulators (the gfx950 output layout, checked on the device).  The
-// complex products take three real products (Karatsuba's method):
-// P1 = Hr Xr, P2 = Hi Xi, P3 = (Hr + Hi)(Xr - Xi), each summed in its own
-// accumulator; the real part is P1 + P2 and the imaginary part (Hi Xr -
+// application) over all targets: D[i][l] = sum h_i conj(x_l), a dense
+// contraction over points or block entries, on FP64 MFMA 16x16x4 steps of four
+// of them: lane t feeds value t % 16 of number 4 s + t / 16 to both operands and
+// keeps D[4 j + t / 16][t % 16], j = 0..3 (the gfx950 output layout, checked on
+// the device).  The complex products take three real products (Karatsuba's
+// method): P1 = Hr Xr, P2 = Hi Xi, P3 = (Hr + Hi)(Xr - Xi), each summed in its
+// own accumulator; the real part is P1 + P2 and the imaginary part (Hi Xr -
 // Hr Xi) is P3 - P1 + P2.  Three MFMAs per step instead of four, and three
 // independent accumulation chains of one MFMA per step instead of two of
 // two.  The hardware fixes the order of accumulation, so the sums are
-// reproducible.  At most 16 rows of H (NPD) and 32 columns of X (NCOL).
+// reproducible.
 typedef double mfma_d4 __attribute__((ext_vector_type(4)));
 
 template <int NT>
@@ -54,28 +50,13 @@ __device__ __forceinline__ void mfma_acc_zero(MfmaAcc<NT>& a) {
   }
 }
 
-template <typename R, int NPD, int NCOL, int NB>
-__device__ __forceinline__ void wave_accum_mfma(const cx<R>* recw, MfmaAcc<(NCOL + 15) / 16>& acc) {
-  static_assert(NPD <= 16 && NCOL <= 32, "one row tile of H, at most two column tiles of X");
-  constexpr int NT = (NCOL + 15) / 16;
-  constexpr int RS = NB + 1;   // records per staging batch, padded row stride
-  const int lane = threadIdx.x & 63;
-  const int row = lane & 15, kq = lane >> 4;
-#pragma unroll 4
-  for (int k0 = 0; k0 < NB; k0 += 4) {
-    const int rc = k0 + kq;
-    const cx<R> h = row < NPD ? recw[row * RS + rc] : czero<R>();
-    const double hx = (double)h.x, hy = (double)h.y, hs = hx + hy;
-#pragma unroll
-    for (int t = 0; t < NT; ++t) {
-      const int col = 16 * t + row;
-      const cx<R> x = col < NCOL ? recw[(NPD + col) * RS + rc] : czero<R>();
-      const double xx = (double)x.x, xy = (double)x.y;
-      acc.p1[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(hx, xx, acc.p1[t], 0, 0, 0);
-      acc.p2[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(hy, xy, acc.p2[t], 0, 0, 0);
-      acc.p3[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(hs, xx - xy, acc.p3[t], 0, 0, 0);
-    }
-  }
+// One step: h and x are the lane's values, x for column tile t.
+template <int NT, typename R>
+__device__ __forceinline__ void mfma_acc_add(MfmaAcc<NT>& a, int t, const cx<R>& h, const cx<R>& x) {
+  const double hx = h.x, hy = h.y, xx = x.x, xy = x.y;
+  a.p1[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(hx, xx, a.p1[t], 0, 0, 0);
+  a.p2[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(hy, xy, a.p2[t], 0, 0, 0);
+  a.p3[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(hx + hy, xx - xy, a.p3[t], 0, 0, 0);
 }
 
 // Writes this lane's accumulated pairs into red[i * NR + l] (a wave's NPD x NR
@@ -99,6 +80,40 @@ __device__ __forceinline__ void mfma_acc_store(const MfmaAcc<(NCOL + 15) / 16>& 
   }
 }
 
+
+constexpr int kTurn = 17;   // row stride of the LDS tile that turns h
+
+// Pointer tables of the reverse step: cotangents of the targets (hp), cotangent
+// slots of the reads (gp), forward values of the reads (xp).
+template <int MD, bool ODD, typename R>
+__device__ __forceinline__ void pt_fill_vjp_pointers(const VjpPtrs<R>& V, uint64_t* hp, uint64_t* gp, uint64_t* xp) {
+  constexpr int NP = 2 * MD;
+  for (int t = threadIdx.x; t < pt_table_entries(MD); t += blockDim.x) {
+    const int K = t / kPtPos, p = t % kPtPos, j = p >> 1, b = p & 1;
+    int ft = -1, fr = -1;   // target (level S, F0: S + 1) and read (level S - 1, F0: S) families
+    if (p < NP) {
+      if (K == MD) {
+        if (ODD) {
+          ft = b ? fam_f1b(MD, j) : fam_f1k(j);
+          fr = b ? fam_f1k(j) : fam_f1b(MD, j);
+        }
+      } else if (p == 2 * K) {
+        ft = fam_f2(MD, K);
+        fr = 0;
+      } else if (p == 2 * K + 1) {
+        ft = 0;
+        fr = fam_f2(MD, K);
+      } else if (j > K) {
+        ft = b ? fam_1001(MD, K, j) : fam_1010(MD, K, j);
+        fr = b ? fam_1010(MD, K, j) : fam_1001(MD, K, j);
+      }
+    }
+    hp[t] = ft < 0 ? 0 : reinterpret_cast<uint64_t>(ft ? V.gcur[ft] : const_cast<cx<R>*>(V.gf0nxt));
+    gp[t] = fr < 1 ? 0 : reinterpret_cast<uint64_t>(V.gprev[fr]);
+    xp[t] = fr < 0 ? 0 : reinterpret_cast<uint64_t>(fr ? V.fprev[fr] : V.fcur[0]);
+    if (ODD && p == NP) xp[t] = reinterpret_cast<uint64_t>(V.fcur[K < MD ? fam_f1k(K) : 0]);   // the pivot's value
+  }
+}
 
 // One level of the reverse sweep of an Algorithm 2 plan (the block kernel
 // for the plan's detected-mode count and block coordinates).
