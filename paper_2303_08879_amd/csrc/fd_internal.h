@@ -190,11 +190,12 @@ struct Plan {
 size_t elem_bytes(fd_dtype dt);
 // True once the library is being unloaded: releases then skip device calls.
 bool unloading();
-// LDS of the undetected-block fill (vjp: its reverse), one wavefront: the
-// block (twice for the reverse: forward values and cotangents), A and b
+// LDS of the undetected-block fill of two or three undetected modes (vjp: its
+// reverse), one wavefront: the block (twice for the reverse: forward values and cotangents), A and b
 // between undetected positions, the square-root tables, the entry list by
 // weight and its offsets.
 inline size_t ufill_lds_bytes(const Plan& P, bool vjp) {
+  if (P.nq == 2) return 0;   // one undetected mode: rows in registers
   const size_t eb = elem_bytes(P.dt);
   return (vjp ? 2 : 1) * (size_t)P.B * eb + (size_t)(kMaxUq * kMaxUq + kMaxUq) * eb + 2 * (kMaxCut + 4) * (eb / 2) +
          (size_t)(P.B + P.wmax + 2) * sizeof(int);
@@ -210,6 +211,7 @@ inline size_t ufill_launch_lds_bytes(const Plan& P, bool vjp) {
 // LDS of the block fill with tangents (forward mode): values and tangents of
 // the block, of A and b between undetected positions, then the tables.
 inline size_t ufill_jvp_lds_bytes(const Plan& P) {
+  if (P.nq == 2) return 0;
   return ufill_lds_bytes(P, false) + (size_t)P.B * elem_bytes(P.dt) +
          (size_t)(kMaxUq * kMaxUq + kMaxUq) * elem_bytes(P.dt);
 }

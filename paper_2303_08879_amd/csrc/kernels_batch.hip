@@ -32,8 +32,7 @@ __global__ __launch_bounds__(kThreads) void k_batch_prep(const BatchCirc<R>* __r
   __syncthreads();
   if (threadIdx.x < 64) {
     if (C->P.nq == 2)
-      ufill_body<R, 2>(C->P, Ai, Ai + npos * npos, f0, load_global(&C->elist), load_global(&C->woff), C->wmax,
-                       reinterpret_cast<cx<R>*>(smem_raw));
+      ufill_rows_body<R, cx<R>>(C->P, Ai, Ai + npos * npos, f0);
     else
       ufill_body<R, 4>(C->P, Ai, Ai + npos * npos, f0, load_global(&C->elist), load_global(&C->woff), C->wmax,
                        reinterpret_cast<cx<R>*>(smem_raw));
@@ -201,7 +200,7 @@ fd_status build_sched(int n, Plan* const* plans, const bool* odd, const void* co
     const int pnb = (int)align16((size_t)(Pl.MD + 1) * (Pl.smax + 3) * sizeof(int));
     out_pn = std::max(out_pn, pnb);
     out_slv = std::max<int64_t>(out_slv, (int64_t)(Pl.smax + 2) * 8);
-    if (Pl.B > 1) ufill_lds = std::max(ufill_lds, ufill_lds_bytes(Pl, false));
+    if (Pl.nq > 2) ufill_lds = std::max(ufill_lds, ufill_lds_bytes(Pl, false));
     if (Pl.MD == 0) continue;
     double work = 0.0;
     for (int s = 0; s <= Pl.smax; ++s) work += (double)Pl.ncnt[s] * Pl.B * Pl.npos * Pl.npos;

@@ -23,8 +23,12 @@ __global__ __launch_bounds__(64) void k_ufill(DevPlan P, const cx<R>* __restrict
                                               const cx<R>* __restrict__ bi, cx<R>* G,
                                               const int* __restrict__ elist, const int* __restrict__ woff,
                                               int wmax, int64_t dT) {
-  extern __shared__ __align__(16) unsigned char smem_raw[];
-  ufill_body<R, NQ, E, ST>(P, Ai, bi, G, elist, woff, wmax, reinterpret_cast<E*>(smem_raw), dT);
+  if constexpr (NQ == 2) {
+    ufill_rows_body<R, E>(P, Ai, bi, G, dT);
+  } else {
+    extern __shared__ __align__(16) unsigned char smem_raw[];
+    ufill_body<R, NQ, E, ST>(P, Ai, bi, G, elist, woff, wmax, reinterpret_cast<E*>(smem_raw), dT);
+  }
 }
 
 // Algorithm 2: one workgroup of WV wavefronts per (lattice point, chunk of
@@ -123,12 +127,9 @@ static hipError_t launch_ufill(const Plan& Pl, const DevPlan& P, const cx<R>* Ai
                                hipStream_t st) {
   const size_t shm = ufill_launch_lds_bytes(Pl, false);
   if (shm > kMaxLds) return hipErrorInvalidConfiguration;
-  auto* kfn = Pl.st_ufill ? (Pl.nq == 2   ? &k_ufill<R, 2, cx<R>, true>
-                             : Pl.nq == 4 ? &k_ufill<R, 4, cx<R>, true>
-                                          : &k_ufill<R, 6, cx<R>, true>)
-                          : (Pl.nq == 2   ? &k_ufill<R, 2>
-                             : Pl.nq == 4 ? &k_ufill<R, 4>
-                                          : &k_ufill<R, 6>);
+  auto* kfn = Pl.nq == 2 ? &k_ufill<R, 2>
+              : Pl.st_ufill ? (Pl.nq == 4 ? &k_ufill<R, 4, cx<R>, true> : &k_ufill<R, 6, cx<R>, true>)
+                            : (Pl.nq == 4 ? &k_ufill<R, 4> : &k_ufill<R, 6>);
   if (shm > 65536)
     (void)hipFuncSetAttribute(reinterpret_cast<const void*>(kfn), hipFuncAttributeMaxDynamicSharedMemorySize,
                               (int)shm);

@@ -249,6 +249,83 @@ __global__ __launch_bounds__(64) void k_ufill_vjp(DevPlan P, const cx<R>* __rest
   if (lane == 0) st(cbar, gf[0]);
 }
 
+// The same for one undetected mode, row by row from the last (see
+// ufill_rows_body): lane l holds column l of the cotangents of three rows.
+template <typename R>
+__global__ __launch_bounds__(64) void k_ufill_vjp_rows(DevPlan P, const cx<R>* __restrict__ Ai,
+                                                       const cx<R>* __restrict__ bi, const cx<R>* __restrict__ G,
+                                                       const cx<R>* __restrict__ gin, double2* slot, cx<R>* cbar) {
+  const int C = P.udims[0], npos = P.npos, NR = npos + 1, lane = threadIdx.x;
+  const R* sqt = reinterpret_cast<const R*>(P.sqt);
+  const R sql = sqt[lane], isql = sqt[kMaxCut + 4 + lane], sqr = sqt[lane + 1];
+  const cx<R> b0 = ld(bi), b1 = ld(bi + 1), a00 = ld(Ai), a01 = ld(Ai + 1), a11 = ld(Ai + npos + 1);
+  const bool in = lane < C;
+  const int col = in ? lane : 0;
+  auto row = [&](const cx<R>* M, int k) { return csel(in && k >= 0, ld(M + (k >= 0 ? k : 0) * C + col), czero<R>()); };
+  // sums h conj(x): rows 0 (direction ket) with x = b term, A00, A01 reads and
+  // 1 (direction bra) with b term, A11 read
+  double sx[5] = {}, sy[5] = {};
+  auto add = [&](int i, const cx<R>& h, const cx<R>& x) {
+    const double hx = h.x, hy = h.y, px = x.x, py = x.y;
+    sx[i] += px * hx + py * hy;
+    sy[i] += px * hy - py * hx;
+  };
+  // cotangents of rows k, k - 1 (the latter without what row k adds), forward
+  // values of rows k - 1, k - 2; the row below next is loaded a step ahead
+  cx<R> gk = row(gin, C - 1), g1 = row(gin, C - 2), g2 = row(gin, C - 3);
+  cx<R> f1 = row(G, C - 2), f2 = row(G, C - 3), f3 = row(G, C - 4);
+  for (int k = C - 1; k >= 1; --k) {
+    const cx<R> gn = row(gin, k - 3), fn = row(G, k - 4);
+    const cx<R> h = cscale(gk, lane_value(isql, k));
+    const R wk = lane_value(sql, k - 1);
+    add(0, h, f1);
+    add(1, h, cscale(f2, wk));
+    const cx<R> fl = shfl_el(f1, lane > 0 ? lane - 1 : 0), hr = shfl_el(h, min(lane + 1, 63));
+    add(2, h, cscale(fl, sql));   // weight 0 in lane 0
+    cfma_conj(g1, b0, h);
+    if (lane + 1 < C) cfma_conj(g1, a01, cscale(hr, sqr));
+    cfma_conj(g2, a00, cscale(h, wk));
+    gk = g1;
+    g1 = g2;
+    g2 = gn;
+    f1 = f2;
+    f2 = f3;
+    f3 = fn;
+  }
+  // row 0: entry l from l - 1 and l - 2
+  const cx<R> f0 = row(G, 0);
+  cx<R> h0 = czero<R>();                       // lane l: its h
+  cx<R> cur = shfl_el(gk, C - 1), nxt = shfl_el(gk, C >= 2 ? C - 2 : 0);
+  for (int l = C - 1; l >= 1; --l) {
+    cx<R> nn = shfl_el(gk, l >= 2 ? l - 2 : 0);
+    const cx<R> h = cscale(cur, lane_value(isql, l));
+    h0 = csel(lane == l, h, h0);
+    cfma_conj(nxt, b1, h);
+    cfma_conj(nn, a11, cscale(h, lane_value(sql, l - 1)));   // weight 0 at l = 1
+    cur = nxt;
+    nxt = nn;
+  }
+  add(3, h0, shfl_el(f0, lane > 0 ? lane - 1 : 0));
+  const R wl = lane_value(sql, max(lane - 1, 0));   // 0 at l = 1
+  add(4, h0, cscale(shfl_el(f0, max(lane - 2, 0)), wl));
+  // butterfly sums over the wavefront (fixed order), lane 0 adds to the slot
+  const int at[5] = {npos, 0, 1, NR + npos, NR + 1};
+#pragma unroll
+  for (int i = 0; i < 5; ++i) {
+    double vx = sx[i], vy = sy[i];
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) {
+      vx += __shfl_xor(vx, off, 64);
+      vy += __shfl_xor(vy, off, 64);
+    }
+    if (lane == 0) {
+      const double2 v = slot[at[i]];
+      slot[at[i]] = make_double2(v.x + vx, v.y + vy);
+    }
+  }
+  if (lane == 0) st(cbar, cur);
+}
+
 // Final: sum the partial slots in order, symmetrise Abar, scatter to the
 // caller's block order (zero for dropped modes), write dc.
 struct FinalArgs {
@@ -501,17 +578,18 @@ static hipError_t run_vjp_t(const Plan& Pl, bool odd, const void* A, const void*
     // streamed: the block's cotangents accumulate in the workspace
     cx<R>* gbuf = Pl.st_ufill_vjp ? reinterpret_cast<cx<R>*>(ws + V.ublk) : nullptr;
     if (Pl.st_ufill_vjp && V.ublk == 0) return hipErrorInvalidValue;
-    auto* kfn = Pl.st_ufill_vjp ? (Pl.nq == 2   ? &k_ufill_vjp<R, 2, true>
-                                   : Pl.nq == 4 ? &k_ufill_vjp<R, 4, true>
-                                                : &k_ufill_vjp<R, 6, true>)
-                                : (Pl.nq == 2   ? &k_ufill_vjp<R, 2, false>
-                                   : Pl.nq == 4 ? &k_ufill_vjp<R, 4, false>
-                                                : &k_ufill_vjp<R, 6, false>);
-    if (shm > 65536)
-      (void)hipFuncSetAttribute(reinterpret_cast<const void*>(kfn), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                (int)shm);
-    hipLaunchKernelGGL(kfn, dim3(1), dim3(64), shm, st, P, Ai, bi, G0blk, gseed, Pl.d_elist, Pl.d_woff, Pl.wmax,
-                       partial + (size_t)(nslots - 1) * PP, cb, gbuf);
+    double2* slot = partial + (size_t)(nslots - 1) * PP;
+    if (Pl.nq == 2) {
+      hipLaunchKernelGGL((k_ufill_vjp_rows<R>), dim3(1), dim3(64), 0, st, P, Ai, bi, G0blk, gseed, slot, cb);
+    } else {
+      auto* kfn = Pl.st_ufill_vjp ? (Pl.nq == 4 ? &k_ufill_vjp<R, 4, true> : &k_ufill_vjp<R, 6, true>)
+                                  : (Pl.nq == 4 ? &k_ufill_vjp<R, 4, false> : &k_ufill_vjp<R, 6, false>);
+      if (shm > 65536)
+        (void)hipFuncSetAttribute(reinterpret_cast<const void*>(kfn), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                  (int)shm);
+      hipLaunchKernelGGL(kfn, dim3(1), dim3(64), shm, st, P, Ai, bi, G0blk, gseed, Pl.d_elist, Pl.d_woff, Pl.wmax,
+                         slot, cb, gbuf);
+    }
     if ((e = hipGetLastError()) != hipSuccess) return e;
     cbar_src = cb;
   }

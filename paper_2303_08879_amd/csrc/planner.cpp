@@ -429,10 +429,10 @@ ChunkGeo fwd_geo(const Plan& Pl, int64_t nwork) {
 
 // Row chunks of the reverse block kernel: own entries per unit on large
 // levels, on levels with fewer than `small_units` units, and that threshold: 512
-// (192 on small levels), so that a chunk's two halo rows are a small part of its
+// (128 on small levels), so that a chunk's two halo rows are a small part of its
 // time; 128 (64) where the taller rows do not fit the LDS.
 VjpChunking vjp_chunking(const Plan& Pl) {
-  if (!Pl.vjp_short) return {128 * kVjpWaves, 48 * kVjpWaves, 1024};
+  if (!Pl.vjp_short) return {128 * kVjpWaves, 32 * kVjpWaves, 1024};
   return {32 * kVjpWaves, 16 * kVjpWaves, kSmallLevelUnits};
 }
 
