@@ -9,10 +9,10 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libfockdiag.so")
-SOURCES = ["planner.cpp", "abi.cpp", "kernels_fwd.hip", "kernels_point.hip", "kernels_vjp.hip", "kernels_vjp_point.hip",
-           "kernels_vjp_block_c128_1.hip", "kernels_vjp_block_c128_5.hip",
-           "kernels_vjp_block_c64_1.hip", "kernels_vjp_block_c64_5.hip", "kernels_batch.hip", "kernels_state.hip",
-           "kernels_batch_level.hip", "scratch.hip"]
+SOURCES = ["planner.cpp", "abi.cpp", "scratch.hip", "kernels_fwd.hip", "kernels_point.hip", "kernels_point_small.hip",
+           "kernels_vjp.hip", "kernels_vjp_point.hip", "kernels_batch.hip", "kernels_batch_level.hip", "kernels_state.hip"]
+# block kernels: one translation unit per kind, precision and four detected-mode counts
+SOURCES += [f"kernels_{k}_block_{t}_{lo}.hip" for lo in (5, 1) for k in ("jvp", "fwd", "vjp") for t in ("c128", "c64")]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 # Packed FP32 instructions are disabled for every device pass.

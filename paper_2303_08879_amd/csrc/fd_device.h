@@ -162,6 +162,19 @@ template <typename R>
 hipError_t launch_fwd_point_level(const Plan& Pl, const DevPlan& P, bool odd, int S, const LevelPtrs<R>& L,
                                   const cx<R>* A, const cx<R>* b, int nwork, hipStream_t st, int64_t dT = 0);
 
+// Whole sweeps of small plans (Plan::point_small) in one workgroup
+// (kernels_point_small.hip); fam / gfam: node-0 pointers per family, [0] = F0.
+// The reverse runs levels hi..lo, hi = smax first and lo = 0 last; between
+// launches its sums stay in `state`.
+template <typename R>
+hipError_t launch_point_small_fwd(const Plan& Pl, const DevPlan& P, bool odd, const cx<R>* A, const cx<R>* b,
+                                  const cx<R>* c, cx<R>* Ai, void* const* fam, bool ring, cx<R>* rho, hipStream_t st);
+template <typename R>
+hipError_t launch_point_small_vjp(const Plan& Pl, const DevPlan& P, bool odd, const cx<R>* A, const cx<R>* b,
+                                  const cx<R>* c, cx<R>* Ai, void* const* fam, void* const* gfam, const cx<R>* drho,
+                                  cx<R>* g0, cx<R>* dA, cx<R>* db, cx<R>* dc, int hi, int lo, double* state,
+                                  hipStream_t st);
+
 // Node record of lattice point r of the level: m, the ranks of m - 1_j at
 // level S-1 and of m + 1_j at level S+1 (one scalar load per unit).
 template <int MD>

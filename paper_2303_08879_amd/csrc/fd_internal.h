@@ -60,6 +60,9 @@ constexpr int64_t kMaxDigitTable = 1 << 20;   // lattice points: 8 MB of digits,
 // wavefronts).  Eight modes: 71 thousand points 30 against 28 us, 143 thousand 41
 // against 48, a million 218 against 236.
 constexpr int kPointTileMin = 1 << 17;
+// Plans with every mode detected whose levels have at most this many (bridge,
+// 16-point tile) items run each sweep in one workgroup.
+constexpr int kSmallItems = 48;
 constexpr int kVjpSlots = 16384;         // reduction slots of the state-vector cotangents
 
 enum FamType { F_F0 = 0, F_F1K, F_F1B, F_F2, F_1010, F_1001 };
@@ -183,6 +186,7 @@ struct Plan {
   // blocks whose rows do not fit the LDS staging stream them from HBM, per
   // kernel: forward block units, block fill, reverse block units, reverse fill
   bool st_fwd = false, st_ufill = false, st_vjp = false, st_ufill_vjp = false;
+  bool point_small = false;          // sweeps in one workgroup (see kSmallItems)
   bool vjp_short = false;            // shorter row chunks of the block reverse kernel (LDS)
   bool odd_for(bool b_zero) const { return !b_zero || MU > 0; }
 };

@@ -32,11 +32,12 @@ __global__ __launch_bounds__(kThreads, 2) void k_batch_point(const BatchCirc<R>*
   const int64_t* lvl = load_global(&P.lvl);
   if (mt) mt += lvl[S];
   PtItems N;
+#pragma unroll
   for (int K = 0; K < MD; ++K) N.n[K] = (int)(lvl[K * (P.smax + 2) + S + 1] - lvl[K * (P.smax + 2) + S]);
   for (int u = I.u0 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6); u < I.u1; u += kThreads / 64) {
-    int K, base;
-    if (!pt_item(N, MD, u, &K, &base)) break;
-    fwd_point_item<MD, ODD, false, R>(P, Y, Q, L.f0cur, L.f0nxt != nullptr, mt, S, K, base, N.n[K], rows);
+    int K = 0, base = 0, n = 0;
+    if (!pt_item<MD>(N, u, &K, &base, &n)) break;
+    fwd_point_item<MD, ODD, false, R>(P, Y, Q, L.f0cur, L.f0nxt != nullptr, mt, S, K, base, n, rows);
   }
 }
 

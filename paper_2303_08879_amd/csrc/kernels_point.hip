@@ -24,10 +24,10 @@ __global__ __launch_bounds__(kThreads, 2) void k_fwd_point(DevPlan P, LevelPtrs<
   C.load(P, Ai, bi, dT);
   __syncthreads();
   const PtLds<R> Y{sq, sq + (kMaxCut + 4), spn, rd, wr};
-  int K, base;
-  if (!pt_item(I, MD, blockIdx.x * (kThreads / 64) + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), &K, &base))
+  int K = 0, base = 0, n = 0;
+  if (!pt_item<MD>(I, blockIdx.x * (kThreads / 64) + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), &K, &base, &n))
     return;
-  fwd_point_item<MD, ODD, DUAL, R>(P, Y, C, L.f0cur, L.f0nxt != nullptr, mt, S, K, base, I.n[K], rows, dT);
+  fwd_point_item<MD, ODD, DUAL, R>(P, Y, C, L.f0cur, L.f0nxt != nullptr, mt, S, K, base, n, rows, dT);
 }
 
 template <typename R>

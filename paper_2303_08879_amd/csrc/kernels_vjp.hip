@@ -436,12 +436,86 @@ static hipError_t run_vjp_t(const Plan& Pl, bool odd, const void* A, const void*
   cx<R>* bi = Ai + (size_t)Pl.npos * Pl.npos;
   cx<R>* cb = bi + Pl.npos;   // reused: holds cbar at the end
   double2* partial = reinterpret_cast<double2*>(ws + V.partial);
-  hipError_t e;
-  {
+  hipError_t e = hipSuccess;
+  const int MD = Pl.MD;
+  // Checkpointed plans: the forward values of one segment of levels at a
+  // time, recomputed from the segment's checkpoint into the segment buffer
+  // (slot k holds level seg_lo - 1 + k); F0 of every level is in `saved`.
+  const bool ck = Pl.ckpt > 0;
+  const CkptLayout Lc = ck ? ckpt_layout(Pl) : CkptLayout();
+  const SegLayout Sg = ck ? seg_layout(Pl) : SegLayout();
+  const size_t f0off = ck ? Lc.f0 : Ls.f0;
+  auto used = [&](int f) { return ckpt_keeps_family(Pl, f) && (odd || f >= 1 + 2 * MD); };
+  // level L of family f in the segment buffer (levels seg_lo - 1 .. held)
+  auto seg_slot = [&](int f, int lo, int L) {
+    return reinterpret_cast<cx<R>*>(ws + Sg.fam[f] +
+                                    (size_t)seg_node(Pl, Pl.fam_group[f], lo, L) * Pl.B * sizeof(cx<R>));
+  };
+  // forward values of levels lo..hi from the checkpoint below lo
+  auto restore = [&](int lo, int hi) -> hipError_t {
+    const int c = lo / Pl.ckpt;
+    if (c > 0) {
+      const void* src[kMaxFam] = {};
+      void* dst[kMaxFam] = {};
+      int64_t n[kMaxFam] = {};
+      for (int f = 1; f < Pl.nfam; ++f) {
+        if (!used(f)) continue;
+        src[f] = sv + Lc.ck[(size_t)(c - 1) * Pl.nfam + f];
+        dst[f] = seg_slot(f, lo, lo - 1);
+        n[f] = Pl.ncnt[(size_t)Pl.fam_group[f] * (Pl.smax + 1) + lo - 1] * Pl.B;
+      }
+      const hipError_t x = launch_copy_fams(Pl, src, dst, n, st);
+      if (x != hipSuccess) return x;
+    }
+    const cx<R>* f0all = reinterpret_cast<const cx<R>*>(sv + f0off);
+    for (int L = lo; L <= hi; ++L) {
+      const void* rd[kMaxFam] = {};
+      void* wr[kMaxFam] = {};
+      for (int f = 1; f < Pl.nfam; ++f) {
+        if (!used(f)) continue;
+        rd[f] = L > 0 ? seg_slot(f, lo, L - 1) : nullptr;
+        wr[f] = seg_slot(f, lo, L);
+      }
+      // F0 of level L + 1 is written again with the values it already holds
+      cx<R>* f0nxt = L < Pl.smax ? const_cast<cx<R>*>(f0all) + (size_t)Pl.lvl[L + 1] * Pl.B : nullptr;
+      KTimer kt(Pl, KK_FWD_LEVEL, st);
+      const hipError_t x = launch_fwd_level(Pl, odd, L, rd, wr, f0all + (size_t)Pl.lvl[L] * Pl.B, f0nxt, Ai, bi, st);
+      if (x != hipSuccess) return x;
+    }
+    return hipSuccess;
+  };
+  if (!Pl.point_small || ck) {
     KTimer kt(Pl, KK_PREP, st);
     e = launch_prep(Pl, A, b, c, Ai, nullptr, st);
   }
   if (e != hipSuccess) return e;
+  if (Pl.point_small) {
+    void *fam[kMaxFam] = {}, *gfam[kMaxFam] = {};
+    for (int f = 0; f < Pl.nfam; ++f) gfam[f] = V.gfam[f] ? ws + V.gfam[f] : nullptr;
+    fam[0] = const_cast<char*>(sv) + f0off;
+    const int every = ck ? Pl.ckpt : Pl.smax + 1;
+    for (int lo = Pl.smax / every * every; lo >= 0; lo -= every) {
+      const int hi = std::min(lo + every - 1, Pl.smax);
+      if (ck && (e = restore(lo, hi)) != hipSuccess) return e;
+      for (int f = 1; f < Pl.nfam; ++f) {
+        // a segment buffer starts with level lo - 1: its node 0 is that many
+        // nodes before it
+        const int64_t skip = ck ? Pl.lvl[(size_t)Pl.fam_group[f] * (Pl.smax + 2) + std::max(lo - 1, 0)] : 0;
+        const bool have = ck ? used(f) : Ls.fam[f] != 0;
+        fam[f] = !have ? nullptr
+                 : ck  ? reinterpret_cast<cx<R>*>(ws + Sg.fam[f]) - skip
+                       : reinterpret_cast<cx<R>*>(const_cast<char*>(sv) + Ls.fam[f]);
+      }
+      KTimer kt(Pl, KK_VJP_LEVEL, st);
+      if ((e = launch_point_small_vjp<R>(Pl, make_devplan(Pl, odd), odd, static_cast<const cx<R>*>(A),
+                                         static_cast<const cx<R>*>(b), static_cast<const cx<R>*>(c), Ai, fam, gfam,
+                                         static_cast<const cx<R>*>(drho), reinterpret_cast<cx<R>*>(ws + V.g0),
+                                         static_cast<cx<R>*>(dA), static_cast<cx<R>*>(db), static_cast<cx<R>*>(dc), hi,
+                                         lo, reinterpret_cast<double*>(partial), st)) != hipSuccess)
+        return e;
+    }
+    return hipSuccess;
+  }
   const int PP = Pl.npos * (Pl.npos + 1);
   // reduction slots in use: one per workgroup of the largest level, and the
   // undetected-block fill's (the last one)
@@ -475,7 +549,6 @@ static hipError_t run_vjp_t(const Plan& Pl, bool odd, const void* A, const void*
                        reinterpret_cast<const cx<R>*>(drho), g0, (int64_t)Pl.nodes_total, total);
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }
-  const int MD = Pl.MD;
   if (Pl.level_cap >= 0 && MD > 0) {
     // under a total photon cutoff the families of the last level feed no
     // target: their cotangents (read by that level's pivots) start at zero
@@ -488,52 +561,11 @@ static hipError_t run_vjp_t(const Plan& Pl, bool odd, const void* A, const void*
       if ((e = hipGetLastError()) != hipSuccess) return e;
     }
   }
-  // Checkpointed plans: the forward values of one segment of levels at a
-  // time, recomputed from the segment's checkpoint into the segment buffer
-  // (slot k holds level seg_lo - 1 + k); F0 of every level is in `saved`.
-  const bool ck = Pl.ckpt > 0;
-  const CkptLayout Lc = ck ? ckpt_layout(Pl) : CkptLayout();
-  const SegLayout Sg = ck ? seg_layout(Pl) : SegLayout();
-  const size_t f0off = ck ? Lc.f0 : Ls.f0;
-  auto used = [&](int f) { return ckpt_keeps_family(Pl, f) && (odd || f >= 1 + 2 * MD); };
-  // level L of family f in the segment buffer (levels seg_lo - 1 .. held)
-  auto seg_slot = [&](int f, int lo, int L) {
-    return reinterpret_cast<cx<R>*>(ws + Sg.fam[f] +
-                                    (size_t)seg_node(Pl, Pl.fam_group[f], lo, L) * Pl.B * sizeof(cx<R>));
-  };
   int seg_lo = Pl.smax + 1;
   for (int S = Pl.smax; S >= 0 && MD > 0; --S) {
     if (ck && S < seg_lo) {
       seg_lo = (S / Pl.ckpt) * Pl.ckpt;
-      const int c = S / Pl.ckpt;
-      if (c > 0) {
-        const void* src[kMaxFam] = {};
-        void* dst[kMaxFam] = {};
-        int64_t n[kMaxFam] = {};
-        for (int f = 1; f < Pl.nfam; ++f) {
-          if (!used(f)) continue;
-          src[f] = sv + Lc.ck[(size_t)(c - 1) * Pl.nfam + f];
-          dst[f] = seg_slot(f, seg_lo, seg_lo - 1);
-          n[f] = Pl.ncnt[(size_t)Pl.fam_group[f] * (Pl.smax + 1) + seg_lo - 1] * Pl.B;
-        }
-        if ((e = launch_copy_fams(Pl, src, dst, n, st)) != hipSuccess) return e;
-      }
-      const cx<R>* f0all = reinterpret_cast<const cx<R>*>(sv + f0off);
-      for (int L = seg_lo; L <= S; ++L) {
-        const void* rd[kMaxFam] = {};
-        void* wr[kMaxFam] = {};
-        for (int f = 1; f < Pl.nfam; ++f) {
-          if (!used(f)) continue;
-          rd[f] = L > 0 ? seg_slot(f, seg_lo, L - 1) : nullptr;
-          wr[f] = seg_slot(f, seg_lo, L);
-        }
-        // F0 of level L + 1 is written again with the values it already holds
-        cx<R>* f0nxt = L < Pl.smax ? const_cast<cx<R>*>(f0all) + (size_t)Pl.lvl[L + 1] * Pl.B : nullptr;
-        KTimer kt(Pl, KK_FWD_LEVEL, st);
-        if ((e = launch_fwd_level(Pl, odd, L, rd, wr, f0all + (size_t)Pl.lvl[L] * Pl.B, f0nxt, Ai, bi, st)) !=
-            hipSuccess)
-          return e;
-      }
+      if ((e = restore(seg_lo, S)) != hipSuccess) return e;
     }
     VjpPtrs<R> Vp;
     std::memset(&Vp, 0, sizeof(Vp));

@@ -201,17 +201,22 @@ struct PtItems {
   int n[kMaxD];
   __host__ __device__ __forceinline__ int tiles(int K) const { return (n[K] + 15) >> 4; }
 };
-__device__ __forceinline__ bool pt_item(const PtItems& I, int MD, int u, int* K, int* base) {
+// Item u: its bridge, first point and the bridge's number of points.
+template <int MD>
+__device__ __forceinline__ bool pt_item(const PtItems& I, int u, int* K, int* base, int* n) {
+  bool found = false;
+#pragma unroll
   for (int k = 0; k < MD; ++k) {
     const int t = I.tiles(k);
-    if (u < t) {
+    if (!found && u < t) {
+      found = true;
       *K = k;
       *base = 16 * u;
-      return true;
+      *n = I.n[k];
     }
     u -= t;
   }
-  return false;
+  return found;
 }
 
 // One item: 16 lattice points base.. of level S (the n points of bridge K), one

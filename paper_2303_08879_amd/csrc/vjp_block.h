@@ -59,7 +59,7 @@ __global__ __launch_bounds__(64 * kVjpWaves, 2) void k_vjp_block(DevPlan P, VjpP
     const R* t = reinterpret_cast<const R*>(P.sqt);
     for (int i = threadIdx.x; i < 2 * (kMaxCut + 4); i += blockDim.x) sq[i] = t[i];
   }
-  pt_fill_vjp_pointers<MD, true, R>(V, hp, gp, xp);
+  pt_fill_vjp_pointers<MD, true, R, false>(V, hp, gp, xp);
   // [A b]^H: row l = 16 t + row, column i = 4 s + kq
   R ar[NT][KS], ai[NT][KS];
 #pragma unroll

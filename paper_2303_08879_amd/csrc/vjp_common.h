@@ -84,9 +84,10 @@ __device__ __forceinline__ void mfma_acc_store(const MfmaAcc<(NCOL + 15) / 16>& 
 constexpr int kTurn = 17;   // row stride of the LDS tile that turns h
 
 // Pointer tables of the reverse step: cotangents of the targets (hp), cotangent
-// slots of the reads (gp), forward values of the reads (xp).
-template <int MD, bool ODD, typename R>
-__device__ __forceinline__ void pt_fill_vjp_pointers(const VjpPtrs<R>& V, uint64_t* hp, uint64_t* gp, uint64_t* xp) {
+// slots of the reads (gp), forward values of the reads (xp; with PIVOTS, then the
+// values of the pivots F1k(K)).
+template <int MD, bool ODD, typename R, bool PIVOTS = ODD, typename VP = VjpPtrs<R>>
+__device__ __forceinline__ void pt_fill_vjp_pointers(const VP& V, uint64_t* hp, uint64_t* gp, uint64_t* xp) {
   constexpr int NP = 2 * MD;
   for (int t = threadIdx.x; t < pt_table_entries(MD); t += blockDim.x) {
     const int K = t / kPtPos, p = t % kPtPos, j = p >> 1, b = p & 1;
@@ -113,6 +114,9 @@ __device__ __forceinline__ void pt_fill_vjp_pointers(const VjpPtrs<R>& V, uint64
     xp[t] = fr < 0 ? 0 : reinterpret_cast<uint64_t>(fr ? V.fprev[fr] : V.fcur[0]);
     if (ODD && p == NP) xp[t] = reinterpret_cast<uint64_t>(V.fcur[K < MD ? fam_f1k(K) : 0]);   // the pivot's value
   }
+  if (PIVOTS)
+    for (int K = threadIdx.x; K < MD; K += blockDim.x)
+      xp[pt_table_entries(MD) + K] = reinterpret_cast<uint64_t>(V.fcur[fam_f1k(K)]);
 }
 
 // One level of the reverse sweep of an Algorithm 2 plan (the block kernel
