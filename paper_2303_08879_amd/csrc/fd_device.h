@@ -162,7 +162,7 @@ template <typename R>
 hipError_t launch_fwd_point_level(const Plan& Pl, const DevPlan& P, bool odd, int S, const LevelPtrs<R>& L,
                                   const cx<R>* A, const cx<R>* b, int nwork, hipStream_t st, int64_t dT = 0);
 
-// Whole sweeps of small plans (Plan::point_small) in one workgroup
+// Whole sweeps of small plans (Plan::small_fwd, small_vjp) in one workgroup
 // (kernels_point_small.hip); fam / gfam: node-0 pointers per family, [0] = F0.
 // The reverse runs levels hi..lo, hi = smax first and lo = 0 last; between
 // launches its sums stay in `state`.

@@ -61,8 +61,12 @@ constexpr int64_t kMaxDigitTable = 1 << 20;   // lattice points: 8 MB of digits,
 // against 48, a million 218 against 236.
 constexpr int kPointTileMin = 1 << 17;
 // Plans with every mode detected whose levels have at most this many (bridge,
-// 16-point tile) items run each sweep in one workgroup.
-constexpr int kSmallItems = 48;
+// 16-point tile) items run the sweep in one workgroup: about as many as it runs
+// at once, past which it falls behind level launches replayed from a graph.
+// Forward + reverse, complex128, displaced, one workgroup against level launches
+// in a graph: two modes of cutoff 10 (1 tile) 148 against 200 us, three of cutoff
+// 9 (8 items) 261 against 324, four of cutoff 8 (27 items) 488 against 413.
+constexpr int kSmallFwdItems = 32, kSmallVjpItems = 16;
 constexpr int kVjpSlots = 16384;         // reduction slots of the state-vector cotangents
 
 enum FamType { F_F0 = 0, F_F1K, F_F1B, F_F2, F_1010, F_1001 };
@@ -186,7 +190,7 @@ struct Plan {
   // blocks whose rows do not fit the LDS staging stream them from HBM, per
   // kernel: forward block units, block fill, reverse block units, reverse fill
   bool st_fwd = false, st_ufill = false, st_vjp = false, st_ufill_vjp = false;
-  bool point_small = false;          // sweeps in one workgroup (see kSmallItems)
+  bool small_fwd = false, small_vjp = false;   // sweeps in one workgroup (see kSmallFwdItems)
   bool vjp_short = false;            // shorter row chunks of the block reverse kernel (LDS)
   bool odd_for(bool b_zero) const { return !b_zero || MU > 0; }
 };

@@ -355,7 +355,7 @@ static hipError_t run_forward_t(const Plan& Pl, bool odd, const void* A, const v
     stop->levels_done = Pl.smax + 1;
     stop->mass = 0.0;
   }
-  if (Pl.point_small && !stop) {
+  if (Pl.small_fwd && !stop) {
     void* fam[kMaxFam] = {};
     fam[0] = f0;
     for (int f = 1; f < Pl.nfam; ++f) fam[f] = LF.fam[f] ? fb + LF.fam[f] : nullptr;

@@ -8,7 +8,7 @@
 // share a CU, so its L1 and a workgroup barrier order one level's writes before
 // the next level's reads.  The tiles are those of the level kernels (pt_units.h,
 // vjp_point_units.h), so the amplitudes are theirs bit for bit.  Which plans:
-// kSmallItems in fd_internal.h.
+// kSmallFwdItems, kSmallVjpItems in fd_internal.h.
 #include <algorithm>
 #include <cstring>
 
@@ -16,6 +16,8 @@
 
 namespace fd {
 
+// sixteen wavefronts forward (128 registers each), eight in the reverse (256)
+constexpr int kSmallFwdThreads = 1024, kSmallFwdWaves = kSmallFwdThreads / 64;
 constexpr int kSmallThreads = 512, kSmallWaves = kSmallThreads / 64;
 
 // Family arrays of a sweep: node-0 pointers, and whether they are two-level
@@ -65,14 +67,14 @@ struct SmallFwd {
 };
 
 template <int MD, bool ODD, typename R>
-__global__ __launch_bounds__(kSmallThreads) void k_point_small_fwd(DevPlan P, SmallFwd<R> a) {
+__global__ __launch_bounds__(kSmallFwdThreads) void k_point_small_fwd(DevPlan P, SmallFwd<R> a) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
   constexpr int NT = pt_table_entries(MD);
   R* sq = reinterpret_cast<R*>(smem_raw);
   uint64_t* tab = reinterpret_cast<uint64_t*>(sq + 2 * (kMaxCut + 4));   // two levels x (read, write)
   int64_t* slv = reinterpret_cast<int64_t*>(tab + 4 * NT);
   int* rows = reinterpret_cast<int*>(slv + P.smax + 2);
-  int* spn = rows + kSmallWaves * pt_row_ints(MD, 1);
+  int* spn = rows + kSmallFwdWaves * pt_row_ints(MD, 1);
   unsigned char* grp = reinterpret_cast<unsigned char*>(spn + (MD + 1) * P.pnw);
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   rows += wave * pt_row_ints(MD, 1);
@@ -107,7 +109,7 @@ __global__ __launch_bounds__(kSmallThreads) void k_point_small_fwd(DevPlan P, Sm
     PtItems I;
 #pragma unroll
     for (int K = 0; K < MD; ++K) I.n[K] = (int)(P.lvl[K * (P.smax + 2) + S + 1] - P.lvl[K * (P.smax + 2) + S]);
-    for (int u = wave;; u += kSmallWaves) {
+    for (int u = wave;; u += kSmallFwdWaves) {
       int K = 0, base = 0, n = 0;
       if (!pt_item<MD>(I, u, &K, &base, &n)) break;
       fwd_point_item<MD, ODD, false, R>(P, Y, C, f0 + slv[S], S < P.smax, a.mt + slv[S], S, K, base, n, rows);
@@ -276,35 +278,36 @@ static void small_prep(const Plan& Pl, PrepArgs* pa) {
   pa->M2 = 2 * Pl.M;
   pa->check_b_zero = Pl.flags == FD_B_ZERO ? 1 : 0;
 }
-static size_t small_tail_lds(const Plan& Pl) {   // level offsets, rank rows, PN table, family groups
-  return (size_t)(Pl.smax + 2) * 8 + (size_t)kSmallWaves * pt_row_ints(Pl.MD, 1) * 4 +
+// level offsets, rank rows, PN table, family groups
+static size_t small_tail_lds(const Plan& Pl, int waves) {
+  return (size_t)(Pl.smax + 2) * 8 + (size_t)waves * pt_row_ints(Pl.MD, 1) * 4 +
          (size_t)(Pl.MD + 1) * (Pl.smax + 3) * 4 + kMaxFam;
 }
 
-#define FD_SMALL(KERN, ODDV)                                                                                       \
+#define FD_SMALL(KERN, THREADS)                                                                                       \
   {                                                                                                                \
     if (shm > 65536)                                                                                               \
       (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&KERN), hipFuncAttributeMaxDynamicSharedMemorySize,  \
                                 (int)shm);                                                                         \
-    hipLaunchKernelGGL(KERN, dim3(1), dim3(kSmallThreads), shm, st, P, a);                                         \
+    hipLaunchKernelGGL(KERN, dim3(1), dim3(THREADS), shm, st, P, a);                                               \
   }
-#define FD_SMALL_CASE(NAME, MDV)                     \
+#define FD_SMALL_CASE(NAME, THREADS, MDV)                     \
   case MDV:                                          \
     if (odd)                                         \
-      FD_SMALL((NAME<MDV, true, R>), true)           \
+      FD_SMALL((NAME<MDV, true, R>), THREADS)         \
     else                                             \
-      FD_SMALL((NAME<MDV, false, R>), false)         \
+      FD_SMALL((NAME<MDV, false, R>), THREADS)        \
     break;
-#define FD_SMALL_SWITCH(NAME)         \
+#define FD_SMALL_SWITCH(NAME, THREADS)         \
   switch (Pl.MD) {                    \
-    FD_SMALL_CASE(NAME, 1)            \
-    FD_SMALL_CASE(NAME, 2)            \
-    FD_SMALL_CASE(NAME, 3)            \
-    FD_SMALL_CASE(NAME, 4)            \
-    FD_SMALL_CASE(NAME, 5)            \
-    FD_SMALL_CASE(NAME, 6)            \
-    FD_SMALL_CASE(NAME, 7)            \
-    FD_SMALL_CASE(NAME, 8)            \
+    FD_SMALL_CASE(NAME, THREADS, 1)            \
+    FD_SMALL_CASE(NAME, THREADS, 2)            \
+    FD_SMALL_CASE(NAME, THREADS, 3)            \
+    FD_SMALL_CASE(NAME, THREADS, 4)            \
+    FD_SMALL_CASE(NAME, THREADS, 5)            \
+    FD_SMALL_CASE(NAME, THREADS, 6)            \
+    FD_SMALL_CASE(NAME, THREADS, 7)            \
+    FD_SMALL_CASE(NAME, THREADS, 8)            \
     default:                          \
       return hipErrorInvalidValue;    \
   }
@@ -325,8 +328,9 @@ hipError_t launch_point_small_fwd(const Plan& Pl, const DevPlan& P, bool odd, co
   small_prep(Pl, &a.pa);
   a.status = Pl.d_status;
   a.level_order = Pl.level_cap >= 0 ? 1 : 0;
-  const size_t shm = 2 * (kMaxCut + 4) * sizeof(R) + (size_t)4 * pt_table_entries(Pl.MD) * 8 + small_tail_lds(Pl);
-  FD_SMALL_SWITCH(k_point_small_fwd)
+  const size_t shm = 2 * (kMaxCut + 4) * sizeof(R) + (size_t)4 * pt_table_entries(Pl.MD) * 8 +
+                     small_tail_lds(Pl, kSmallFwdWaves);
+  FD_SMALL_SWITCH(k_point_small_fwd, kSmallFwdThreads)
   return hipGetLastError();
 }
 
@@ -361,9 +365,9 @@ hipError_t launch_point_small_vjp(const Plan& Pl, const DevPlan& P, bool odd, co
   a.lo = lo;
   a.state = state;
   const size_t shm = std::max(2 * (kMaxCut + 4) * sizeof(R) + (size_t)2 * pt_vjp_entries(Pl.MD) * 8 +
-                                  (size_t)kSmallWaves * kPtPos * kTurn * sizeof(cx<R>) + small_tail_lds(Pl),
+                                  (size_t)kSmallWaves * kPtPos * kTurn * sizeof(cx<R>) + small_tail_lds(Pl, kSmallWaves),
                               (size_t)kSmallWaves * 2 * Pl.MD * (2 * Pl.MD + 1) * sizeof(cx<double>));
-  FD_SMALL_SWITCH(k_point_small_vjp)
+  FD_SMALL_SWITCH(k_point_small_vjp, kSmallThreads)
   return hipGetLastError();
 }
 

@@ -484,12 +484,12 @@ static hipError_t run_vjp_t(const Plan& Pl, bool odd, const void* A, const void*
     }
     return hipSuccess;
   };
-  if (!Pl.point_small || ck) {
+  if (!Pl.small_vjp || ck) {
     KTimer kt(Pl, KK_PREP, st);
     e = launch_prep(Pl, A, b, c, Ai, nullptr, st);
   }
   if (e != hipSuccess) return e;
-  if (Pl.point_small) {
+  if (Pl.small_vjp) {
     void *fam[kMaxFam] = {}, *gfam[kMaxFam] = {};
     for (int f = 0; f < Pl.nfam; ++f) gfam[f] = V.gfam[f] ? ws + V.gfam[f] : nullptr;
     fam[0] = const_cast<char*>(sv) + f0off;

@@ -313,12 +313,15 @@ fd_status build_plan(int M, const int* cutoffs, uint32_t mask, fd_dtype dt, uint
     P->st_vjp = P->MD > 0 && vjp_lds_bytes(*P) > kMaxLds;
     P->st_ufill_vjp = ufill_lds_bytes(*P, true) > kMaxLds;
   }
-  P->point_small = P->B == 1 && P->MD > 0 && P->nodes_total <= kMaxDigitTable;
-  for (int S = 0; S <= P->smax && P->point_small; ++S) {
+  int64_t most = 0;   // items of the largest level
+  for (int S = 0; S <= P->smax; ++S) {
     int64_t items = 0;
     for (int K = 0; K < P->MD; ++K) items += (P->ncnt[(size_t)K * (P->smax + 1) + S] + 15) / 16;
-    P->point_small = items <= kSmallItems;
+    most = std::max(most, items);
   }
+  const bool points = P->B == 1 && P->MD > 0 && P->nodes_total <= kMaxDigitTable;
+  P->small_fwd = points && most <= kSmallFwdItems;
+  P->small_vjp = points && most <= kSmallVjpItems;
   P->targets = -1;
   P->terms = -1;
   return FD_OK;
