@@ -60,6 +60,7 @@ constexpr int64_t kMaxDigitTable = 1 << 20;   // lattice points: 8 MB of digits,
 // wavefronts).  Eight modes: 71 thousand points 30 against 28 us, 143 thousand 41
 // against 48, a million 218 against 236.
 constexpr int kPointTileMin = 1 << 17;
+constexpr int kWideTiles = 2048;         // tiles of a level up to which its first ones get a workgroup each
 // Plans with every mode detected whose levels have at most this many (bridge,
 // 16-point tile) items run the sweep in one workgroup: about as many as it runs
 // at once, past which it falls behind level launches replayed from a graph.

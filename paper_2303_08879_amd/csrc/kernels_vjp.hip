@@ -521,7 +521,7 @@ static hipError_t run_vjp_t(const Plan& Pl, bool odd, const void* A, const void*
   // undetected-block fill's (the last one)
   int nslots = Pl.B > 1 ? 1 : 0;
   for (int S = 0; S <= Pl.smax && Pl.MD > 0; ++S)
-    nslots = std::max(nslots, (Pl.B > 1 ? 1 + vjp_block_grid(Pl, (int)Pl.ncnt[S]) : vjp_point_grid((int)Pl.ncnt[S])));
+    nslots = std::max(nslots, (Pl.B > 1 ? 1 + vjp_block_grid(Pl, (int)Pl.ncnt[S]) : vjp_point_grid(Pl, S)));
   const int64_t npart = (int64_t)nslots * PP;
   {
     KTimer kt(Pl, KK_ZERO, st);

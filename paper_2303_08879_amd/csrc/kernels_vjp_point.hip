@@ -11,7 +11,8 @@ namespace fd {
 template <int MD, bool ODD, int T, typename R>
 __global__ __launch_bounds__(kThreads, 2) void k_vjp_point(DevPlan P, VjpPtrs<R> V, const uint64_t* __restrict__ mt,
                                                         const cx<R>* __restrict__ Ai, const cx<R>* __restrict__ bi,
-                                                        int S, int nwork, double2* __restrict__ partial) {
+                                                        int S, int nwork, int nwide, int wide_off,
+                                                        double2* __restrict__ partial) {
   constexpr int NP = 2 * MD, NR = NP + 1, NPAIR = NP * NR, SL = 16 * T;
   extern __shared__ __align__(16) unsigned char smem_raw[];
   R* sq = reinterpret_cast<R*>(smem_raw);
@@ -32,9 +33,15 @@ __global__ __launch_bounds__(kThreads, 2) void k_vjp_point(DevPlan P, VjpPtrs<R>
   const VjpPtLevel<R> L{hp, gp, xp, sq, sq + (kMaxCut + 4), spn, V.fcur[0], V.d0cur, V.gcur[0], V.gf0nxt != nullptr};
   VjpPtSums<MD, R> Z;
   Z.zero();
-  const int stride = gridDim.x * (kThreads / 64) * SL;
-  for (int base = (blockIdx.x * (kThreads / 64) + wave) * SL; base < nwork; base += stride)
-    vjp_point_tile<MD, ODD, T, R>(P, L, C, Z, mt, S, base, nwork, turn, rows);
+  if (T == 1 && (int)blockIdx.x < nwide) {
+    // the first tiles, which take several bridges: one workgroup each
+    cx<R>* shared = reinterpret_cast<cx<R>*>(reinterpret_cast<unsigned char*>(smem_raw) + wide_off);
+    vjp_point_tile<MD, ODD, 1, R, true>(P, L, C, Z, mt, S, 16 * (int)blockIdx.x, nwork, turn, rows, shared, wave);
+  } else {
+    const int stride = (gridDim.x - nwide) * (kThreads / 64) * SL;
+    for (int base = 16 * nwide + ((blockIdx.x - nwide) * (kThreads / 64) + wave) * SL; base < nwork; base += stride)
+      vjp_point_tile<MD, ODD, T, R>(P, L, C, Z, mt, S, base, nwork, turn, rows);
+  }
   // fold the wavefronts' pair tables (fixed order) into this workgroup's slot
   cx<double>* red = reinterpret_cast<cx<double>*>(smem_raw);
   __syncthreads();
@@ -53,27 +60,38 @@ __global__ __launch_bounds__(kThreads, 2) void k_vjp_point(DevPlan P, VjpPtrs<R>
   }
 }
 
-int vjp_point_grid(int nwork) {
+// Tiles of a level that get a workgroup of their own (those whose points take
+// more than one bridge), while the level leaves the device idle wavefronts.
+static int wide_tiles(const Plan& Pl, int S) {
+  if (Pl.MD < 2 || Pl.ncnt[S] > 16 * kWideTiles) return 0;
+  return (int)((Pl.ncnt[(size_t)(Pl.smax + 1) + S] + 15) / 16);
+}
+int vjp_point_grid(const Plan& Pl, int S) {
+  const int nwork = (int)Pl.ncnt[S], wide = wide_tiles(Pl, S);
   const int per = kThreads / 64 * 16 * (nwork >= kPointTileMin ? 4 : 1);
-  return std::min((nwork + per - 1) / per, kPartialSlots - 1);
+  return std::min(wide + (std::max(nwork - 16 * wide, 0) + per - 1) / per, kPartialSlots - 1);
 }
 
 template <int T, typename R>
 static hipError_t launch_t(const Plan& Pl, const DevPlan& P, bool odd, int S, const VjpPtrs<R>& V, const cx<R>* A,
                            const cx<R>* b, int nwork, double2* partial, hipStream_t st) {
+  // (the rows shared by a workgroup's tile after everything else)
+  const size_t wide_off = (pt_lds_bytes(Pl, T, kThreads / 64, 3) + kPtPos * 8 +
+                           (size_t)(kThreads / 64) * kPtPos * kTurn * sizeof(cx<R>) + 15) / 16 * 16;
+  const int nwide = T == 1 ? wide_tiles(Pl, S) : 0;
   const size_t shm =
-      std::max(pt_lds_bytes(Pl, T, kThreads / 64, 3) + kPtPos * 8 + (size_t)(kThreads / 64) * kPtPos * kTurn * sizeof(cx<R>),
+      std::max(wide_off + (nwide ? (size_t)wide_entries(Pl.MD) * sizeof(cx<R>) : 0),
                (size_t)(kThreads / 64) * 2 * Pl.MD * (2 * Pl.MD + 1) * sizeof(cx<double>));
   const uint64_t* mt = Pl.d_mtab ? Pl.d_mtab + Pl.lvl[S] : nullptr;
-  const int grid = vjp_point_grid(nwork);
+  const int grid = vjp_point_grid(Pl, S);
 #define FD_VJP_POINT(MDV)                                                                                          \
   case MDV:                                                                                                        \
     if (odd)                                                                                                       \
       hipLaunchKernelGGL((k_vjp_point<MDV, true, T, R>), dim3(grid), dim3(kThreads), shm, st, P, V, mt, A, b, S,   \
-                         nwork, partial);                                                                          \
+                         nwork, nwide, (int)wide_off, partial);                                                                        \
     else                                                                                                           \
       hipLaunchKernelGGL((k_vjp_point<MDV, false, T, R>), dim3(grid), dim3(kThreads), shm, st, P, V, mt, A, b, S,  \
-                         nwork, partial);                                                                          \
+                         nwork, nwide, (int)wide_off, partial);                                                                        \
     break;
   switch (Pl.MD) {
     FD_VJP_POINT(1)

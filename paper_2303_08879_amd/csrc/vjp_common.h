@@ -132,6 +132,6 @@ int vjp_block_grid(const Plan& Pl, int nwork);
 template <typename R>
 hipError_t launch_vjp_point_level(const Plan& Pl, const DevPlan& P, bool odd, int S, const VjpPtrs<R>& V,
                                   const cx<R>* A, const cx<R>* b, int nwork, double2* partial, hipStream_t st);
-int vjp_point_grid(int nwork);
+int vjp_point_grid(const Plan& Pl, int S);
 
 }  // namespace fd

@@ -101,11 +101,19 @@ struct VjpPtSums {
   }
 };
 
-// One tile of 16 T points base.. of a level of n points, one wavefront.
-template <int MD, bool ODD, int T, typename R>
+// One tile of 16 T points base.. of a level of n points, one wavefront; or (WIDE,
+// T = 1) the wavefronts of a workgroup on one tile, bridge K on wavefront K mod
+// kWideWaves, which leave the bridges' F0 cotangents and pivot cotangents in LDS
+// (`shared`) for the first to finish: the tiles at the start of a level take up to
+// 2 MD pivots, 2 us each in one wavefront.
+constexpr int kWideWaves = kThreads / 64;
+constexpr int wide_entries(int MD) { return (kWideWaves + MD) * 16; }
+template <int MD, bool ODD, int T, typename R, bool WIDE = false>
 __device__ __forceinline__ void vjp_point_tile(const DevPlan& P, const VjpPtLevel<R>& L,
                                                const VjpPtConst<MD, ODD, R>& C, VjpPtSums<MD, R>& Z,
-                                               const uint64_t* mt, int S, int base, int n, cx<R>* turn, int* rows) {
+                                               const uint64_t* mt, int S, int base, int n, cx<R>* turn, int* rows,
+                                               cx<R>* shared = nullptr, int wave = 0) {
+  static_assert(!WIDE || T == 1, "a workgroup takes one 16-point tile");
   constexpr int NP = 2 * MD, KS = PtMat<MD, R>::KS, SL = 16 * T;
   constexpr bool kCol = VjpPtConst<MD, ODD, R>::kCol;
   constexpr int NCOL = VjpPtConst<MD, ODD, R>::NCOL;
@@ -148,7 +156,9 @@ __device__ __forceinline__ void vjp_point_tile(const DevPlan& P, const VjpPtLeve
         const int m = (int)((pt_digits<MD, T>(rows, q) >> (8 * jr)) & 255);
         const bool ok = ((vm >> (4 * s + kq)) & 1) && pr < NCOL &&
                         (first || ((pr > 2 * K || K == MD) && m > 0));
-        const cx<R> v = ld(ok ? global_at<const cx<R>>(b) + (first ? r0 + 4 * s + kq : rows[jr * SL + q]) : L.f0);
+        const int dn = rows[jr * SL + q];
+        const cx<R>* a = global_at<const cx<R>>(b) + (first ? r0 + 4 * s + kq : dn);
+        const cx<R> v = ld(ok ? a : L.f0);
         x[s] = cscale(csel(ok, v, czero<R>()), piv ? R(1) : L.sq[m + (first ? 1 : 0)]);
       }
     };
@@ -184,7 +194,7 @@ __device__ __forceinline__ void vjp_point_tile(const DevPlan& P, const VjpPtLeve
     };
 
 #pragma unroll 1
-    for (int K = 0; K < MD; ++K) {
+    for (int K = WIDE ? wave : 0; K < MD; K += WIDE ? kWideWaves : 1) {
       if (__ballot(live && K <= K0) == 0ull) break;
       const int mK = (int)((pk >> (8 * K)) & 255);
       const bool valid = live && K <= K0 && mK <= P.CD[K] - 2;
@@ -198,7 +208,8 @@ __device__ __forceinline__ void vjp_point_tile(const DevPlan& P, const VjpPtLeve
         const int two = p == 2 * K ? 1 : 0;
         const bool nxt = p == 2 * K + 1;
         const bool ok = valid && p < NP && p >= 2 * K && digit(s) + two <= C.cj[s] - 2 && (!nxt || L.has_next);
-        const cx<R> v = ld(ok ? global_at<const cx<R>>(L.hp[K * kPtPos + p]) + (nxt ? up : r) : L.f0);
+        const cx<R>* a = global_at<const cx<R>>(L.hp[K * kPtPos + p]) + (nxt ? up : r);
+        const cx<R> v = ld(ok ? a : L.f0);
         h[s] = cscale(csel(ok, v, czero<R>()), L.isq[digit(s) + 1 + two]);
       }
       load_x(K, (uint32_t)vb & 0xffffu, x);
@@ -206,7 +217,8 @@ __device__ __forceinline__ void vjp_point_tile(const DevPlan& P, const VjpPtLeve
       if (ODD) {
         const bool has_diag_reader = (K > 0) || (mK + 1 <= P.CD[0] - 2);
         const bool lv = valid && has_diag_reader;
-        const cx<R> g = ld(lv ? global_at<const cx<R>>(L.hp[MD * kPtPos + 2 * K]) + r : L.f0);
+        const cx<R>* a = global_at<const cx<R>>(L.hp[MD * kPtPos + 2 * K]) + r;
+        const cx<R> g = ld(lv ? a : L.f0);
         gc = csel(lv, g, czero<R>());
         if (!kCol) {
           const cx<R> v = ld(valid ? global_at<const cx<R>>(L.xp[pt_table_entries(MD) + K]) + r : L.f0);
@@ -232,9 +244,25 @@ __device__ __forceinline__ void vjp_point_tile(const DevPlan& P, const VjpPtLeve
         const cx<R> g = cadd(gc, dot_b(h, pv, re, im));
 #pragma unroll
         for (int s = 0; s < KS; ++s)
-          if (4 * s + kq == 2 * K) yk[s] = g;
+          if (4 * s + kq == 2 * K) {
+            yk[s] = g;
+            if (WIDE) shared[(kWideWaves + K) * 16 + c] = g;
+          }
       }
       reduce(h, x);
+    }
+
+    // F0 cotangent: positions 2 K sit in lanes kq = 0 and kq = 2
+    g0 = cadd(g0, cmake<R>(__shfl_xor(g0.x, 32), __shfl_xor(g0.y, 32)));
+    if (WIDE) {
+      if (kq == 0) shared[wave * 16 + c] = g0;
+      __syncthreads();
+      if (wave != 0) return;
+#pragma unroll
+      for (int w = 1; w < kWideWaves; ++w) g0 = cadd(g0, shared[w * 16 + c]);
+#pragma unroll
+      for (int s = 0; s < KS; ++s)
+        if (ODD && side == 0 && 2 * s + hk < MD) yk[s] = shared[(kWideWaves + 2 * s + hk) * 16 + c];
     }
 
     if (ODD) {
@@ -249,7 +277,8 @@ __device__ __forceinline__ void vjp_point_tile(const DevPlan& P, const VjpPtLeve
           const int room = (j == 0 ? P.CD[0] - 2 - side : C.cj[s] - 2) - digit(s);
           const bool ok = valid && p < NP && room >= 0;
           const bool bridge = side == 0 && j <= K0 && digit(s) <= C.cj[s] - 2;   // its cotangent is at hand
-          const cx<R> v = ld(ok && !bridge ? global_at<const cx<R>>(L.hp[MD * kPtPos + p]) + r : L.f0);
+          const cx<R>* a = global_at<const cx<R>>(L.hp[MD * kPtPos + p]) + r;
+          const cx<R> v = ld(ok && !bridge ? a : L.f0);
           h[s] = cscale(csel(ok, csel(bridge, yk[s], v), czero<R>()), L.isq[digit(s) + 1]);
         }
         load_x(MD, (uint32_t)vb & 0xffffu, x);
@@ -272,9 +301,7 @@ __device__ __forceinline__ void vjp_point_tile(const DevPlan& P, const VjpPtLeve
         reduce(h, x);
       }
     }
-    // F0 cotangent: positions 2 K sit in lanes kq = 0 and kq = 2
-    const cx<R> o = cmake<R>(__shfl_xor(g0.x, 32), __shfl_xor(g0.y, 32));
-    if (kq == 0 && live) st(L.g0 + r, cadd(cadd(d0, gdiag), cadd(g0, o)));
+    if (kq == 0 && live) st(L.g0 + r, cadd(cadd(d0, gdiag), g0));
   }
   wave_sync();   // the rows are rewritten by the next tile
 }
