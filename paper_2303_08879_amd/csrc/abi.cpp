@@ -28,9 +28,17 @@ fd_status ok() {
 }
 
 // Decide the b = 0 schedule (Sec. 2.4) for this call; b has nb entries
-// (2M for a density matrix, M for a state vector).
-fd_status decide_b_zero(const fd::Plan& P, const void* b, hipStream_t s, bool* b_zero, int nb = -1) {
+// (2M for a density matrix, M for a state vector).  b is read only where the
+// answer matters: plans with undetected modes sweep every level anyway, and
+// `on_device` says that the sweep's kernel decides for itself (it takes false
+// as "not known to be zero").
+fd_status decide_b_zero(const fd::Plan& P, const void* b, hipStream_t s, bool* b_zero, int nb = -1,
+                        bool on_device = false) {
   if (nb < 0) nb = 2 * P.M;
+  if (P.flags == FD_B_AUTO && (on_device || P.MU > 0)) {
+    *b_zero = false;
+    return FD_OK;
+  }
   if (P.flags == FD_B_ZERO) {
     *b_zero = true;
     return FD_OK;
@@ -265,7 +273,9 @@ fd_status fock_diag_fwd(fd_plan p, const void* A, const void* b, const void* c, 
   if (saved && !aligned(saved, 256)) return fail(FD_ERR_INVALID_ARG, "saved must be 256-byte aligned");
   if (!aligned(workspace, 256)) return fail(FD_ERR_INVALID_ARG, "workspace must be 256-byte aligned");
   bool b_zero = false;
-  if ((s = decide_b_zero(P, b, stream, &b_zero)) != FD_OK) return s;
+  // (a workspace that only holds the b = 0 sweep keeps the host's decision)
+  const bool on_device = P.small_fwd && (saved ? P.ckpt == 0 : ws_bytes >= fd::fwd_layout(P, true, false, 0).total);
+  if ((s = decide_b_zero(P, b, stream, &b_zero, -1, on_device)) != FD_OK) return s;
   const bool odd = P.odd_for(b_zero);
   if (saved) {
     if (saved_bytes < fd::saved_bytes(P)) return fail(FD_ERR_WORKSPACE, "saved buffer too small");
@@ -395,7 +405,10 @@ fd_status fock_diag_vjp(fd_plan p, const void* A, const void* b, const void* c, 
   if (P.B > 1 && (fd::vjp_lds_bytes(P) > fd::kMaxLds || fd::ufill_launch_lds_bytes(P, true) > fd::kMaxLds))
     return fail(FD_ERR_UNSUPPORTED, "undetected block too large for the reverse sweep's LDS staging");
   bool b_zero = false;
-  if ((s = decide_b_zero(P, b, stream, &b_zero)) != FD_OK) return s;
+  const size_t vall = fd::vjp_layout(P, true, 0).total;
+  const bool on_device = P.small_vjp && P.ckpt == 0 &&
+                         ws_bytes >= vall + (saved ? 0 : 255 + fd::saved_bytes(P));
+  if ((s = decide_b_zero(P, b, stream, &b_zero, -1, on_device)) != FD_OK) return s;
   const bool odd = P.odd_for(b_zero);
   const size_t vneed = P.ckpt > 0 ? fd::vjp_ws_bytes(P) : fd::vjp_layout(P, odd, 0).total;
   const size_t sneed = fd::saved_bytes(P);

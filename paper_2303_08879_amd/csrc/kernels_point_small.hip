@@ -66,9 +66,21 @@ struct SmallFwd {
   int level_order;    // output in level order (a total photon cutoff)
 };
 
+// Which levels a sweep takes: the even ones (b = 0), all, or as b says -- read
+// on the device, so that a call need not wait for its stream and read b first.
+enum SmallMode { kSmallEven = 0, kSmallAll = 1, kSmallByB = 2 };
+template <typename R>
+__device__ __forceinline__ bool b_is_zero(const cx<R>* b, int n) {
+  int nz = 0;
+  for (int i = threadIdx.x; i < n; i += blockDim.x) {
+    const cx<R> v = ld(b + i);
+    nz |= !(v.x == R(0) && v.y == R(0));   // (a NaN is not zero)
+  }
+  return __syncthreads_or(nz) == 0;
+}
+
 template <int MD, bool ODD, typename R>
-__global__ __launch_bounds__(kSmallFwdThreads) void k_point_small_fwd(DevPlan P, SmallFwd<R> a) {
-  extern __shared__ __align__(16) unsigned char smem_raw[];
+__device__ __forceinline__ void point_small_fwd(const DevPlan& P, const SmallFwd<R>& a, unsigned char* smem_raw) {
   constexpr int NT = pt_table_entries(MD);
   R* sq = reinterpret_cast<R*>(smem_raw);
   uint64_t* tab = reinterpret_cast<uint64_t*>(sq + 2 * (kMaxCut + 4));   // two levels x (read, write)
@@ -127,6 +139,15 @@ __global__ __launch_bounds__(kSmallFwdThreads) void k_point_small_fwd(DevPlan P,
   if (bad) atomicOr(a.status, 1);
 }
 
+template <int MD, int MODE, typename R>
+__global__ __launch_bounds__(kSmallFwdThreads) void k_point_small_fwd(DevPlan P, SmallFwd<R> a) {
+  extern __shared__ __align__(16) unsigned char smem_raw[];
+  if (MODE == kSmallEven || (MODE == kSmallByB && b_is_zero(a.b, a.pa.M2)))
+    point_small_fwd<MD, false, R>(P, a, smem_raw);
+  else
+    point_small_fwd<MD, true, R>(P, a, smem_raw);
+}
+
 template <typename R>
 struct SmallVjp {
   SmallFams<R> fam;    // forward values, every level (f[0] = F0)
@@ -145,8 +166,7 @@ struct SmallVjp {
 };
 
 template <int MD, bool ODD, typename R>
-__global__ __launch_bounds__(kSmallThreads) void k_point_small_vjp(DevPlan P, SmallVjp<R> a) {
-  extern __shared__ __align__(16) unsigned char smem_raw[];
+__device__ __forceinline__ void point_small_vjp(const DevPlan& P, const SmallVjp<R>& a, unsigned char* smem_raw) {
   constexpr int NE = pt_vjp_entries(MD), NT = pt_table_entries(MD), NP = 2 * MD, NR = NP + 1, NPAIR = NP * NR;
   R* sq = reinterpret_cast<R*>(smem_raw);
   uint64_t* tab = reinterpret_cast<uint64_t*>(sq + 2 * (kMaxCut + 4));   // two levels
@@ -268,6 +288,15 @@ __global__ __launch_bounds__(kSmallThreads) void k_point_small_vjp(DevPlan P, Sm
   if (threadIdx.x == 0) st(a.dc, ld(a.gfam.f[0]));
 }
 
+template <int MD, int MODE, typename R>
+__global__ __launch_bounds__(kSmallThreads) void k_point_small_vjp(DevPlan P, SmallVjp<R> a) {
+  extern __shared__ __align__(16) unsigned char smem_raw[];
+  if (MODE == kSmallEven || (MODE == kSmallByB && b_is_zero(a.b, a.pa.M2)))
+    point_small_vjp<MD, false, R>(P, a, smem_raw);
+  else
+    point_small_vjp<MD, true, R>(P, a, smem_raw);
+}
+
 // ---------------------------------------------------------------------------
 // host launchers
 // ---------------------------------------------------------------------------
@@ -292,11 +321,13 @@ static size_t small_tail_lds(const Plan& Pl, int waves) {
     hipLaunchKernelGGL(KERN, dim3(1), dim3(THREADS), shm, st, P, a);                                               \
   }
 #define FD_SMALL_CASE(NAME, THREADS, MDV)                     \
-  case MDV:                                          \
-    if (odd)                                         \
-      FD_SMALL((NAME<MDV, true, R>), THREADS)         \
-    else                                             \
-      FD_SMALL((NAME<MDV, false, R>), THREADS)        \
+  case MDV:                                                   \
+    if (by_b)                                                 \
+      FD_SMALL((NAME<MDV, kSmallByB, R>), THREADS)            \
+    else if (odd)                                             \
+      FD_SMALL((NAME<MDV, kSmallAll, R>), THREADS)            \
+    else                                                      \
+      FD_SMALL((NAME<MDV, kSmallEven, R>), THREADS)           \
     break;
 #define FD_SMALL_SWITCH(NAME, THREADS)         \
   switch (Pl.MD) {                    \
@@ -330,6 +361,7 @@ hipError_t launch_point_small_fwd(const Plan& Pl, const DevPlan& P, bool odd, co
   a.level_order = Pl.level_cap >= 0 ? 1 : 0;
   const size_t shm = 2 * (kMaxCut + 4) * sizeof(R) + (size_t)4 * pt_table_entries(Pl.MD) * 8 +
                      small_tail_lds(Pl, kSmallFwdWaves);
+  const bool by_b = odd && Pl.flags == FD_B_AUTO;   // (odd: not known to be zero)
   FD_SMALL_SWITCH(k_point_small_fwd, kSmallFwdThreads)
   return hipGetLastError();
 }
@@ -367,6 +399,7 @@ hipError_t launch_point_small_vjp(const Plan& Pl, const DevPlan& P, bool odd, co
   const size_t shm = std::max(2 * (kMaxCut + 4) * sizeof(R) + (size_t)2 * pt_vjp_entries(Pl.MD) * 8 +
                                   (size_t)kSmallWaves * kPtPos * kTurn * sizeof(cx<R>) + small_tail_lds(Pl, kSmallWaves),
                               (size_t)kSmallWaves * 2 * Pl.MD * (2 * Pl.MD + 1) * sizeof(cx<double>));
+  const bool by_b = odd && Pl.flags == FD_B_AUTO && hi == Pl.smax && lo == 0;
   FD_SMALL_SWITCH(k_point_small_vjp, kSmallThreads)
   return hipGetLastError();
 }
