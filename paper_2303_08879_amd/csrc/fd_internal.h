@@ -54,7 +54,7 @@ constexpr int kFwdWaves = 4;             // wavefronts per workgroup of the bloc
 constexpr int kFwdChunk = 448;           // own entries of one of its (lattice point, row chunk) units,
 constexpr int kFwdChunkSmall = 192;      // on levels with fewer than kSmallLevelUnits units
 constexpr int kNodeStride = 3 * kMaxD;   // ints per node record: m, rank(m - 1_j), rank(m + 1_j)
-constexpr int64_t kMaxDigitTable = 1 << 20;   // lattice points: 8 MB of digits, a few ms of host work
+constexpr int64_t kMaxDigitTable = 1 << 25;   // lattice points with a digit table (8 bytes each)
 // Points of a level from which the reverse point kernel ranks 64 points per
 // wavefront (a quarter of the rank work) instead of 16 (four times the
 // wavefronts).  Eight modes: 71 thousand points 30 against 28 us, 143 thousand 41

@@ -635,27 +635,9 @@ static bool build_node_table(const Plan& P, std::vector<int>* out, std::string* 
   return true;
 }
 
-// Digits of every lattice point in node order, mode j at bits 8 j..8 j + 7:
-// C order visits the points of one level in lexicographic order, so each
-// point takes the next place of its level.
-static void build_digit_table(const Plan& P, std::vector<uint64_t>* out) {
-  out->assign((size_t)P.nodes_total, 0);
-  std::vector<int64_t> next(P.lvl.begin(), P.lvl.begin() + P.smax + 1);
-  int m[kMaxD] = {};
-  int S = 0;
-  for (int64_t it = 0; it < P.nodes_total; ++it) {
-    uint64_t pk = 0;
-    for (int j = 0; j < P.MD; ++j) pk |= (uint64_t)m[j] << (8 * j);
-    (*out)[(size_t)next[S]++] = pk;
-    for (int j = P.MD - 1; j >= 0; --j) {
-      ++m[j];
-      ++S;
-      if (m[j] < P.CD[j] && S <= P.smax) break;   // (the cap of a total photon cutoff)
-      S -= m[j];
-      m[j] = 0;
-    }
-  }
-}
+// Weak, so that the planner also links without the kernels (host-only builds
+// never bring a plan to a device).
+__attribute__((weak)) hipError_t fill_digit_table(const Plan& P);
 
 fd_status ensure_device(Plan* P, std::string* err) {
   int dev = 0;
@@ -707,15 +689,18 @@ fd_status ensure_device(Plan* P, std::string* err) {
       return FD_ERR_HIP;
     }
   }
-  if (P->MD > 0 && P->B == 1 && P->nodes_total <= kMaxDigitTable) {
-    std::vector<uint64_t> mt;
-    build_digit_table(*P, &mt);
-    if (hipMalloc((void**)&P->d_mtab, mt.size() * 8) != hipSuccess) {
-      *err = "hipMalloc of the digit table failed";
-      return FD_ERR_OOM;
-    }
-    if (hipMemcpy(P->d_mtab, mt.data(), mt.size() * 8, hipMemcpyHostToDevice) != hipSuccess) {
-      *err = "upload of the digit table failed";
+  if (P->MD > 0 && P->B == 1 && P->nodes_total <= kMaxDigitTable && fill_digit_table) {
+    // Without room for it the level kernels unrank each point instead (the
+    // one-workgroup sweeps, whose plans have a few thousand points, need it).
+    if (hipMalloc((void**)&P->d_mtab, (size_t)P->nodes_total * 8) != hipSuccess) {
+      (void)hipGetLastError();
+      P->d_mtab = nullptr;
+      if (P->small_fwd || P->small_vjp) {
+        *err = "hipMalloc of the digit table failed";
+        return FD_ERR_OOM;
+      }
+    } else if (fill_digit_table(*P) != hipSuccess) {
+      *err = "filling the digit table failed";
       return FD_ERR_HIP;
     }
   }
