@@ -564,6 +564,7 @@ fd_status fd_state_plan_create(int M, const int* cutoffs, fd_dtype dt, uint32_t 
     delete sp;
     return s;
   }
+  sp->inner->P.digit_table = false;
   *out = sp;
   return ok();
 }

@@ -191,6 +191,7 @@ struct Plan {
   // blocks whose rows do not fit the LDS staging stream them from HBM, per
   // kernel: forward block units, block fill, reverse block units, reverse fill
   bool st_fwd = false, st_ufill = false, st_vjp = false, st_ufill_vjp = false;
+  bool digit_table = true;     // whether the plan's kernels read d_mtab (state vectors unrank: 308 us of levels without, 286 with it and 148 to fill it, 8 modes cutoff 8)
   bool small_fwd = false, small_vjp = false;   // sweeps in one workgroup (see kSmallFwdItems)
   bool vjp_short = false;            // shorter row chunks of the block reverse kernel (LDS)
   bool odd_for(bool b_zero) const { return !b_zero || MU > 0; }

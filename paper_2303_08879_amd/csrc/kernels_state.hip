@@ -159,12 +159,12 @@ __global__ __launch_bounds__(kThreads) void k_state_level(DevPlan P, const cx<R>
 // ---------------------------------------------------------------------------
 // Tile geometry of each kernel (entries per tile, entries per lane, lanes per
 // workgroup): the forward mode stages 64 KB tiles in sixteen-wavefront
-// workgroups, the reverse mode 8 KB tiles in one-wavefront workgroups (the faster of the two shapes for each on the 8-mode cutoff-8
-// state).
+// workgroups.
 constexpr int kJvpTile = 4096, kJvpEPT = 4, kJvpThreads = kJvpTile / kJvpEPT;
-constexpr int kVjpTile = 512, kVjpEPT = 8, kVjpThreads = kVjpTile / kVjpEPT;
-constexpr int kVjpGrid = kVjpSlots;   // reverse-mode workgroups at most (one reduction slot each)
-constexpr int kVjpCols = kMaxD + kMaxD * (kMaxD + 1) / 2 + 1;   // bbar, Abar (i <= l), c
+// The reverse mode stages no amplitudes: its tiles only number the entries (and
+// at most 2048 of them leave 33 lanes of 64 busy at the worst cutoffs), two
+// workgroups of four wavefronts on each CU.
+constexpr int kVjpTile = 2048, kVjpGrid = 512, kVjpChunk = 8, kVjpUw = kMaxCut;
 
 struct StateTiles {
   int MD, sp, T, ntiles;
@@ -360,183 +360,251 @@ __global__ __launch_bounds__(kJvpThreads) void k_state_jvp(
 
 // Column of each cotangent: bbar_i (i), Abar_il for i <= l (MD + the upper
 // triangle row by row), sum g conj(psi) (last).
-__host__ __device__ __forceinline__ int vjp_col_pair(int MD, int i, int l) { return MD + i * MD - i * (i - 1) / 2 + (l - i); }
+__host__ __device__ constexpr int vjp_col_pair(int MD, int i, int l) { return MD + i * MD - i * (i - 1) / 2 + (l - i); }
+__host__ __device__ constexpr int vjp_cols(int MD) { return MD + MD * (MD + 1) / 2 + 1; }
 
-template <typename R>
-size_t state_vjp_lds_bytes() {
-  return (size_t)kVjpTile * sizeof(cx<R>) + (size_t)(kVjpThreads / 64) * kVjpCols * sizeof(double2) +
-         (kMaxCut + 1) * sizeof(double) + 2 * kMaxD * sizeof(int);
+// Reverse mode.  With m = k - 1_i the weights of a pair split into one factor
+// per mode:
+//   Abar_il = 1/2 sum_m u_i(m) conj(v_l(m)),   bbar_i = sum_m u_i(m) conj(psi_m),
+//   u_i(m) = sqrt(m_i + 1) g_{m+1_i},  v_l(m) = sqrt(m_l) psi_{m-1_l}
+// (zero outside the box), so an entry takes 2 MD shifted loads and scalings for
+// its MD (MD + 1) / 2 products, and the lanes keep every sum in registers: one
+// butterfly per sum and wavefront at the end.  Six to eight modes (28 to 45
+// complex sums) are shared by two wavefronts: each has half of the modes as rows i and
+// takes every other pair (i, l) between the halves, as u_i v_l or u_l v_i.
+//
+// What bounds it (8 modes, cutoff 8, c128: 480 us): 537 MB of psi and g once, 6
+// times that through the L1s for the shifts, with two wavefronts per SIMD to hide
+// the loads; the f64 FMAs take 257 us.  Loading an item only after the products
+// of the one before: 574 us; all loads of an item ahead: 28 registers spilled, 827.
+// The order of the items does not matter (chunks of 2 to 512: 1045 to 1081 us for the
+// call).  The version before staged tiles of psi in LDS and folded each of the
+// 45 sums of every tile over the lanes: 620 us.
+constexpr int vjp_halves(int MD) { return MD > 5 ? 2 : 1; }
+template <int MD>
+struct StateVjpSplit {
+  static constexpr int half(int i) { return vjp_halves(MD) == 2 && i >= (MD + 1) / 2 ? 1 : 0; }
+  // the mode of pair (i, l) that is the row; its half takes the pair
+  static constexpr int row(int i, int l) { return half(i) != half(l) && ((i + l) & 1) ? l : i; }
+};
+template <int MD>
+struct StateVjpSums {
+  double x[vjp_cols(MD)], y[vjp_cols(MD)];
+};
+__device__ __forceinline__ void add_conj(double& sx, double& sy, double ux, double uy, double vx, double vy) {
+  sx += ux * vx + uy * vy;
+  sy += uy * vx - ux * vy;
 }
 
-// Adds the wavefront's sum of (sx, sy) to *dst (a fixed butterfly, lane 0
-// writes: bitwise reproducible).
-__device__ __forceinline__ void wave_sum_into(double2* dst, double sx, double sy) {
+// The items of a wavefront (an item: 64 entries of a tile): items j, j + NG ..
+// of every chunk c0, c0 + step .. < c1 of kVjpChunk items.
+struct StateVjpItems {
+  int c0, c1, step, j, items;
+};
+// An item's entry m and its loads of psi (its own entry where there is no neighbour).
+template <int MD, typename R>
+struct StateVjpRaw {
+  uint64_t pk;   // trailing digits
+  int x0, fc;    // tile, entry
+  int kd;        // leading digit of mode `lane`
+  bool live;
+  cx<R> pv[MD > 0 ? MD : 1], p0;
+};
+// A wavefront's sums over its items.  The next item's loads of psi are issued
+// before an item's products, those of row i of g after the products of row i (in the
+// same registers).  Where an entry lacks one factor of a product, its weight is
+// zero; EXACT leaves the product out instead (the value may not be finite).
+// sq: the weights of v_l (sqrt(k)), then per mode those of u_i (kVjpUw each).
+template <int MD, int HALF, bool EXACT, typename R>
+__device__ __forceinline__ void state_vjp_sums(const StateTiles& G, const cx<R>* __restrict__ psi,
+                                               const cx<R>* __restrict__ g, const double* sq, const uint64_t* kp,
+                                               const StateVjpItems& I, StateVjpSums<MD>& Z) {
+  typedef StateVjpSplit<MD> W;
+  constexpr int MDA = MD > 0 ? MD : 1, NG = kThreads / 64 / vjp_halves(MD);
+  const int lane = threadIdx.x & 63, ept = (G.T + 63) >> 6;
+  const double* su = sq + kMaxCut + 1;
 #pragma unroll
-  for (int o = 32; o > 0; o >>= 1) {
-    sx += __shfl_xor(sx, o);
-    sy += __shfl_xor(sy, o);
-  }
-  if ((threadIdx.x & 63) == 0) {
-    dst->x += sx;
-    dst->y += sy;
-  }
-  // one term at a time: the scheduler keeps the next term's LDS reads behind
-  // this one (interleaving them only raises the register count)
-  __builtin_amdgcn_sched_barrier(0);
-}
-
-// sum over e of g_e conj(w_e p_e)
-template <typename R>
-__device__ __forceinline__ void dot_acc(double& sx, double& sy, double w, double gx, double gy, const cx<R>& p) {
-  const double px = w * (double)p.x, py = w * (double)p.y;
-  sx += gx * px + gy * py;
-  sy += gy * px - gx * py;
-}
-
-// Reverse mode: workgroup w visits tiles w, w + grid, ... (grid a multiple of
-// 8, so every visit of a workgroup stays on its XCD's range), each lane
-// holding the cotangent of its kVjpEPT entries; per term the lanes sum
-// their entries in order, each wavefront folds its lanes into its own LDS
-// row, and at the end the workgroup adds its wavefront rows in order into
-// slot (workgroup, column); the final kernel adds the slots of a column in
-// order (bitwise reproducible).  Terms are walked by runtime loops over the
-// modes, one term at a time (unrolled over the modes, the per-entry weights
-// of every mode stay live and the register count grows with the modes).
-template <typename R>
-__global__ __launch_bounds__(kVjpThreads) __attribute__((amdgpu_waves_per_eu(4))) void k_state_vjp(StateTiles G, const cx<R>* psi,
-                                                             const cx<R>* __restrict__ g, double2* __restrict__ slots) {
-  extern __shared__ __align__(16) unsigned char smem_raw[];
-  cx<R>* buf = reinterpret_cast<cx<R>*>(smem_raw);
-  double2* red = reinterpret_cast<double2*>(smem_raw + (size_t)kVjpTile * sizeof(cx<R>));   // waves x kVjpCols
-  double* sq = reinterpret_cast<double*>(red + (kVjpThreads / 64) * kVjpCols);
-  int* ks = reinterpret_cast<int*>(sq + kMaxCut + 1);   // leading digits of the tile
-  int* sst = ks + kMaxD;                                  // C-order strides
-  const int MD = G.MD, sp = G.sp, T = G.T;
-  const int ncol = MD + MD * (MD + 1) / 2 + 1;
-  for (int v = threadIdx.x; v <= kMaxCut; v += kVjpThreads) sq[v] = sqrt((double)v);
-  for (int p = threadIdx.x; p < (kVjpThreads / 64) * kVjpCols; p += kVjpThreads) red[p] = make_double2(0.0, 0.0);
-  if (threadIdx.x < kMaxD) sst[threadIdx.x] = G.stride[threadIdx.x];
-  double2* wred = red + (threadIdx.x >> 6) * kVjpCols;
-  // trailing digits of this lane's tile entries (the same in every tile), 6
-  // bits per mode; an entry beyond the tile gets digit 0 everywhere, which
-  // zeroes every shifted term
-  uint64_t kp[kVjpEPT];
+  for (int p = 0; p < vjp_cols(MD); ++p) Z.x[p] = Z.y[p] = 0.0;
+  // lane d finds leading digit d of an item's tile
+  int dst = 1, dc = 1;
+  double dis = 1.0, dic = 1.0;
 #pragma unroll
-  for (int e = 0; e < kVjpEPT; ++e) {
-    const int f = threadIdx.x + e * kVjpThreads;
+  for (int d = 0; d < MD; ++d)
+    if (lane == d) {
+      dst = G.stride[d];
+      dc = G.C[d];
+      dis = G.inv_stride[d];
+      dic = G.inv_c[d];
+    }
+  cx<R> gu[MDA], g0 = czero<R>();
+  auto fetch = [&](int q, StateVjpRaw<MD, R>& r) {
+    const int tile = q / ept, f = (q - tile * ept) * 64 + lane;
+    r.x0 = tile * G.T;
+    r.kd = lane < G.sp ? cdigit(r.x0, dst, dc, dis, dic) : 0;
+    r.live = f < G.T;
+    r.fc = r.live ? f : 0;
+    r.pk = kp[r.fc];
+    const cx<R>* pp = psi + r.x0;
+#pragma unroll
+    for (int d = 0; d < MD; ++d) {
+      // a leading mode's shift is the same for all lanes, a trailing one's is short
+      const bool lead = d < G.sp;
+      const int s = G.stride[d], kl = __builtin_amdgcn_readlane(r.kd, d), kt = (int)((r.pk >> (8 * d)) & 255);
+      r.pv[d] = ld(pp - (lead && kl > 0 ? s : 0) + (r.fc - (!lead && kt > 0 ? s : 0)));
+    }
+    r.p0 = ld(pp + r.fc);
+  };
+  auto fetch_row = [&](int d, const StateVjpRaw<MD, R>& r) {
+    const bool lead = d < G.sp;
+    const int s = G.stride[d], kl = __builtin_amdgcn_readlane(r.kd, d), kt = (int)((r.pk >> (8 * d)) & 255);
+    gu[d] = ld(g + r.x0 + (lead && kl + 1 < G.C[d] ? s : 0) + (r.fc + (!lead && kt + 1 < G.C[d] ? s : 0)));
+  };
+  auto fetch_rows = [&](const StateVjpRaw<MD, R>& r) {
+    if (HALF == 0) g0 = ld(g + r.x0 + r.fc);
+#pragma unroll
+    for (int d = 0; d < MD; ++d)
+      if (W::half(d) == HALF) fetch_row(d, r);
+  };
+  // the products of item r, then the loads of row after row of item n
+  auto add = [&](const StateVjpRaw<MD, R>& r, const StateVjpRaw<MD, R>& n) {
+    const double px = (double)r.p0.x, py = (double)r.p0.y;
+    int k[MDA];
+    double vx[MDA], vy[MDA];
+#pragma unroll
+    for (int d = 0; d < MD; ++d) {
+      k[d] = __builtin_amdgcn_readlane(r.kd, d) + (int)((r.pk >> (8 * d)) & 255);
+      const double w = sq[k[d]];
+      vx[d] = w * (double)r.pv[d].x;
+      vy[d] = w * (double)r.pv[d].y;
+    }
+    if (HALF == 0) {
+      if (r.live) add_conj(Z.x[vjp_cols(MD) - 1], Z.y[vjp_cols(MD) - 1], (double)g0.x, (double)g0.y, px, py);
+      g0 = ld(g + n.x0 + n.fc);
+    }
+#pragma unroll
+    for (int i = 0; i < MD; ++i) {
+      if (W::half(i) != HALF) continue;
+      const double w = r.live ? su[i * kVjpUw + k[i]] : 0.0;
+      const bool up = w != 0.0;
+      const double ux = w * (double)gu[i].x, uy = w * (double)gu[i].y;
+      fetch_row(i, n);
+      if (!EXACT || up) add_conj(Z.x[i], Z.y[i], ux, uy, px, py);
+#pragma unroll
+      for (int l = 0; l < MD; ++l) {
+        const int a = i < l ? i : l, b = i < l ? l : i;
+        if (W::row(a, b) != i) continue;
+        if (!EXACT || (up && k[l] > 0))
+          add_conj(Z.x[vjp_col_pair(MD, a, b)], Z.y[vjp_col_pair(MD, a, b)], ux, uy, vx[l], vy[l]);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  };
+  int c = I.c0, j = I.j;
+  // the next item of this wavefront, -1 after the last
+  auto next = [&]() -> int {
+    if (c >= I.c1 || c * kVjpChunk + j >= I.items) return -1;   // (only the last chunk is short)
+    const int q = c * kVjpChunk + j;
+    j += NG;
+    if (j >= kVjpChunk) {
+      j = I.j;
+      c += I.step;
+    }
+    return q;
+  };
+  StateVjpRaw<MD, R> ra, rb;
+  int q = next();
+  if (q < 0) return;
+  fetch(q, ra);
+  fetch_rows(ra);
+  for (;;) {
+    const int qb = next();
+    fetch(qb >= 0 ? qb : q, rb);
+    add(ra, rb);
+    if (qb < 0) return;
+    q = next();
+    fetch(q >= 0 ? q : qb, ra);
+    add(rb, ra);
+    if (q < 0) return;
+  }
+}
+
+// The sums of one wavefront, folded over its lanes, into red (its row of columns).
+template <int MD, int HALF, typename R>
+__device__ __forceinline__ void state_vjp_wave(const StateTiles& G, const cx<R>* __restrict__ psi,
+                                               const cx<R>* __restrict__ g, const double* sq, const uint64_t* kp,
+                                               const StateVjpItems& I, double2* red) {
+  typedef StateVjpSplit<MD> W;
+  constexpr int NC = vjp_cols(MD);
+  StateVjpSums<MD> Z;
+  state_vjp_sums<MD, HALF, false, R>(G, psi, g, sq, kp, I, Z);
+  auto each = [&](auto&& fn) {   // the columns this half takes
+    if (HALF == 0) fn(NC - 1);
+#pragma unroll
+    for (int i = 0; i < MD; ++i) {
+      if (W::half(i) == HALF) fn(i);
+#pragma unroll
+      for (int l = i; l < MD; ++l)
+        if (W::half(W::row(i, l)) == HALF) fn(vjp_col_pair(MD, i, l));
+    }
+  };
+  bool bad = false;
+  each([&](int p) { bad = bad || !(fabs(Z.x[p]) + fabs(Z.y[p]) < __builtin_inf()); });
+  if (__ballot(bad) != 0ull) state_vjp_sums<MD, HALF, true, R>(G, psi, g, sq, kp, I, Z);
+  each([&](int p) {
+    double x = Z.x[p], y = Z.y[p];
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+      x += __shfl_xor(x, o);
+      y += __shfl_xor(y, o);
+    }
+    const double h = p >= MD && p < NC - 1 ? 0.5 : 1.0;
+    if ((threadIdx.x & 63) == 0) red[p] = make_double2(h * x, h * y);
+  });
+}
+
+// Persistent workgroups (a multiple of 8): workgroup v runs on XCD v mod 8,
+// which takes one contiguous eighth of the items in order, so that the shifted
+// entries of the faster modes are found in its own L2.  Wavefronts (pairs of
+// them where two share the sums) take items in turn; the workgroup adds its
+// wavefronts' rows in order into its slot, the final kernel the slots of a column.
+template <int MD, typename R>
+__global__ __launch_bounds__(kThreads, 2) void k_state_vjp(StateTiles G, const cx<R>* __restrict__ psi,
+                                                           const cx<R>* __restrict__ g, double2* __restrict__ slots) {
+  constexpr int NC = vjp_cols(MD), NW = kThreads / 64, NG = NW / vjp_halves(MD);
+  __shared__ uint64_t kp[kVjpTile];        // trailing digits of a tile's entries, 8 bits per mode
+  __shared__ double sq[kMaxCut + 1 + (MD > 0 ? MD : 1) * kVjpUw];
+  __shared__ double2 red[NW * NC];
+  for (int v = threadIdx.x; v <= kMaxCut; v += kThreads) sq[v] = sqrt((double)v);
+#pragma unroll
+  for (int d = 0; d < MD; ++d)
+    for (int v = threadIdx.x; v < kVjpUw; v += kThreads)
+      sq[kMaxCut + 1 + d * kVjpUw + v] = v + 1 < G.C[d] ? sqrt(v + 1.0) : 0.0;
+  for (int p = threadIdx.x; p < NW * NC; p += kThreads) red[p] = make_double2(0.0, 0.0);
+  for (int f = threadIdx.x; f < G.T; f += kThreads) {
     uint64_t p = 0;
 #pragma unroll
-    for (int d = 0; d < kMaxD; ++d)
-      if (f < T && d >= sp && d < MD)
-        p |= (uint64_t)cdigit(f, G.stride[d], G.C[d], G.inv_stride[d], G.inv_c[d]) << (6 * d);
-    kp[e] = p;
-  }
-  auto digit = [](uint64_t p, int d) { return (int)((p >> (6 * d)) & 63); };
-  for (int v = blockIdx.x; v < G.ntiles; v += gridDim.x) {
-    const int x0 = state_tile_of(G.ntiles, v) * T;
-    __syncthreads();   // the previous tile's LDS reads are done
-    if (threadIdx.x < sp) ks[threadIdx.x] = cdigit(x0, G.stride[threadIdx.x], G.C[threadIdx.x],
-                                                   G.inv_stride[threadIdx.x], G.inv_c[threadIdx.x]);
-    cx<R> gv[kVjpEPT];
-    load_lane_entries<kVjpThreads, kVjpEPT>(gv, g + x0, T);
-    stage_tile<kVjpThreads, kVjpEPT>(buf, psi + x0, T);
-    double gx[kVjpEPT], gy[kVjpEPT];
-#pragma unroll
-    for (int e = 0; e < kVjpEPT; ++e) {
-      gx[e] = (double)gv[e].x;
-      gy[e] = (double)gv[e].y;
-    }
-    __syncthreads();
-    // terms inside tile t
-    {
-      double sx = 0.0, sy = 0.0;
-#pragma unroll
-      for (int e = 0; e < kVjpEPT; ++e) {
-        const int f = threadIdx.x + e * kVjpThreads;
-        if (f < T) dot_acc(sx, sy, 1.0, gx[e], gy[e], buf[f]);
-      }
-      wave_sum_into(wred + ncol - 1, sx, sy);
-    }
-#pragma unroll 1
-    for (int i = sp; i < MD; ++i) {
-      const int si = sst[i];
-      {
-        double sx = 0.0, sy = 0.0;
-#pragma unroll
-        for (int e = 0; e < kVjpEPT; ++e) {
-          const int f = threadIdx.x + e * kVjpThreads;
-          const int ki = digit(kp[e], i);
-          if (ki >= 1) dot_acc(sx, sy, sq[ki], gx[e], gy[e], buf[f - si]);
-        }
-        wave_sum_into(wred + i, sx, sy);
-      }
-#pragma unroll 1
-      for (int l = i; l < MD; ++l) {
-        const int sil = si + sst[l];
-        double sx = 0.0, sy = 0.0;
-#pragma unroll
-        for (int e = 0; e < kVjpEPT; ++e) {
-          const int f = threadIdx.x + e * kVjpThreads;
-          const int ki = digit(kp[e], i), kl = digit(kp[e], l) - (l == i ? 1 : 0);
-          if (ki >= 1 && kl >= 1) dot_acc(sx, sy, 0.5 * sq[ki] * sq[kl], gx[e], gy[e], buf[f - sil]);
-        }
-        wave_sum_into(wred + vjp_col_pair(MD, i, l), sx, sy);
-      }
-    }
-    // terms whose leading part is 1_i: tile t - 1_i
-#pragma unroll 1
-    for (int i = 0; i < sp; ++i) {
-      const int ki = ks[i];
-      if (ki < 1) continue;   // uniform
-      const int xs = x0 - sst[i];
-      __syncthreads();
-      stage_tile<kVjpThreads, kVjpEPT>(buf, psi + xs, T);
-      __syncthreads();
-      const double wi = sq[ki];
-      {
-        double sx = 0.0, sy = 0.0;
-#pragma unroll
-        for (int e = 0; e < kVjpEPT; ++e) {
-          const int f = threadIdx.x + e * kVjpThreads;
-          if (f < T) dot_acc(sx, sy, wi, gx[e], gy[e], buf[f]);
-        }
-        wave_sum_into(wred + i, sx, sy);
-      }
-#pragma unroll 1
-      for (int l = sp; l < MD; ++l) {
-        const int sl = sst[l];
-        double sx = 0.0, sy = 0.0;
-#pragma unroll
-        for (int e = 0; e < kVjpEPT; ++e) {
-          const int f = threadIdx.x + e * kVjpThreads;
-          const int kl = digit(kp[e], l);
-          if (kl >= 1) dot_acc(sx, sy, 0.5 * wi * sq[kl], gx[e], gy[e], buf[f - sl]);
-        }
-        wave_sum_into(wred + vjp_col_pair(MD, i, l), sx, sy);
-      }
-      // two leading modes: one amplitude per entry from memory
-#pragma unroll 1
-      for (int l = i; l < sp; ++l) {
-        const int kl = ks[l] - (l == i ? 1 : 0);
-        if (kl < 1) continue;   // uniform
-        cx<R> p[kVjpEPT];
-        load_lane_entries<kVjpThreads, kVjpEPT>(p, psi + (xs - sst[l]), T);
-        const double w = 0.5 * wi * sq[kl];
-        double sx = 0.0, sy = 0.0;
-#pragma unroll
-        for (int e = 0; e < kVjpEPT; ++e) dot_acc(sx, sy, w, gx[e], gy[e], p[e]);
-        wave_sum_into(wred + vjp_col_pair(MD, i, l), sx, sy);
-      }
-    }
+    for (int d = 0; d < MD; ++d)
+      if (d >= G.sp) p |= (uint64_t)cdigit(f, G.stride[d], G.C[d], G.inv_stride[d], G.inv_c[d]) << (8 * d);
+    kp[f] = p;
   }
   __syncthreads();
-  for (int p = threadIdx.x; p < ncol; p += kVjpThreads) {
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int items = G.ntiles * ((G.T + 63) >> 6), chunks = (items + kVjpChunk - 1) / kVjpChunk;
+  const int per = (chunks + 7) >> 3, xcd = blockIdx.x & 7;
+  const StateVjpItems I{xcd * per + (int)(blockIdx.x >> 3), min((xcd + 1) * per, chunks), (int)(gridDim.x >> 3),
+                        wave / vjp_halves(MD), items};
+  if (vjp_halves(MD) == 1 || (wave & 1) == 0)
+    state_vjp_wave<MD, 0, R>(G, psi, g, sq, kp, I, red + wave * NC);
+  else
+    state_vjp_wave<MD, vjp_halves(MD) - 1, R>(G, psi, g, sq, kp, I, red + wave * NC);
+  __syncthreads();
+  for (int p = threadIdx.x; p < NC; p += kThreads) {
     double sx = 0.0, sy = 0.0;
-    for (int wv = 0; wv < kVjpThreads / 64; ++wv) {
-      sx += red[wv * kVjpCols + p].x;
-      sy += red[wv * kVjpCols + p].y;
+    for (int wv = 0; wv < NW; ++wv) {
+      sx += red[wv * NC + p].x;
+      sy += red[wv * NC + p].y;
     }
-    slots[(size_t)blockIdx.x * ncol + p] = make_double2(sx, sy);
+    slots[(size_t)blockIdx.x * NC + p] = make_double2(sx, sy);
   }
 }
 
@@ -650,12 +718,28 @@ static hipError_t run_state_vjp_t(const Plan& Pl, const void* c, const void* psi
   const StateTiles G = state_tiles(Pl, kVjpTile);
   // at most kVjpGrid <= kVjpSlots workgroups (a multiple of 8), one slot each
   static_assert(kVjpGrid <= kVjpSlots && kVjpGrid % 8 == 0, "reduction slots");
-  const int grid = std::min(G.ntiles, kVjpGrid);
+  const int64_t items = (int64_t)G.ntiles * ((G.T + 63) / 64);
+  const int grid = (int)std::min<int64_t>((items + 8 * kVjpChunk - 1) / (8 * kVjpChunk) * 8, kVjpGrid);
   {
     KTimer kt(Pl, KK_VJP_LEVEL, st);
-    const size_t shm = state_vjp_lds_bytes<R>();
-    hipLaunchKernelGGL((k_state_vjp<R>), dim3((unsigned)grid), dim3(kVjpThreads), shm, st, G,
-                       static_cast<const cx<R>*>(psi), static_cast<const cx<R>*>(g), slots);
+#define FD_STATE_VJP(MDV)                                                                                  \
+  case MDV:                                                                                                \
+    hipLaunchKernelGGL((k_state_vjp<MDV, R>), dim3((unsigned)grid), dim3(kThreads), 0, st, G,              \
+                       static_cast<const cx<R>*>(psi), static_cast<const cx<R>*>(g), slots);               \
+    break;
+    switch (MD) {
+      FD_STATE_VJP(0)
+      FD_STATE_VJP(1)
+      FD_STATE_VJP(2)
+      FD_STATE_VJP(3)
+      FD_STATE_VJP(4)
+      FD_STATE_VJP(5)
+      FD_STATE_VJP(6)
+      FD_STATE_VJP(7)
+      FD_STATE_VJP(8)
+      default: return hipErrorInvalidValue;
+    }
+#undef FD_STATE_VJP
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }

@@ -689,7 +689,7 @@ fd_status ensure_device(Plan* P, std::string* err) {
       return FD_ERR_HIP;
     }
   }
-  if (P->MD > 0 && P->B == 1 && P->nodes_total <= kMaxDigitTable && fill_digit_table) {
+  if (P->digit_table && P->MD > 0 && P->B == 1 && P->nodes_total <= kMaxDigitTable && fill_digit_table) {
     // Without room for it the level kernels unrank each point instead (the
     // one-workgroup sweeps, whose plans have a few thousand points, need it).
     if (hipMalloc((void**)&P->d_mtab, (size_t)P->nodes_total * 8) != hipSuccess) {
