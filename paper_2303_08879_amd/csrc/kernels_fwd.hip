@@ -140,7 +140,8 @@ hipError_t launch_fwd_level(const Plan& Pl, bool odd, int S, const void* const* 
   return launch_fwd_level_t<double>(Pl, P, odd, S, L, Ai, bi, st);
 }
 
-// Copy of one level of every family (checkpoints of a checkpointed sweep):
+// Copy of one level of every family (a checkpoint before its segment, for the
+// one-workgroup reverse sweep, which takes a segment in one piece):
 // family blockIdx.y, n[f] 16-byte (complex128) or 8-byte entries.
 struct CopyFams {
   const void* src[kMaxFam];
@@ -268,8 +269,11 @@ static hipError_t launch_out_perm_t(const Plan& Pl, const DevPlan& P, const cx<R
 
 // Forward sweep for a checkpointed reverse sweep: F0 at every level goes to
 // the saved buffer, the other families run in a two-level ring (the first
-// two slots of the segment buffer), and the level just below each segment is
-// copied into its checkpoint.
+// two slots of the segment buffer) except at the level just below each segment,
+// which is written to its checkpoint and read there by the next level (copying
+// these levels out of the ring and, in the reverse sweep, into the segment
+// buffer took 1.09 of the 17.1 ms of five detected modes of cutoff 8 and an undetected one of
+// cutoff 30 in segments of six levels).
 template <typename R>
 static hipError_t run_forward_ckpt_t(const Plan& Pl, bool odd, const void* A, const void* b, const void* c,
                                      void* rho, char* ws, char* saved, hipStream_t st) {
@@ -292,16 +296,17 @@ static hipError_t run_forward_ckpt_t(const Plan& Pl, bool odd, const void* A, co
   }
   const int s = Pl.ckpt, MD = Pl.MD;
   auto used = [&](int f) { return ckpt_keeps_family(Pl, f) && (odd || f >= 1 + 2 * MD); };
-  auto slot = [&](int f, int k) {   // ring slot k of family f
-    return ws + Sg.fam[f] + (size_t)k * Pl.maxN[Pl.fam_group[f]] * Pl.B * eb;
+  auto level = [&](int f, int S) -> char* {   // family f at level S
+    if ((S + 1) % s == 0 && S < Pl.smax) return saved + Lc.ck[(size_t)((S + 1) / s - 1) * Pl.nfam + f];
+    return ws + Sg.fam[f] + (size_t)(S & 1) * Pl.maxN[Pl.fam_group[f]] * Pl.B * eb;
   };
   for (int S = 0; S <= Pl.smax && MD > 0; ++S) {
     const void* rd[kMaxFam] = {};
     void* wr[kMaxFam] = {};
     for (int f = 1; f < Pl.nfam; ++f) {
       if (!used(f)) continue;
-      rd[f] = S > 0 ? slot(f, (S - 1) & 1) : nullptr;
-      wr[f] = slot(f, S & 1);
+      rd[f] = S > 0 ? level(f, S - 1) : nullptr;
+      wr[f] = level(f, S);
     }
     const cx<R>* f0cur = f0 + (size_t)Pl.lvl[S] * Pl.B;
     cx<R>* f0nxt = S < Pl.smax ? f0 + (size_t)Pl.lvl[S + 1] * Pl.B : nullptr;
@@ -310,20 +315,6 @@ static hipError_t run_forward_ckpt_t(const Plan& Pl, bool odd, const void* A, co
       e = launch_fwd_level(Pl, odd, S, rd, wr, f0cur, f0nxt, Ai, bi, st);
     }
     if (e != hipSuccess) return e;
-    if ((S + 1) % s == 0 && S < Pl.smax) {
-      // level S is the one below segment (S + 1) / s: keep it
-      const int ck = (S + 1) / s - 1;
-      const void* src[kMaxFam] = {};
-      void* dst[kMaxFam] = {};
-      int64_t n[kMaxFam] = {};
-      for (int f = 1; f < Pl.nfam; ++f) {
-        if (!used(f)) continue;
-        src[f] = wr[f];
-        dst[f] = saved + Lc.ck[(size_t)ck * Pl.nfam + f];
-        n[f] = Pl.ncnt[(size_t)Pl.fam_group[f] * (Pl.smax + 1) + S] * Pl.B;
-      }
-      if ((e = launch_copy_fams(Pl, src, dst, n, st)) != hipSuccess) return e;
-    }
   }
   if (!rho) return hipSuccess;
   return launch_out_perm_t<R>(Pl, P, f0, rho, st);

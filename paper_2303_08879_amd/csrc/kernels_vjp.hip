@@ -451,16 +451,20 @@ static hipError_t run_vjp_t(const Plan& Pl, bool odd, const void* A, const void*
     return reinterpret_cast<cx<R>*>(ws + Sg.fam[f] +
                                     (size_t)seg_node(Pl, Pl.fam_group[f], lo, L) * Pl.B * sizeof(cx<R>));
   };
-  // forward values of levels lo..hi from the checkpoint below lo
-  auto restore = [&](int lo, int hi) -> hipError_t {
-    const int c = lo / Pl.ckpt;
-    if (c > 0) {
+  // the checkpoint below segment lo > 0
+  auto ck_level = [&](int f, int lo) {
+    return reinterpret_cast<const cx<R>*>(sv + Lc.ck[(size_t)(lo / Pl.ckpt - 1) * Pl.nfam + f]);
+  };
+  // forward values of levels lo..hi from the checkpoint below lo (`whole`: which
+  // then stands before them in the segment buffer)
+  auto restore = [&](int lo, int hi, bool whole) -> hipError_t {
+    if (lo > 0 && whole) {
       const void* src[kMaxFam] = {};
       void* dst[kMaxFam] = {};
       int64_t n[kMaxFam] = {};
       for (int f = 1; f < Pl.nfam; ++f) {
         if (!used(f)) continue;
-        src[f] = sv + Lc.ck[(size_t)(c - 1) * Pl.nfam + f];
+        src[f] = ck_level(f, lo);
         dst[f] = seg_slot(f, lo, lo - 1);
         n[f] = Pl.ncnt[(size_t)Pl.fam_group[f] * (Pl.smax + 1) + lo - 1] * Pl.B;
       }
@@ -473,7 +477,7 @@ static hipError_t run_vjp_t(const Plan& Pl, bool odd, const void* A, const void*
       void* wr[kMaxFam] = {};
       for (int f = 1; f < Pl.nfam; ++f) {
         if (!used(f)) continue;
-        rd[f] = L > 0 ? seg_slot(f, lo, L - 1) : nullptr;
+        rd[f] = L > lo ? seg_slot(f, lo, L - 1) : L > 0 ? ck_level(f, lo) : nullptr;
         wr[f] = seg_slot(f, lo, L);
       }
       // F0 of level L + 1 is written again with the values it already holds
@@ -496,7 +500,7 @@ static hipError_t run_vjp_t(const Plan& Pl, bool odd, const void* A, const void*
     const int every = ck ? Pl.ckpt : Pl.smax + 1;
     for (int lo = Pl.smax / every * every; lo >= 0; lo -= every) {
       const int hi = std::min(lo + every - 1, Pl.smax);
-      if (ck && (e = restore(lo, hi)) != hipSuccess) return e;
+      if (ck && (e = restore(lo, hi, true)) != hipSuccess) return e;
       for (int f = 1; f < Pl.nfam; ++f) {
         // a segment buffer starts with level lo - 1: its node 0 is that many
         // nodes before it
@@ -565,7 +569,7 @@ static hipError_t run_vjp_t(const Plan& Pl, bool odd, const void* A, const void*
   for (int S = Pl.smax; S >= 0 && MD > 0; --S) {
     if (ck && S < seg_lo) {
       seg_lo = (S / Pl.ckpt) * Pl.ckpt;
-      if ((e = restore(seg_lo, S)) != hipSuccess) return e;
+      if ((e = restore(seg_lo, S, false)) != hipSuccess) return e;
     }
     VjpPtrs<R> Vp;
     std::memset(&Vp, 0, sizeof(Vp));
@@ -576,7 +580,7 @@ static hipError_t run_vjp_t(const Plan& Pl, bool odd, const void* A, const void*
         Vp.fprev[f] = fptr<R>(Pl, sv, foff, g, S - 1);
         Vp.fcur[f] = fptr<R>(Pl, sv, foff, g, S);
       } else if (used(f)) {
-        Vp.fprev[f] = S > 0 ? seg_slot(f, seg_lo, S - 1) : nullptr;
+        Vp.fprev[f] = S > seg_lo ? seg_slot(f, seg_lo, S - 1) : S > 0 ? ck_level(f, seg_lo) : nullptr;
         Vp.fcur[f] = seg_slot(f, seg_lo, S);
       }
       Vp.gprev[f] = gptr<R>(Pl, ws, V.gfam[f], g, S - 1);
