@@ -14,7 +14,7 @@ amplitude forward, 48 B reverse, complex128) over its HIP-event time, against
 (2 modes; 4 modes with an undetected mode; 5 modes with an undetected mode),
 the complex64 variant of every single-circuit workload with its measured
 error against the complex128 result, the 64-circuit gradient batch, the
-256-circuit uneven batch (persistent batched launch against a graph-replayed
+256-circuit uneven batch (merged level launches against a graph-replayed
 per-circuit loop), the pure-state, total-cutoff and forward-mode legs, and
 the CPU oracle on a bounded sample.
 
@@ -55,10 +55,10 @@ def workload(name):
 # Sources each level kernel is compiled from: a counter summary applies to a
 # kernel only while these hash to the value recorded with it.
 KERNEL_SOURCES = {
-    "k_vjp_point": ["kernels_vjp.hip", "vjp_common.h", "fd_device.h"],
-    "k_vjp_block": ["kernels_vjp_block.hip", "vjp_common.h", "fd_device.h"],
-    "k_fwd_point": ["kernels_fwd.hip", "fwd_units.h", "fd_device.h"],
-    "k_fwd_block": ["kernels_fwd.hip", "fwd_units.h", "fd_device.h"],
+    "k_vjp_point": ["kernels_vjp_point.hip", "vjp_point_units.h", "vjp_common.h", "pt_units.h", "fd_device.h"],
+    "k_vjp_block": ["vjp_block.h", "vjp_common.h", "fd_device.h"],
+    "k_fwd_point": ["kernels_point.hip", "pt_units.h", "fd_device.h"],
+    "k_fwd_block": ["fwd_block.h", "fwd_units.h", "fd_device.h"],
     "k_state_level": ["kernels_state.hip", "fd_device.h"],
     "k_state_jvp": ["kernels_state.hip", "fd_device.h"],
     "k_state_vjp": ["kernels_state.hip", "fd_device.h"],
@@ -304,7 +304,7 @@ def cpu_selective(circ, s128, s64):
 
 def batched_leg(reps=1):
     """The uneven batch (256 circuits, M 3..6, cutoffs 8..16, 0 or 1 undetected
-    mode with cutoff 20..40, b = 0, complex128): batched persistent launches
+    mode with cutoff 20..40, b = 0, complex128): batched calls
     (one per memory group) against a loop of per-circuit fock_diag_fwd calls on
     the same stream and buffers, each replaying its captured graph; then the
     complex64 variant of every circuit (per-circuit calls, equal to the batched

@@ -303,7 +303,7 @@ size_t saved_bytes(const Plan& P);
 // with one); includes the segment buffer of a checkpointed plan.
 size_t vjp_ws_bytes(const Plan& P);
 void count_work(const Plan& P, bool b_zero, int64_t* targets, int64_t* terms);
-// Batched forward (one persistent sweep launch over every circuit); plans
+// Batched forward (the levels of every circuit in shared launches); plans
 // already on the current device, workspaces checked by the caller.
 fd_status run_forward_batch(int n, Plan* const* plans, const bool* odd, const void* const* A,
                             const void* const* b, const void* const* c, void* const* rho, void* const* ws,
