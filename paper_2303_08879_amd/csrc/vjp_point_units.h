@@ -15,9 +15,13 @@
 // and b^H h come out of the same products; eight modes fill the tile and form
 // both on the vector unit.
 //
-// What bounds it: 48 bytes per computed amplitude.  With one point per lane the
-// two 16-vectors and the reduction's staging held 202 VGPRs + 17 KB of LDS per
-// wavefront (two wavefronts per SIMD, 60 % of their cycles waiting).
+// What bounds it: 48 bytes per computed amplitude, which the counters put at 1.25x;
+// the large levels of eight modes of cutoff 8 move 495 MB in 134 us, 3.7 TB/s (a
+// large copy on this card: 4.9).  Loading a tile's first bridge before the products
+// of the tile before it made no difference (3608 against 3620 us).  With one point
+// per lane the two 16-vectors and the reduction's staging held 202 VGPRs + 17 KB of
+// LDS per wavefront (two wavefronts per SIMD, 60 % of their cycles waiting): 5.24 ms
+// per reverse sweep, now 4.06.
 #pragma once
 
 #include "vjp_common.h"
