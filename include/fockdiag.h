@@ -62,10 +62,13 @@ typedef enum {
 typedef enum { FD_C128 = 0, FD_C64 = 1 } fd_dtype;
 
 /* Plan flags: how the displacement vector b is treated.
- * FD_B_AUTO    the forward call copies b to the host (one synchronising
- *              2M-element read) and takes the b = 0 schedule when b is
+ * FD_B_AUTO    takes the b = 0 schedule when every mode is detected and b is
  *              exactly zero (Sec. 2.4: odd-weight amplitudes then vanish and
- *              pivots need not be read);
+ *              pivots need not be read).  The call copies b to the host for
+ *              this (one synchronising 2M-element read) unless it runs in one
+ *              workgroup, which decides on the device (small plans, with room
+ *              for the general schedule), or has undetected modes, whose
+ *              schedule is the same for every b;
  * FD_B_ZERO    the caller promises b == 0 (the b = 0 schedule, no host read);
  *              a non-zero b is then reported through fd_device_status;
  * FD_B_GENERAL always the general schedule (no host read). */
