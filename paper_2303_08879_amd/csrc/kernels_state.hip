@@ -141,13 +141,13 @@ __global__ __launch_bounds__(kThreads) void k_state_level(DevPlan P, const cx<R>
 // directional derivative for the symmetric part of dA, as A enters through
 // (A + A^T)/2.
 //
-// Both kernels walk psi (C order, last kept mode fastest) by tiles: the
+// Both kernels number psi (C order, last kept mode fastest) by tiles: the
 // trailing modes sp..MD-1 span a tile of T = prod_{d >= sp} C_d entries (at
 // most the kernel's tile size) and the leading modes number the tiles, so entry x is
 // entry x mod T of tile x / T.  A shifted amplitude of a tile-t entry lies in
 // tile t (every mode of the shift trailing), in tile t - 1_i (one leading
-// mode i) or in tile t - 1_i - 1_l (two leading modes).  A workgroup stages
-// tile t in LDS and serves the terms of the first kind from it, then stages
+// mode i) or in tile t - 1_i - 1_l (two leading modes).  In the forward mode a
+// workgroup stages tile t in LDS and serves the terms of the first kind from it, then stages
 // tile t - 1_i for each leading i with k_i >= 1 and serves the terms whose
 // leading part is 1_i, reading the one amplitude of each two-leading-mode
 // term straight from memory.  Each psi entry is so read 1 + (leading modes)

@@ -126,7 +126,7 @@ def test_undetected_rows(cut):
 
 # sums in one wavefront and split over two (six and more modes), tiles that are
 # not whole wavefronts, a last chunk that is short
-STATES = [[64], [64, 33], [40, 37], [13, 9, 8], [5, 4, 3, 6, 2], [4, 3, 5, 2, 3, 4], [3, 4, 2, 3, 2, 3, 3], [4] * 8]
+STATES = [[1, 1], [64], [64, 33], [40, 37], [13, 9, 8], [5, 4, 3, 6, 2], [4, 3, 5, 2, 3, 4], [3, 4, 2, 3, 2, 3, 3], [4] * 8]
 
 
 def state_vjp(cut, c, psi, g, dtype):
