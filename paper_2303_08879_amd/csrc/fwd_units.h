@@ -422,42 +422,44 @@ __device__ __forceinline__ cx<R> out_perm_elem(const DevPlan& P, const int* spn,
   return ld(f0 + node_of_cindex(P, spn, slv, (int)idx));
 }
 
+// Node of lattice point n0 + lane in C order (the last point beyond the end).
+__device__ __forceinline__ int out_tile_node(const DevPlan& P, const int* spn, const int64_t* slv, int64_t n0,
+                                             int64_t N) {
+  static_assert(kOutTN == 64, "a tile's points are the lanes of a wavefront");
+  return (int)node_of_cindex(P, spn, slv, (int)min(n0 + (threadIdx.x & 63), N - 1));
+}
+
 // F0 -> rho for plans with undetected modes, one tile of kOutTN consecutive
 // C-order lattice points n by kOutTK consecutive block entries kappa, through
 // LDS: every node's kOutTK entries are read as one contiguous run and every
 // kappa's kOutTN outputs written as one (the element-wise gather reads a
 // 64-byte sector per 16-byte element).  256 threads; returns 1 if a
-// non-finite value was stored.
+// non-finite value was stored.  Bound by HBM: five detected modes of cutoff 8 and an
+// undetected one of cutoff 30 (944 MB) 178 us, 5.3 TB/s; splitting the index of each
+// of the 1024 entries with 64-bit divisions, one load after the other, took 272.
 template <typename R>
 __device__ __forceinline__ int out_perm_tile(const DevPlan& P, const int* spn, const int64_t* slv,
                                              const cx<R>* __restrict__ f0, cx<R>* __restrict__ rho, int64_t N,
                                              int64_t tile, cx<R>* tl) {
-  const int MD = P.MD, B = P.B, pnw = P.pnw;
+  const int B = P.B;
   const int64_t ntn = (N + kOutTN - 1) / kOutTN;
   const int64_t tn = tile % ntn, tk = tile / ntn;
   const int64_t n0 = tn * kOutTN;
   const int kap0 = (int)tk * kOutTK;
   constexpr int LD = kOutTK + 1;   // padded row: the column reads of the write phase spread over banks
-  const int kl = threadIdx.x % kOutTK;
-  for (int nl = threadIdx.x / kOutTK; nl < kOutTN; nl += kThreads / kOutTK) {
-    const int64_t n = n0 + nl;
-    if (n < N && kap0 + kl < B) {
-      int64_t rem = n;
-      int v[kMaxD];
-      int S = 0;
-      for (int d = MD - 1; d >= 0; --d) {
-        v[d] = (int)(rem % P.CD[d]);
-        rem /= P.CD[d];
-        S += v[d];
-      }
-      int rank = 0, sd = S;
-      for (int d = 0; d < MD; ++d) {
-        rank += pnv(spn, pnw, d + 1, sd) - pnv(spn, pnw, d + 1, sd - v[d]);
-        sd -= v[d];
-      }
-      tl[nl * LD + kl] = ld(f0 + (size_t)(slv[S] + rank) * B + kap0 + kl);
-    }
+  constexpr int STEP = kThreads / kOutTK, NE = kOutTN / STEP;
+  const int kl = threadIdx.x % kOutTK, nl0 = threadIdx.x / kOutTK;
+  // each wavefront finds the nodes of the tile's points once, a point per lane
+  const int node = out_tile_node(P, spn, slv, n0, N);
+  cx<R> in[NE];
+#pragma unroll
+  for (int e = 0; e < NE; ++e) {
+    const int nd = __shfl(node, nl0 + e * STEP);
+    const bool ok = n0 + nl0 + e * STEP < N && kap0 + kl < B;
+    in[e] = ok ? ld(f0 + (size_t)nd * B + kap0 + kl) : czero<R>();
   }
+#pragma unroll
+  for (int e = 0; e < NE; ++e) tl[(nl0 + e * STEP) * LD + kl] = in[e];
   __syncthreads();
   int bad = 0;
   const int nl = threadIdx.x % kOutTN;

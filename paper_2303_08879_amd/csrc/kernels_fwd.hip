@@ -49,11 +49,19 @@ __global__ __launch_bounds__(kThreads) void k_out_perm(DevPlan P, const cx<R>* _
     const int64_t tiles = ((N + kOutTN - 1) / kOutTN) * ((P.B + kOutTK - 1) / kOutTK);
     for (int64_t t = blockIdx.x; t < tiles; t += gridDim.x) bad |= out_perm_tile<R>(P, spn, slv, f0, rho, N, t, tl);
   } else {
-    for (int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; idx < total;
-         idx += (int64_t)gridDim.x * blockDim.x) {
-      const cx<R> v = out_perm_elem<R>(P, spn, slv, f0, N, idx);
-      if (!isfinite(v.x) || !isfinite(v.y)) bad = 1;
-      st(rho + idx, v);
+    for (int64_t i0 = (int64_t)blockIdx.x * kThreads * kOutEPT; i0 < total;
+         i0 += (int64_t)gridDim.x * kThreads * kOutEPT) {
+      cx<R> v[kOutEPT];
+#pragma unroll
+      for (int e = 0; e < kOutEPT; ++e)
+        v[e] = out_perm_elem<R>(P, spn, slv, f0, N, min(i0 + e * kThreads + threadIdx.x, total - 1));
+#pragma unroll
+      for (int e = 0; e < kOutEPT; ++e) {
+        const int64_t idx = i0 + e * kThreads + threadIdx.x;
+        if (idx >= total) break;
+        if (!isfinite(v[e].x) || !isfinite(v[e].y)) bad = 1;
+        st(rho + idx, v[e]);
+      }
     }
   }
   if (bad) atomicOr(status, 1);
@@ -258,7 +266,8 @@ static hipError_t launch_out_perm_t(const Plan& Pl, const DevPlan& P, const cx<R
   }
   const int64_t total = Pl.out_elems;
   const int64_t tiles = ((Pl.nodes_total + kOutTN - 1) / kOutTN) * ((Pl.B + kOutTK - 1) / kOutTK);
-  const int64_t grid = std::min<int64_t>(Pl.B > 1 ? tiles : (total + kThreads - 1) / kThreads, 65536);
+  const int64_t grid =
+      std::min<int64_t>(Pl.B > 1 ? tiles : (total + kThreads * kOutEPT - 1) / (kThreads * kOutEPT), 65536);
   const size_t shm = 16 * ((((size_t)(Pl.MD + 1) * (Pl.smax + 3)) * 4 + 15) / 16) +
                      16 * (((size_t)(Pl.smax + 2) * 8 + 15) / 16) + (size_t)kOutTN * (kOutTK + 1) * sizeof(cx<R>);
   KTimer kt(Pl, KK_OUT_PERM, st);

@@ -48,7 +48,7 @@ __global__ __launch_bounds__(kThreads) void k_perm_in(DevPlan P, const cx<R>* __
   for (int i = threadIdx.x; i < npn; i += blockDim.x) spn[i] = P.pn[i];
   for (int i = threadIdx.x; i <= P.smax; i += blockDim.x) slv[i] = P.MD > 0 ? P.lvl[i] : 0;
   __syncthreads();
-  const int MD = P.MD, B = P.B, pnw = P.pnw;
+  const int B = P.B;
   if (B > 1) {
     // tiles of kOutTN consecutive C-order lattice points n by kOutTK block
     // entries kappa through LDS, the inverse of the output permutation: each
@@ -65,34 +65,29 @@ __global__ __launch_bounds__(kThreads) void k_perm_in(DevPlan P, const cx<R>* __
           if (n0 + nl < N && kap0 + k < B) tl[nl * LD + k] = ld(drho + (size_t)(kap0 + k) * N + n0 + nl);
       }
       __syncthreads();
-      const int kl = threadIdx.x % kOutTK;
-      for (int nl = threadIdx.x / kOutTK; nl < kOutTN; nl += kThreads / kOutTK) {
-        const int64_t n = n0 + nl;
-        if (n < N && kap0 + kl < B) {
-          int64_t rem = n;
-          int v[kMaxD];
-          int S = 0;
-          for (int d = MD - 1; d >= 0; --d) {
-            v[d] = (int)(rem % P.CD[d]);
-            rem /= P.CD[d];
-            S += v[d];
-          }
-          int rank = 0, sd = S;
-          for (int d = 0; d < MD; ++d) {
-            rank += pnv(spn, pnw, d + 1, sd) - pnv(spn, pnw, d + 1, sd - v[d]);
-            sd -= v[d];
-          }
-          st(g0 + (size_t)(slv[S] + rank) * B + kap0 + kl, tl[nl * LD + kl]);
-        }
+      const int kl = threadIdx.x % kOutTK, nl0 = threadIdx.x / kOutTK;
+      const int node = out_tile_node(P, spn, slv, n0, N);
+#pragma unroll
+      for (int e = 0; e < kOutTN * kOutTK / kThreads; ++e) {
+        const int nl = nl0 + e * (kThreads / kOutTK), nd = __shfl(node, nl);
+        if (n0 + nl < N && kap0 + kl < B) st(g0 + (size_t)nd * B + kap0 + kl, tl[nl * LD + kl]);
       }
       __syncthreads();
     }
     return;
   }
   // one entry per node (no undetected modes): C-order index -> node order
-  for (int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; idx < total;
-       idx += (int64_t)gridDim.x * blockDim.x)
-    st(g0 + node_of_cindex(P, spn, slv, (int)idx), ld(drho + idx));
+  for (int64_t i0 = (int64_t)blockIdx.x * kThreads * kOutEPT; i0 < total;
+       i0 += (int64_t)gridDim.x * kThreads * kOutEPT) {
+    cx<R> v[kOutEPT];
+#pragma unroll
+    for (int e = 0; e < kOutEPT; ++e) v[e] = ld(drho + min(i0 + e * kThreads + threadIdx.x, total - 1));
+#pragma unroll
+    for (int e = 0; e < kOutEPT; ++e) {
+      const int64_t idx = i0 + e * kThreads + threadIdx.x;
+      if (idx < total) st(g0 + node_of_cindex(P, spn, slv, (int)idx), v[e]);
+    }
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -544,7 +539,8 @@ static hipError_t run_vjp_t(const Plan& Pl, bool odd, const void* A, const void*
   } else {
     const int64_t total = Pl.out_elems;
     const int64_t tiles = ((Pl.nodes_total + kOutTN - 1) / kOutTN) * ((Pl.B + kOutTK - 1) / kOutTK);
-    const int64_t grid = std::min<int64_t>(Pl.B > 1 ? tiles : (total + kThreads - 1) / kThreads, 65536);
+    const int64_t grid =
+        std::min<int64_t>(Pl.B > 1 ? tiles : (total + kThreads * kOutEPT - 1) / (kThreads * kOutEPT), 65536);
     const size_t shm = 16 * ((((size_t)(Pl.MD + 1) * (Pl.smax + 3)) * 4 + 15) / 16) +
                        16 * (((size_t)(Pl.smax + 2) * 8 + 15) / 16) +
                        (Pl.B > 1 ? (size_t)kOutTN * (kOutTK + 1) * sizeof(cx<R>) : 0);
