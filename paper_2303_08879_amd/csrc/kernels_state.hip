@@ -165,6 +165,13 @@ constexpr int kJvpTile = 4096, kJvpEPT = 4, kJvpThreads = kJvpTile / kJvpEPT;
 // at most 2048 of them leave 33 lanes of 64 busy at the worst cutoffs), two
 // workgroups of four wavefronts on each CU.
 constexpr int kVjpTile = 2048, kVjpGrid = 512, kVjpChunk = 8, kVjpUw = kMaxCut;
+// Items of a wavefront between two folds of its sums over the lanes (even): a
+// lane adds that many terms in a row and the folds go into a compensated sum.  One
+// chain over all 256 items of 8 modes cutoff 8 made the gradient's error 6.0e-16 and
+// 6.6e-16 on two random states where 512-entry tiles folded one by one had 3.5e-16
+// and 4.2e-16; now 2.2e-16 and 3.0e-16, in the same time (912 -> 909 us, amplitudes and
+// gradient).
+constexpr int kVjpFold = 16;
 
 struct StateTiles {
   int MD, sp, T, ntiles;
@@ -368,8 +375,7 @@ __host__ __device__ constexpr int vjp_cols(int MD) { return MD + MD * (MD + 1) /
 //   Abar_il = 1/2 sum_m u_i(m) conj(v_l(m)),   bbar_i = sum_m u_i(m) conj(psi_m),
 //   u_i(m) = sqrt(m_i + 1) g_{m+1_i},  v_l(m) = sqrt(m_l) psi_{m-1_l}
 // (zero outside the box), so an entry takes 2 MD shifted loads and scalings for
-// its MD (MD + 1) / 2 products, and the lanes keep every sum in registers: one
-// butterfly per sum and wavefront at the end.  Six to eight modes (28 to 45
+// its MD (MD + 1) / 2 products, and the lanes keep every sum in registers.  Six to eight modes (28 to 45
 // complex sums) are shared by two wavefronts: each has half of the modes as rows i and
 // takes every other pair (i, l) between the halves, as u_i v_l or u_l v_i.
 //
@@ -387,11 +393,88 @@ struct StateVjpSplit {
   static constexpr int half(int i) { return vjp_halves(MD) == 2 && i >= (MD + 1) / 2 ? 1 : 0; }
   // the mode of pair (i, l) that is the row; its half takes the pair
   static constexpr int row(int i, int l) { return half(i) != half(l) && ((i + l) & 1) ? l : i; }
+  // columns of half h (the first also has the last column), and its values:
+  // real and imaginary parts
+  static constexpr int values(int h) {
+    int n = h == 0 ? 1 : 0;
+    for (int i = 0; i < MD; ++i) {
+      if (half(i) == h) ++n;
+      for (int l = i; l < MD; ++l)
+        if (half(row(i, l)) == h) ++n;
+    }
+    return 2 * n;
+  }
+  // fn(column) for each of them, in order
+  template <int H, typename F>
+  static __device__ __forceinline__ void each(F&& fn) {
+    if (H == 0) fn(vjp_cols(MD) - 1);
+#pragma unroll
+    for (int i = 0; i < MD; ++i) {
+      if (half(i) == H) fn(i);
+#pragma unroll
+      for (int l = i; l < MD; ++l)
+        if (half(row(i, l)) == H) fn(vjp_col_pair(MD, i, l));
+    }
+  }
 };
-template <int MD>
-struct StateVjpSums {
-  double x[vjp_cols(MD)], y[vjp_cols(MD)];
-};
+
+// Sums of N <= 64 values over the lanes of a wavefront.  A step takes values j and
+// j + H, H = (N + 1) / 2, of two lanes that differ in one bit: the lane without the
+// bit ends with the sum of value j, the other with that of value j + H, so the
+// steps halve the number of values (46: 47 exchanges and additions, a butterfly of
+// each value 276).  At the end a lane holds one value, fold_index of them.
+template <int BIT>
+__device__ __forceinline__ double fold_pair(double a, double c) {
+  if constexpr (BIT >= 16) {
+    // v_permlane32_swap / v_permlane16_swap exchange the upper half (odd rows) of
+    // a with the lower half (even rows) of c
+    typedef unsigned int u2 __attribute__((ext_vector_type(2)));
+    const u2 ua = __builtin_bit_cast(u2, a), uc = __builtin_bit_cast(u2, c);
+    u2 lo, hi;
+    if constexpr (BIT == 32) {
+      lo = __builtin_amdgcn_permlane32_swap(ua.x, uc.x, false, false);
+      hi = __builtin_amdgcn_permlane32_swap(ua.y, uc.y, false, false);
+    } else {
+      lo = __builtin_amdgcn_permlane16_swap(ua.x, uc.x, false, false);
+      hi = __builtin_amdgcn_permlane16_swap(ua.y, uc.y, false, false);
+    }
+    return __builtin_bit_cast(double, u2{lo.x, hi.x}) + __builtin_bit_cast(double, u2{lo.y, hi.y});
+  } else {
+    const bool up = (threadIdx.x & BIT) != 0;
+    const double keep = up ? c : a, send = up ? a : c;
+    // the partner by a data-parallel move: row mirror, half-row mirror, quad swaps
+    constexpr int kMove = BIT == 8 ? 0x140 : BIT == 4 ? 0x141 : BIT == 2 ? 0x4e : 0xb1;
+    typedef int i2 __attribute__((ext_vector_type(2)));
+    const i2 w = __builtin_bit_cast(i2, send);
+    const i2 from = {__builtin_amdgcn_update_dpp(0, w.x, kMove, 0xf, 0xf, true),
+                     __builtin_amdgcn_update_dpp(0, w.y, kMove, 0xf, 0xf, true)};
+    return keep + __builtin_bit_cast(double, from);
+  }
+}
+template <int N, int BIT = 32, int NV>
+__device__ __forceinline__ double fold_lanes(double (&v)[NV]) {
+  if constexpr (BIT == 0) {
+    static_assert(N == 1, "at most 64 values");
+    return v[0];
+  } else {
+    constexpr int H = (N + 1) / 2;
+#pragma unroll
+    for (int j = 0; j < H; ++j) v[j] = fold_pair<BIT>(v[j], j + H < N ? v[j + H] : 0.0);
+    return fold_lanes<H, BIT / 2>(v);
+  }
+}
+// The value that this lane holds after fold_lanes<N>, -1: none.
+template <int N, int BIT = 32>
+__device__ __forceinline__ int fold_index(int lane) {
+  if constexpr (BIT == 0) {
+    return 0;
+  } else {
+    constexpr int H = (N + 1) / 2;
+    const int i = fold_index<H, BIT / 2>(lane);
+    const int j = i + ((lane & BIT) ? H : 0);
+    return i < 0 || j >= N ? -1 : j;
+  }
+}
 __device__ __forceinline__ void add_conj(double& sx, double& sy, double ux, double uy, double vx, double vy) {
   sx += ux * vx + uy * vy;
   sy += uy * vx - ux * vy;
@@ -411,7 +494,8 @@ struct StateVjpRaw {
   bool live;
   cx<R> pv[MD > 0 ? MD : 1], p0;
 };
-// A wavefront's sums over its items.  The next item's loads of psi are issued
+// A wavefront's sums over its items, folded over its lanes every kVjpFold items
+// (into the lane's `sum` in LDS: value fold_index of the half's columns).  The next item's loads of psi are issued
 // before an item's products, those of row i of g after the products of row i (in the
 // same registers).  Where an entry lacks one factor of a product, its weight is
 // zero; EXACT leaves the product out instead (the value may not be finite).
@@ -419,13 +503,17 @@ struct StateVjpRaw {
 template <int MD, int HALF, bool EXACT, typename R>
 __device__ __forceinline__ void state_vjp_sums(const StateTiles& G, const cx<R>* __restrict__ psi,
                                                const cx<R>* __restrict__ g, const double* sq, const uint64_t* kp,
-                                               const StateVjpItems& I, StateVjpSums<MD>& Z) {
+                                               const StateVjpItems& I, double2* sum) {
   typedef StateVjpSplit<MD> W;
-  constexpr int MDA = MD > 0 ? MD : 1, NG = kThreads / 64 / vjp_halves(MD);
+  constexpr int MDA = MD > 0 ? MD : 1, NG = kThreads / 64 / vjp_halves(MD), NV = W::values(HALF);
   const int lane = threadIdx.x & 63, ept = (G.T + 63) >> 6;
   const double* su = sq + kMaxCut + 1;
+  struct {
+    double x[vjp_cols(MD)], y[vjp_cols(MD)];
+  } Z;
 #pragma unroll
   for (int p = 0; p < vjp_cols(MD); ++p) Z.x[p] = Z.y[p] = 0.0;
+  *sum = make_double2(0.0, 0.0);
   // lane d finds leading digit d of an item's tile
   int dst = 1, dc = 1;
   double dis = 1.0, dic = 1.0;
@@ -500,6 +588,23 @@ __device__ __forceinline__ void state_vjp_sums(const StateTiles& G, const cx<R>*
       __builtin_amdgcn_sched_barrier(0);
     }
   };
+  // the lanes' sums since the last fold into sum->x (Knuth's two-sum: sum->y
+  // collects what the additions round away)
+  auto fold = [&]() {
+    __builtin_amdgcn_sched_barrier(0);
+    double v[NV];
+    int n = 0;
+    W::template each<HALF>([&](int p) {
+      v[n++] = Z.x[p];
+      v[n++] = Z.y[p];
+      Z.x[p] = Z.y[p] = 0.0;
+    });
+    const double t = fold_lanes<NV>(v);
+    const double2 a = *sum;
+    const double s = a.x + t, b = s - a.x;
+    *sum = make_double2(s, a.y + ((a.x - (s - b)) + (t - b)));
+    __builtin_amdgcn_sched_barrier(0);
+  };
   int c = I.c0, j = I.j;
   // the next item of this wavefront, -1 after the last
   auto next = [&]() -> int {
@@ -517,50 +622,39 @@ __device__ __forceinline__ void state_vjp_sums(const StateTiles& G, const cx<R>*
   if (q < 0) return;
   fetch(q, ra);
   fetch_rows(ra);
-  for (;;) {
+  for (int left = kVjpFold / 2;; --left) {
+    if (left == 0) {
+      fold();
+      left = kVjpFold / 2;
+    }
     const int qb = next();
     fetch(qb >= 0 ? qb : q, rb);
     add(ra, rb);
-    if (qb < 0) return;
+    if (qb < 0) break;
     q = next();
     fetch(q >= 0 ? q : qb, ra);
     add(rb, ra);
-    if (q < 0) return;
+    if (q < 0) break;
   }
+  fold();
 }
 
-// The sums of one wavefront, folded over its lanes, into red (its row of columns).
+// The sums of one wavefront into red (its row of columns).
 template <int MD, int HALF, typename R>
 __device__ __forceinline__ void state_vjp_wave(const StateTiles& G, const cx<R>* __restrict__ psi,
                                                const cx<R>* __restrict__ g, const double* sq, const uint64_t* kp,
-                                               const StateVjpItems& I, double2* red) {
+                                               const StateVjpItems& I, double2* sums, double2* red) {
   typedef StateVjpSplit<MD> W;
-  constexpr int NC = vjp_cols(MD);
-  StateVjpSums<MD> Z;
-  state_vjp_sums<MD, HALF, false, R>(G, psi, g, sq, kp, I, Z);
-  auto each = [&](auto&& fn) {   // the columns this half takes
-    if (HALF == 0) fn(NC - 1);
-#pragma unroll
-    for (int i = 0; i < MD; ++i) {
-      if (W::half(i) == HALF) fn(i);
-#pragma unroll
-      for (int l = i; l < MD; ++l)
-        if (W::half(W::row(i, l)) == HALF) fn(vjp_col_pair(MD, i, l));
-    }
-  };
-  bool bad = false;
-  each([&](int p) { bad = bad || !(fabs(Z.x[p]) + fabs(Z.y[p]) < __builtin_inf()); });
-  if (__ballot(bad) != 0ull) state_vjp_sums<MD, HALF, true, R>(G, psi, g, sq, kp, I, Z);
-  each([&](int p) {
-    double x = Z.x[p], y = Z.y[p];
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-      x += __shfl_xor(x, o);
-      y += __shfl_xor(y, o);
-    }
-    const double h = p >= MD && p < NC - 1 ? 0.5 : 1.0;
-    if ((threadIdx.x & 63) == 0) red[p] = make_double2(h * x, h * y);
-  });
+  constexpr int NC = vjp_cols(MD), NV = W::values(HALF);
+  double2* own = sums + threadIdx.x;
+  state_vjp_sums<MD, HALF, false, R>(G, psi, g, sq, kp, I, own);
+  if (__ballot(!(fabs(own->x) < __builtin_inf())) != 0ull) state_vjp_sums<MD, HALF, true, R>(G, psi, g, sq, kp, I, own);
+  const double sum = own->x + (fabs(own->x) < __builtin_inf() ? own->y : 0.0);
+  // this lane's value: real or imaginary part of its column
+  const int v = fold_index<NV>(threadIdx.x & 63);
+  int n = 0, col = 0;
+  W::template each<HALF>([&](int p) { col = (v >> 1) == n++ ? p : col; });
+  if (v >= 0) reinterpret_cast<double*>(red + col)[v & 1] = (col >= MD && col < NC - 1 ? 0.5 : 1.0) * sum;
 }
 
 // Persistent workgroups (a multiple of 8): workgroup v runs on XCD v mod 8,
@@ -574,7 +668,7 @@ __global__ __launch_bounds__(kThreads, 2) void k_state_vjp(StateTiles G, const c
   constexpr int NC = vjp_cols(MD), NW = kThreads / 64, NG = NW / vjp_halves(MD);
   __shared__ uint64_t kp[kVjpTile];        // trailing digits of a tile's entries, 8 bits per mode
   __shared__ double sq[kMaxCut + 1 + (MD > 0 ? MD : 1) * kVjpUw];
-  __shared__ double2 red[NW * NC];
+  __shared__ double2 red[NW * NC], sums[kThreads];
   for (int v = threadIdx.x; v <= kMaxCut; v += kThreads) sq[v] = sqrt((double)v);
 #pragma unroll
   for (int d = 0; d < MD; ++d)
@@ -595,9 +689,9 @@ __global__ __launch_bounds__(kThreads, 2) void k_state_vjp(StateTiles G, const c
   const StateVjpItems I{xcd * per + (int)(blockIdx.x >> 3), min((xcd + 1) * per, chunks), (int)(gridDim.x >> 3),
                         wave / vjp_halves(MD), items};
   if (vjp_halves(MD) == 1 || (wave & 1) == 0)
-    state_vjp_wave<MD, 0, R>(G, psi, g, sq, kp, I, red + wave * NC);
+    state_vjp_wave<MD, 0, R>(G, psi, g, sq, kp, I, sums, red + wave * NC);
   else
-    state_vjp_wave<MD, vjp_halves(MD) - 1, R>(G, psi, g, sq, kp, I, red + wave * NC);
+    state_vjp_wave<MD, vjp_halves(MD) - 1, R>(G, psi, g, sq, kp, I, sums, red + wave * NC);
   __syncthreads();
   for (int p = threadIdx.x; p < NC; p += kThreads) {
     double sx = 0.0, sy = 0.0;
