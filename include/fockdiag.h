@@ -270,7 +270,9 @@ fd_status detection_probs(fd_plan p, const void* A, const void* b, const void* c
  * Results equal fock_diag_fwd's bit for bit.  The library keeps the work-item
  * table and per-circuit descriptors of the last 8 (plan set, pointer set)
  * combinations in device memory (freed with the plans); two batched calls
- * with the same plans and pointers must not overlap in time. */
+ * with the same plans and pointers must not overlap in time.  While the caller
+ * captures `stream` the classes run one after the other on it, and the tables
+ * that the captured launches read stay until one of the plans is destroyed. */
 fd_status fock_diag_fwd_batch(int n, const fd_plan* plans, const void* const* A,
                               const void* const* b, const void* const* c, void* const* rho,
                               void* const* workspace, const size_t* ws_bytes, hipStream_t stream);

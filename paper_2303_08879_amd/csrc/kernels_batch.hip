@@ -106,6 +106,7 @@ struct BatchClass {
 
 struct BatchSched {
   uint64_t id = 0;                      // unique per built schedule
+  bool pinned = false;                  // a caller's captured graph reads its tables: kept as long as the plans
   int device = -1;
   std::vector<uint64_t> key;
   std::vector<uint64_t> uids;
@@ -483,9 +484,11 @@ fd_status sweep_sched(int n, Plan* const* plans, const bool* odd, const void* co
   const fd_status bs = plans[0]->dt == FD_C64 ? build_sched<float>(n, plans, odd, A, b, c, rho, ws, st, &ns, err)
                                               : build_sched<double>(n, plans, odd, A, b, c, rho, ws, st, &ns, err);
   if (bs != FD_OK) return bs;
-  if (g_cache.size() >= kBatchCache) {
-    auto it = std::min_element(g_cache.begin(), g_cache.end(),
-                               [](const BatchSched& x, const BatchSched& y) { return x.last_use < y.last_use; });
+  if (std::count_if(g_cache.begin(), g_cache.end(), [](const BatchSched& x) { return !x.pinned; }) >=
+      (std::ptrdiff_t)kBatchCache) {
+    auto it = std::min_element(g_cache.begin(), g_cache.end(), [](const BatchSched& x, const BatchSched& y) {
+      return x.pinned != y.pinned ? y.pinned : x.last_use < y.last_use;
+    });
     drop_sched(*it);
     g_cache.erase(it);
   }
@@ -511,11 +514,13 @@ Split split_batch(int n, Plan* const* plans, const fd_batch_tuning& T) {
 // their classes on the side streams while `st` runs the level launches of the
 // circuits that fill the device (or that the batched kernels do not take), then
 // the permutation.  `st` waits for the side streams before it goes on, so
-// everything the call touches is ordered on `st`.
+// everything the call touches is ordered on `st`.  Without `fork` everything
+// runs on `st`: a stream that the caller captures would draw the side streams into
+// its capture, and every other batched call that then used them would fail.
 template <typename R>
 hipError_t enqueue_batch_t(const Split& sp, Plan* const* plans, const bool* odd, const void* const* A,
                            const void* const* b, const void* const* c, void* const* rho, void* const* ws,
-                           const BatchSched* S, hipStream_t st) {
+                           const BatchSched* S, bool fork, hipStream_t st) {
   hipError_t e = hipSuccess;
   auto big = [&]() -> hipError_t {
     for (int i : sp.big) {
@@ -528,6 +533,15 @@ hipError_t enqueue_batch_t(const Split& sp, Plan* const* plans, const bool* odd,
   const int n = (int)sp.small.size();
   const Plan& P0 = *plans[sp.small[0]];
   if ((e = launch_batch_prep<R>(*S, n, P0, st)) != hipSuccess) return e;
+  if (!fork) {
+    {
+      KTimer kt(P0, KK_BATCH_SWEEP, st);
+      if ((e = big()) != hipSuccess) return e;
+      for (int k = 0; k < kBatchLanes; ++k)
+        if ((e = launch_lane<R>(*S, k, st)) != hipSuccess) return e;
+    }
+    return launch_batch_out<R>(*S, n, P0, st);
+  }
   BatchLanes* L = nullptr;
   if ((e = batch_lanes(S->device, &L)) != hipSuccess) return e;
   bool used[kBatchLanes] = {};
@@ -558,10 +572,10 @@ hipError_t enqueue_batch_t(const Split& sp, Plan* const* plans, const bool* odd,
 
 hipError_t enqueue_batch(const Split& sp, Plan* const* plans, const bool* odd, const void* const* A,
                          const void* const* b, const void* const* c, void* const* rho, void* const* ws,
-                         const BatchSched* S, hipStream_t st) {
+                         const BatchSched* S, bool fork, hipStream_t st) {
   const bool c64 = !sp.small.empty() && plans[sp.small[0]]->dt == FD_C64;
-  return c64 ? enqueue_batch_t<float>(sp, plans, odd, A, b, c, rho, ws, S, st)
-             : enqueue_batch_t<double>(sp, plans, odd, A, b, c, rho, ws, S, st);
+  return c64 ? enqueue_batch_t<float>(sp, plans, odd, A, b, c, rho, ws, S, fork, st)
+             : enqueue_batch_t<double>(sp, plans, odd, A, b, c, rho, ws, S, fork, st);
 }
 
 }  // namespace
@@ -589,14 +603,8 @@ fd_status run_forward_batch(int n, Plan* const* plans, const bool* odd, const vo
     r2[k] = rho[i];
     w2[k] = ws[i];
   }
-  BatchSched* S = nullptr;
-  if (m > 0) {
-    const fd_status s = sweep_sched((int)m, p2.data(), o2.get(), A2.data(), b2.data(), c2.data(), r2.data(),
-                                    w2.data(), T, st, &S, err);
-    if (s != FD_OK) return s;
-  }
-  bool timing = false;
-  for (int i = 0; i < n; ++i) timing = timing || plans[i]->timing.mask != 0;
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  const bool captured_by_caller = hipStreamIsCapturing(st, &cap) == hipSuccess && cap != hipStreamCaptureStatusNone;
   auto fail_hip = [&](hipError_t e) {
     *err = std::string("kernel launch failed: ") + hipGetErrorString(e);
     return FD_ERR_HIP;
@@ -604,8 +612,31 @@ fd_status run_forward_batch(int n, Plan* const* plans, const bool* odd, const vo
   int dev = 0;
   (void)hipGetDevice(&dev);
   if (dev < 0 || dev >= 64) return fail_hip(hipErrorInvalidDevice);
+  BatchSched* S = nullptr;
+  if (m > 0) {
+    // an upload captured by the caller would not have run when the next call
+    // finds the schedule: it goes to a side stream and is waited for
+    hipStream_t up = st;
+    BatchLanes* L = nullptr;
+    if (captured_by_caller) {
+      const hipError_t e = batch_lanes(dev, &L);
+      if (e != hipSuccess) return fail_hip(e);
+      up = L->s[0];
+    }
+    const uint64_t built = g_sched_id;
+    const fd_status s = sweep_sched((int)m, p2.data(), o2.get(), A2.data(), b2.data(), c2.data(), r2.data(),
+                                    w2.data(), T, up, &S, err);
+    if (s != FD_OK) return s;
+    if (captured_by_caller && g_sched_id != built) {
+      const hipError_t e = hipStreamSynchronize(up);
+      if (e != hipSuccess) return fail_hip(e);
+    }
+    S->pinned = S->pinned || captured_by_caller;
+  }
+  bool timing = false;
+  for (int i = 0; i < n; ++i) timing = timing || plans[i]->timing.mask != 0;
   if (T.use_graph <= 0 || g_graph_failed || timing) {
-    const hipError_t e = enqueue_batch(sp, plans, odd, A, b, c, rho, ws, S, st);
+    const hipError_t e = enqueue_batch(sp, plans, odd, A, b, c, rho, ws, S, !captured_by_caller, st);
     return e == hipSuccess ? FD_OK : fail_hip(e);
   }
   std::vector<uint64_t> key = batch_key(n, plans, odd, A, b, c, rho, ws, T);
@@ -623,7 +654,7 @@ fd_status run_forward_batch(int n, Plan* const* plans, const bool* odd, const vo
   hipGraphExec_t exec = nullptr;
   bool captured = false;
   if (hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal) == hipSuccess) {
-    const hipError_t eb = enqueue_batch(sp, plans, odd, A, b, c, rho, ws, S, cs);
+    const hipError_t eb = enqueue_batch(sp, plans, odd, A, b, c, rho, ws, S, true, cs);
     const hipError_t ee = hipStreamEndCapture(cs, &graph);
     captured = eb == hipSuccess && ee == hipSuccess && graph &&
                hipGraphInstantiate(&exec, graph, nullptr, nullptr, 0) == hipSuccess;
@@ -634,7 +665,7 @@ fd_status run_forward_batch(int n, Plan* const* plans, const bool* odd, const vo
     if (exec) (void)hipGraphExecDestroy(exec);
     if (graph) (void)hipGraphDestroy(graph);
     g_graph_failed = true;
-    e = enqueue_batch(sp, plans, odd, A, b, c, rho, ws, S, st);
+    e = enqueue_batch(sp, plans, odd, A, b, c, rho, ws, S, !captured_by_caller, st);
     return e == hipSuccess ? FD_OK : fail_hip(e);
   }
   if (g_graphs.size() >= kBatchCache) {
