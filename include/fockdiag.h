@@ -114,7 +114,12 @@ fd_status fd_plan_destroy(fd_plan p);
  *                 intermediate amplitude for the reverse sweep, *fwd_bytes =
  *                 workspace of both fock_diag_fwd (with saved) and
  *                 fock_diag_vjp (with saved).  fock_diag_vjp with saved ==
- *                 NULL needs fwd_bytes + saved_bytes of workspace. */
+ *                 NULL needs fwd_bytes + saved_bytes of workspace.
+ * Beside these buffers a plan keeps tables of its own in device memory from its
+ * first call on: some KB (plans with undetected modes 96 bytes per lattice
+ * point), and with every mode detected and at most 2^25 lattice points a digit
+ * table of 8 bytes per point (FD_Q_TABLE_BYTES; eight modes of cutoff 8: 134 MB;
+ * see fd_plan_use_digit_table). */
 fd_status fd_plan_workspace(fd_plan p, int with_vjp, size_t* fwd_bytes, size_t* saved_bytes);
 
 /* fd_plan_set_checkpoint -- memory of the reverse sweep.  Sec. 2.5's
@@ -151,6 +156,17 @@ fd_status fd_plan_set_checkpoint(fd_plan p, int every);
  * not hold every amplitude).  Drops the plan's captured graphs. */
 fd_status fd_plan_set_write_counters(fd_plan p, unsigned int* counters, size_t n);
 
+/* fd_plan_use_digit_table -- whether the plan keeps a digit table (default: 1).
+ * The table holds the photon numbers of every lattice point of a plan with every
+ * mode detected, so that the level kernels need not derive them from the point's
+ * rank (eight modes of cutoff 8: 7110 -> 6717 us per forward + reverse step).
+ * Plans of the same detected cutoffs and total cutoff share one table per
+ * device; it is freed with the last of them, and all tables together take at most
+ * 1 GiB of a device, beyond which further plans do without.  Amplitudes are
+ * the same bit for bit either way.  enable = 0 gives the plan's table back (plans small
+ * enough for one workgroup then run level by level).  Drops the plan's captured graphs. */
+fd_status fd_plan_use_digit_table(fd_plan p, int enable);
+
 /* fd_plan_query -- integer facts about the plan (host only, for tests and
  * reports).  `what`: see FD_Q_* below. */
 enum {
@@ -166,7 +182,8 @@ enum {
   FD_Q_NODES_F2 = 9,       /* type-2 offset nodes                               */
   FD_Q_NODES_F1010 = 10,   /* type-1010 offset nodes                            */
   FD_Q_NODES_F1001 = 11,   /* type-1001 offset nodes                            */
-  FD_Q_B_SCHEDULE = 12     /* 1 if the plan will use the b = 0 schedule         */
+  FD_Q_B_SCHEDULE = 12,    /* 1 if the plan will use the b = 0 schedule         */
+  FD_Q_TABLE_BYTES = 13    /* device bytes of the plan's digit table (0: none)  */
 };
 fd_status fd_plan_query(fd_plan p, int what, int64_t* out);
 

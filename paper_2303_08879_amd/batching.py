@@ -17,6 +17,9 @@ import torch
 from . import fockdiag as F
 
 
+MAX_TABLE_BYTES = 1 << 30   # all digit tables of the library on a device
+
+
 def _al(x, a=256):
     return (int(x) + a - 1) // a * a
 
@@ -34,7 +37,11 @@ class BatchRunner:
         if budget_bytes is None:
             free, _ = torch.cuda.mem_get_info()
             budget_bytes = int(0.6 * free)
-        budget_bytes = max(int(budget_bytes), max(need))
+        # the digit tables of the plans with every mode detected stay for all
+        # groups (one per set of cutoffs, see fd_plan_use_digit_table)
+        self.table_bytes = sum({tuple(c for c in p.cutoffs if c > 1): p.query(F.FD_Q_TABLE_BYTES)
+                                for p in self.plans}.values())
+        budget_bytes = max(int(budget_bytes) - min(self.table_bytes, MAX_TABLE_BYTES), max(need))
         order = sorted(range(len(need)), key=lambda i: -need[i])
         self.groups, load = [], []
         for i in order:

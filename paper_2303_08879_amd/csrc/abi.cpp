@@ -178,7 +178,7 @@ fd_status fd_plan_destroy(fd_plan p) {
     (void)hipFree(P.d_woff);
     (void)hipFree(P.d_node);
     (void)hipFree(P.d_sqt);
-    (void)hipFree(P.d_mtab);
+    fd::give_digit_table(&P);
     (void)hipFree(P.d_mass);
     (void)hipSetDevice(cur);
   }
@@ -214,6 +214,28 @@ fd_status fd_plan_set_checkpoint(fd_plan p, int every) {
   fd::Plan& P = p->P;
   if (P.ckpt != every) drop_graphs(P);
   P.ckpt = every;
+  return ok();
+}
+
+fd_status fd_plan_use_digit_table(fd_plan p, int enable) {
+  if (!p) return fail(FD_ERR_INVALID_ARG, "plan is NULL");
+  fd::Plan& P = p->P;
+  if (P.digit_table == (enable != 0)) return ok();
+  // graphs and batch schedules hold the table's address
+  drop_graphs(P);
+  fd::batch_forget(P.uid);
+  P.digit_table = enable != 0;
+  fd::plan_small(&P);
+  if (!enable) {
+    fd::give_digit_table(&P);
+  } else if (P.d_pn) {
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess) return fail(FD_ERR_HIP, "hipGetDevice failed");
+    if (dev != P.device) return fail(FD_ERR_INVALID_ARG, "plan was initialised on another device");
+    std::string err;
+    const fd_status s = fd::take_digit_table(&P, &err);
+    if (s != FD_OK) return fail(s, err);
+  }
   return ok();
 }
 
@@ -258,6 +280,7 @@ fd_status fd_plan_query(fd_plan p, int what, int64_t* out) {
     case FD_Q_NODES_F2: *out = P.stored[fd::F_F2]; break;
     case FD_Q_NODES_F1010: *out = P.stored[fd::F_1010]; break;
     case FD_Q_NODES_F1001: *out = P.stored[fd::F_1001]; break;
+    case FD_Q_TABLE_BYTES: *out = (int64_t)fd::digit_table_bytes(P); break;
     case FD_Q_B_SCHEDULE: *out = P.flags == FD_B_ZERO ? 1 : 0; break;
     default: return fail(FD_ERR_INVALID_ARG, "unknown query");
   }
@@ -565,6 +588,7 @@ fd_status fd_state_plan_create(int M, const int* cutoffs, fd_dtype dt, uint32_t 
     return s;
   }
   sp->inner->P.digit_table = false;
+  fd::plan_small(&sp->inner->P);
   *out = sp;
   return ok();
 }

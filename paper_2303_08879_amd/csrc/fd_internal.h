@@ -55,6 +55,7 @@ constexpr int kFwdChunk = 448;           // own entries of one of its (lattice p
 constexpr int kFwdChunkSmall = 192;      // on levels with fewer than kSmallLevelUnits units
 constexpr int kNodeStride = 3 * kMaxD;   // ints per node record: m, rank(m - 1_j), rank(m + 1_j)
 constexpr int64_t kMaxDigitTable = 1 << 25;   // lattice points with a digit table (8 bytes each)
+constexpr size_t kDigitTableBudget = size_t(1) << 30;   // bytes of all digit tables on a device
 // Points of a level from which the reverse point kernel ranks 64 points per
 // wavefront (a quarter of the rank work) instead of 16 (four times the
 // wavefronts).  Eight modes: 71 thousand points 30 against 28 us, 143 thousand 41
@@ -169,7 +170,9 @@ struct Plan {
   int64_t* d_lvl = nullptr;
   int* d_node = nullptr;             // node records (Algorithm 2 plans)
   void* d_sqt = nullptr;             // square-root tables
-  uint64_t* d_mtab = nullptr;        // digits of every lattice point in node order (Algorithm 1 plans of at most kMaxDigitTable points)
+  // digits of every lattice point in node order (Algorithm 1 plans of at most
+  // kMaxDigitTable points), shared by the plans of a lattice
+  uint64_t* d_mtab = nullptr;
   double* d_mass = nullptr;          // per-level probability masses (stopping rule)
   int* d_status = nullptr;
   // undetected-block fill order (step 1 of Algorithm 2): entries sorted by weight
@@ -191,7 +194,9 @@ struct Plan {
   // blocks whose rows do not fit the LDS staging stream them from HBM, per
   // kernel: forward block units, block fill, reverse block units, reverse fill
   bool st_fwd = false, st_ufill = false, st_vjp = false, st_ufill_vjp = false;
-  bool digit_table = true;     // whether the plan's kernels read d_mtab (state vectors unrank: 308 us of levels without, 286 with it and 148 to fill it, 8 modes cutoff 8)
+  // whether the plan's kernels read d_mtab (state vectors unrank: 308 us of
+  // levels without, 286 with it and 148 to fill it, 8 modes cutoff 8)
+  bool digit_table = true;
   bool small_fwd = false, small_vjp = false;   // sweeps in one workgroup (see kSmallFwdItems)
   bool vjp_short = false;            // shorter row chunks of the block reverse kernel (LDS)
   bool odd_for(bool b_zero) const { return !b_zero || MU > 0; }
@@ -232,6 +237,11 @@ inline size_t ufill_jvp_lds_bytes(const Plan& P) {
 fd_status build_plan(int M, const int* cutoffs, uint32_t mask, fd_dtype dt, uint32_t flags, Plan* P,
                      std::string* err, int level_cap = -1);
 fd_status ensure_device(Plan* P, std::string* err);
+void plan_small(Plan* P);
+size_t digit_table_bytes(const Plan& P);   // of the plan's digit table, 0: it uses none
+// The plan's digit table on the current device, and giving it back.
+fd_status take_digit_table(Plan* P, std::string* err);
+void give_digit_table(Plan* P);
 DevPlan make_devplan(const Plan& P, bool odd);
 
 // Workspace layouts (byte offsets from the start of the buffer).

@@ -7,6 +7,7 @@
 #include <cstdlib>
 #include <atomic>
 #include <cstring>
+#include <mutex>
 
 #include "fd_internal.h"
 
@@ -313,18 +314,27 @@ fd_status build_plan(int M, const int* cutoffs, uint32_t mask, fd_dtype dt, uint
     P->st_vjp = P->MD > 0 && vjp_lds_bytes(*P) > kMaxLds;
     P->st_ufill_vjp = ufill_lds_bytes(*P, true) > kMaxLds;
   }
+  plan_small(P);
+  P->targets = -1;
+  P->terms = -1;
+  return FD_OK;
+}
+
+// Plans whose sweeps run in one workgroup; their kernels read the digit table.
+void plan_small(Plan* P) {
   int64_t most = 0;   // items of the largest level
   for (int S = 0; S <= P->smax; ++S) {
     int64_t items = 0;
     for (int K = 0; K < P->MD; ++K) items += (P->ncnt[(size_t)K * (P->smax + 1) + S] + 15) / 16;
     most = std::max(most, items);
   }
-  const bool points = P->B == 1 && P->MD > 0 && P->nodes_total <= kMaxDigitTable;
-  P->small_fwd = points && most <= kSmallFwdItems;
-  P->small_vjp = points && most <= kSmallVjpItems;
-  P->targets = -1;
-  P->terms = -1;
-  return FD_OK;
+  const bool table = digit_table_bytes(*P) > 0;
+  P->small_fwd = table && most <= kSmallFwdItems;
+  P->small_vjp = table && most <= kSmallVjpItems;
+}
+
+size_t digit_table_bytes(const Plan& P) {
+  return P.digit_table && P.MD > 0 && P.B == 1 && P.nodes_total <= kMaxDigitTable ? (size_t)P.nodes_total * 8 : 0;
 }
 
 DevPlan make_devplan(const Plan& P, bool odd) {
@@ -639,6 +649,75 @@ static bool build_node_table(const Plan& P, std::vector<int>* out, std::string* 
 // never bring a plan to a device).
 __attribute__((weak)) hipError_t fill_digit_table(const Plan& P);
 
+// Digit tables on a device, one for all plans of the same detected cutoffs and
+// level cap (whatever their precision and flags), freed with the last of them.
+// Together they take at most kDigitTableBudget bytes of a device; a plan beyond
+// that does without (its level kernels unrank each point), except where its
+// sweeps run in one workgroup, which takes some ten KB.
+namespace {
+struct DigitTable {
+  int device, cap;
+  std::vector<int> CD;
+  uint64_t* ptr;
+  size_t bytes;
+  int users;
+};
+std::mutex g_table_mu;
+std::vector<DigitTable> g_tables;
+}  // namespace
+
+fd_status take_digit_table(Plan* P, std::string* err) {
+  const size_t bytes = digit_table_bytes(*P);
+  if (bytes == 0 || P->d_mtab || !fill_digit_table) return FD_OK;
+  int dev = 0;
+  if (hipGetDevice(&dev) != hipSuccess) {
+    *err = "hipGetDevice failed";
+    return FD_ERR_HIP;
+  }
+  const bool needed = P->small_fwd || P->small_vjp;
+  std::lock_guard<std::mutex> lock(g_table_mu);
+  size_t held = 0;
+  for (DigitTable& t : g_tables) {
+    if (t.device != dev) continue;
+    if (t.cap == P->level_cap && t.CD == P->CD) {
+      ++t.users;
+      P->d_mtab = t.ptr;
+      return FD_OK;
+    }
+    held += t.bytes;
+  }
+  if (!needed && held + bytes > kDigitTableBudget) return FD_OK;
+  if (hipMalloc((void**)&P->d_mtab, bytes) != hipSuccess) {
+    (void)hipGetLastError();
+    P->d_mtab = nullptr;
+    if (!needed) return FD_OK;
+    *err = "hipMalloc of the digit table failed";
+    return FD_ERR_OOM;
+  }
+  if (fill_digit_table(*P) != hipSuccess) {
+    (void)hipFree(P->d_mtab);
+    P->d_mtab = nullptr;
+    *err = "filling the digit table failed";
+    return FD_ERR_HIP;
+  }
+  g_tables.push_back({dev, P->level_cap, P->CD, P->d_mtab, bytes, 1});
+  return FD_OK;
+}
+
+void give_digit_table(Plan* P) {
+  if (!P->d_mtab) return;
+  std::lock_guard<std::mutex> lock(g_table_mu);
+  for (size_t i = 0; i < g_tables.size(); ++i) {
+    if (g_tables[i].ptr != P->d_mtab) continue;
+    if (--g_tables[i].users == 0) {
+      (void)hipFree(g_tables[i].ptr);   // waits for the kernels that read it
+      g_tables.erase(g_tables.begin() + i);
+    }
+    break;
+  }
+  P->d_mtab = nullptr;
+}
+
 fd_status ensure_device(Plan* P, std::string* err) {
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess) {
@@ -689,21 +768,8 @@ fd_status ensure_device(Plan* P, std::string* err) {
       return FD_ERR_HIP;
     }
   }
-  if (P->digit_table && P->MD > 0 && P->B == 1 && P->nodes_total <= kMaxDigitTable && fill_digit_table) {
-    // Without room for it the level kernels unrank each point instead (the
-    // one-workgroup sweeps, whose plans have a few thousand points, need it).
-    if (hipMalloc((void**)&P->d_mtab, (size_t)P->nodes_total * 8) != hipSuccess) {
-      (void)hipGetLastError();
-      P->d_mtab = nullptr;
-      if (P->small_fwd || P->small_vjp) {
-        *err = "hipMalloc of the digit table failed";
-        return FD_ERR_OOM;
-      }
-    } else if (fill_digit_table(*P) != hipSuccess) {
-      *err = "filling the digit table failed";
-      return FD_ERR_HIP;
-    }
-  }
+  const fd_status ts = take_digit_table(P, err);
+  if (ts != FD_OK) return ts;
   if (P->MD > 0 && P->B == 1 &&
       hipMalloc((void**)&P->d_mass, (size_t)(P->smax + 1) * kMassParts * sizeof(double)) != hipSuccess) {
     *err = "hipMalloc of the level masses failed";

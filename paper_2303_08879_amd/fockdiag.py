@@ -21,7 +21,8 @@ FD_OK, FD_ERR_INVALID_ARG, FD_ERR_UNSUPPORTED, FD_ERR_WORKSPACE, FD_ERR_OOM, FD_
 FD_C128, FD_C64 = 0, 1
 FD_B_AUTO, FD_B_ZERO, FD_B_GENERAL = 0, 1, 2
 (FD_Q_OUT_ELEMS, FD_Q_LEVELS, FD_Q_PIVOTS, FD_Q_STORED_NODES, FD_Q_TARGETS, FD_Q_READ_TERMS, FD_Q_BLOCK,
- FD_Q_NODES_F0, FD_Q_NODES_F1, FD_Q_NODES_F2, FD_Q_NODES_F1010, FD_Q_NODES_F1001, FD_Q_B_SCHEDULE) = range(13)
+ FD_Q_NODES_F0, FD_Q_NODES_F1, FD_Q_NODES_F2, FD_Q_NODES_F1010, FD_Q_NODES_F1001, FD_Q_B_SCHEDULE,
+ FD_Q_TABLE_BYTES) = range(14)
 
 EXPORTS = [
     "fd_plan_create", "fd_plan_destroy", "fd_plan_workspace", "fd_plan_query", "fock_diag_fwd",
@@ -31,7 +32,7 @@ EXPORTS = [
     "fock_state_fwd", "fd_state_device_status", "fd_state_plan_timing", "fd_state_plan_kernel_times",
     "fd_plan_create_total", "fd_plan_level_offsets", "detection_probs_until", "fd_state_plan_vjp_workspace",
     "fock_state_vjp", "fock_state_jvp", "fd_plan_jvp_workspace", "fock_diag_jvp", "fock_diag_fwd_static",
-    "fd_plan_set_checkpoint", "fd_plan_set_write_counters",
+    "fd_plan_set_checkpoint", "fd_plan_set_write_counters", "fd_plan_use_digit_table",
 ]
 (FD_K_PREP, FD_K_UFILL, FD_K_FWD_LEVEL, FD_K_OUT_PERM, FD_K_PERM_IN, FD_K_VJP_LEVEL, FD_K_UFILL_VJP,
  FD_K_VJP_FINAL, FD_K_ZERO, FD_K_BATCH_PREP, FD_K_BATCH_SWEEP, FD_K_BATCH_OUT) = range(12)
@@ -85,6 +86,7 @@ def lib():
     L.fd_plan_timing.argtypes = [vp, u32]
     L.fd_plan_use_graphs.argtypes = [vp, i32]
     L.fd_plan_set_checkpoint.argtypes = [vp, i32]
+    L.fd_plan_use_digit_table.argtypes = [vp, i32]
     L.fd_plan_set_write_counters.argtypes = [vp, vp, sz]
     L.fd_plan_kernel_times.argtypes = [vp, i32, i64p, ctypes.POINTER(ctypes.c_double)]
     L.fd_batch_set_tuning.argtypes = [ctypes.POINTER(BatchTuning)]
@@ -372,6 +374,10 @@ def fd_plan_set_write_counters(plan, counters=None):
         _check(lib().fd_plan_set_write_counters(plan.handle, None, 0))
     else:
         _check(lib().fd_plan_set_write_counters(plan.handle, _ptr(counters), counters.numel()))
+
+
+def fd_plan_use_digit_table(plan, enable=True):
+    _check(lib().fd_plan_use_digit_table(plan.handle, int(bool(enable))))
 
 
 def fd_plan_use_graphs(plan, enable=True):
