@@ -42,13 +42,6 @@ struct BatchCirc {
   int64_t out_elems, N;        // output elements; nodes (prod of detected cutoffs)
 };
 
-// One workgroup's share of a launch: units [u0, u1) of circuit `circ` at the
-// launch's step ((bridge, 16-point tile) items of Algorithm 1; (lattice point,
-// row chunk) pairs of geometry (RC, nchunks) for Algorithm 2).
-struct BatchItem {
-  int circ, u0, u1, RC, nchunks, pad[3];
-};
-
 // Pointers the level kernels load from memory are generic to the compiler, which
 // then emits flat loads and stores (counted by both the vector-memory and the
 // LDS wait counters, so LDS waits also wait for HBM traffic).  They all point

@@ -318,6 +318,17 @@ void count_work(const Plan& P, bool b_zero, int64_t* targets, int64_t* terms);
 fd_status run_forward_batch(int n, Plan* const* plans, const bool* odd, const void* const* A,
                             const void* const* b, const void* const* c, void* const* rho, void* const* ws,
                             hipStream_t st, std::string* err);
+// One workgroup's share of a batched launch: units [u0, u1) of circuit `circ` at
+// the launch's step ((bridge, 16-point tile) items of Algorithm 1; (lattice point,
+// row chunk) pairs of geometry (RC, nchunks) for Algorithm 2).
+struct BatchItem {
+  int circ, u0, u1, RC, nchunks, pad[3];
+};
+// Appends the items of a step of `units` units, `per` units each, to `items` (I:
+// their other members).  The kernels find a unit's point from its number with no
+// bound of their own, so an item outside 0 <= u0 < u1 <= units, or a number of
+// units that an item cannot hold, is refused (false) here.
+bool batch_cut(int64_t units, int64_t per, BatchItem I, std::vector<BatchItem>* items);
 void batch_forget(uint64_t plan_uid);   // drops cached batch schedules that use this plan
 fd_status batch_set_tuning(const fd_batch_tuning& T);
 fd_batch_tuning batch_get_tuning();

@@ -276,10 +276,10 @@ fd_status build_sched(int n, Plan* const* plans, const bool* odd, const void* co
           *err = "a step of circuit " + std::to_string(i) + " has too many units for one work item table";
           return FD_ERR_UNSUPPORTED;
         }
-        for (int64_t u0 = 0; u0 < units; u0 += per) {
-          I.u0 = (int)u0;
-          I.u1 = (int)std::min(units, u0 + per);
-          S->h_items.push_back(I);
+        if ((k.kind && (I.RC < 1 || I.nchunks < 1 || (int64_t)(I.nchunks - 1) * I.RC >= Pl.udims[0])) ||
+            !batch_cut(units, per, I, &S->h_items)) {
+          *err = "internal error: a work item of circuit " + std::to_string(i) + " outside its step";
+          return FD_ERR_UNSUPPORTED;
         }
       }
       st_.n = (int)S->h_items.size() - st_.i0;

@@ -455,6 +455,17 @@ VjpChunking vjp_chunking(const Plan& Pl) {
   return {32 * kVjpWaves, 16 * kVjpWaves, kSmallLevelUnits};
 }
 
+bool batch_cut(int64_t units, int64_t per, BatchItem I, std::vector<BatchItem>* items) {
+  if (units < 0 || units > 0x7fffffff || per < 1) return false;
+  for (int64_t u0 = 0; u0 < units; u0 += per) {
+    I.u0 = (int)u0;
+    I.u1 = (int)std::min(units, u0 + per);
+    if (I.u0 < 0 || I.u1 <= I.u0 || I.u1 > units) return false;
+    items->push_back(I);
+  }
+  return true;
+}
+
 // Chunk geometry of a reverse level with nwork lattice points.
 ChunkGeo vjp_geo(const Plan& Pl, int64_t nwork) {
   const VjpChunking t = vjp_chunking(Pl);
