@@ -49,7 +49,14 @@ constexpr int kPartialSlots = 4096;      // deterministic VJP partial accumulato
 constexpr int kStreamSlots = 1024;       // workgroups of a block kernel whose rows stream from HBM
 constexpr int kThreads = 256;
 constexpr int kBT = 64;                  // threads of the block (Algorithm 2) kernels: one wavefront
-constexpr int kVjpWaves = 4;             // wavefronts per workgroup of the block reverse kernel
+// Wavefronts per workgroup of the block reverse kernel (MD detected modes, nq
+// block coordinates).  With two or three undetected modes a row is so long that the
+// two halo rows of a chunk double its entries, and few chunks share the device:
+// eight wavefronts halve that chain (cutoffs 6, 6 undetected and 20: 499 -> 414 us per
+// reverse sweep, 3, 3, 3 undetected and 12: 352 -> 300, 10, 9 and 5, 5: 1198 -> 942).
+// Five and more detected modes keep four, as does one undetected mode.
+constexpr int kVjpWaves = 4;
+__host__ __device__ constexpr inline int vjp_waves(int MD, int nq) { return nq > 2 && MD <= 4 ? 2 * kVjpWaves : kVjpWaves; }
 constexpr int kFwdWaves = 4;             // wavefronts per workgroup of the block forward kernel
 constexpr int kFwdChunk = 448;           // own entries of one of its (lattice point, row chunk) units,
 constexpr int kFwdChunkSmall = 192;      // on levels with fewer than kSmallLevelUnits units

@@ -428,8 +428,8 @@ size_t vjp_lds_bytes_for(const Plan& Pl, const ChunkGeo& G) {
   const size_t rows =
       Pl.st_vjp ? 0 : ((size_t)(G.RC + 1) + G.RC + (size_t)Pl.nq * (G.RC + 2)) * G.R0;
   return std::max(2 * (kMaxCut + 4) * (eb / 2) + 3 * (size_t)(MD + 1) * 16 * 8 +
-                      ((size_t)kVjpWaves * NPD * 17 + rows) * eb,
-                  (size_t)kVjpWaves * NPD * NR * 16);
+                      ((size_t)vjp_waves(MD, Pl.nq) * NPD * 17 + rows) * eb,
+                  (size_t)vjp_waves(MD, Pl.nq) * NPD * NR * 16);
 }
 
 // Chunk geometry of a forward level with nwork lattice points (its units

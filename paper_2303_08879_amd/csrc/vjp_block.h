@@ -10,8 +10,8 @@
 namespace fd {
 
 // ---------------------------------------------------------------------------
-// Algorithm 2 reverse step.  One workgroup of four wavefronts per (lattice
-// point, chunk of rows of the first undetected coordinate).  The undetected
+// Algorithm 2 reverse step.  One workgroup of four or eight wavefronts (vjp_waves)
+// per (lattice point, chunk of rows of the first undetected coordinate).  The undetected
 // neighbour terms make the cotangent of a pivot entry pull from the entry one
 // row below, so a chunk recomputes the target cotangents of two rows past its
 // own (bridge pivots: the rows its diagonal pivot needs; diagonal pivot: one
@@ -30,14 +30,34 @@ namespace fd {
 // slot in global memory (blocks whose rows do not fit the LDS); the
 // __syncthreads between phases are workgroup-scope fences.
 // ---------------------------------------------------------------------------
+// Wavefronts per SIMD that the registers are cut to.  From 16 positions on the
+// instances in double precision hold 330 to 460 registers, and one wavefront that
+// keeps them beats two that spill 200 (reverse sweeps: an undetected mode of cutoff
+// 10 behind eight detected of cutoff 3 1664 -> 1058 us, cutoff 16 behind eight of
+// cutoff 2 733 -> 514); in single precision two with 60-110 spilled are no slower
+// (898 -> 876; one without: 886).
+template <int MD, int NQ, typename R>
+constexpr int kVjpBlockSimd = NQ + 2 * MD >= 16 && sizeof(R) == 8 ? 1 : 2;
+
 template <int MD, int NQ, typename R, bool ST>
-__global__ __launch_bounds__(64 * kVjpWaves, 2) void k_vjp_block(DevPlan P, VjpPtrs<R> V, const cx<R>* __restrict__ Ai,
+__global__ __launch_bounds__(64 * vjp_waves(MD, NQ), (kVjpBlockSimd<MD, NQ, R>)) void k_vjp_block(DevPlan P, VjpPtrs<R> V, const cx<R>* __restrict__ Ai,
                                                                  const cx<R>* __restrict__ bi, int S, int nwork,
                                                                  ChunkGeo G, double2* __restrict__ partial) {
   constexpr int NPD = 2 * MD, NPOS = NQ + NPD, NR = NPOS + 1, NPAIR = NPD * NR;
+  // 16 positions: the pivot's row and column would take a second tile each, so
+  // they are formed on the vector unit (cutoff 20 behind seven detected of cutoff 3
+  // 1124 -> 965 us per reverse sweep, in single precision 847 -> 701)
+  constexpr bool kPiv = NPOS == 16;
+  constexpr int NM = kPiv ? NPOS : NR;   // rows of u and columns of D that are products
   constexpr int KS = (NPD + 3) / 4;      // steps over the targets
-  constexpr int NT = (NR + 15) / 16;     // tiles of rows of u, and of columns of D
-  constexpr int WV = kVjpWaves;
+  constexpr int NT = (NM + 15) / 16;     // tiles of rows of u, and of columns of D
+  constexpr int WV = vjp_waves(MD, NQ);
+  // one undetected mode with five and six detected in double precision, seven in single:
+  // 10-25 registers over the two wavefronts' 256, unless what a lane derives from its
+  // position is formed anew for every pivot and the scales are looked up where they are
+  // used (five of cutoff 8 behind cutoff 30: 7920 -> 7790 us, six of cutoff 4 behind
+  // 12: 739 -> 667); the other instances lose 3-10 % by it
+  constexpr bool kTight = NQ == 2 && (sizeof(R) == 8 ? KS > 2 && kVjpBlockSimd<MD, NQ, R> == 2 : kPiv);
   typedef typename Mma<R>::v4 v4;
   extern __shared__ __align__(16) unsigned char smem_raw[];
   const int B = P.B, R0 = G.R0, RC = G.RC;
@@ -67,7 +87,7 @@ __global__ __launch_bounds__(64 * kVjpWaves, 2) void k_vjp_block(DevPlan P, VjpP
 #pragma unroll
     for (int s = 0; s < KS; ++s) {
       const int l = 16 * t + Mma<R>::row_pos(c), i = 4 * s + kq;
-      const bool in = l < NR && i < NPD;
+      const bool in = l < NM && i < NPD;
       const cx<R> v = ld(!in ? Ai : l < NPOS ? Ai + (NQ + i) * NPOS + l : bi + NQ + i);
       ar[t][s] = in ? v.x : R(0);
       ai[t][s] = in ? -v.y : R(0);
@@ -81,8 +101,20 @@ __global__ __launch_bounds__(64 * kVjpWaves, 2) void k_vjp_block(DevPlan P, VjpP
   int cj[KS];
 #pragma unroll
   for (int s = 0; s < KS; ++s) cj[s] = P.CD[min((4 * s + kq) >> 1, MD - 1)];
+  // the cotangent that a row is added to is read before the products (three
+  // undetected modes, double precision: 446 -> 411 us and 520 -> 505 per reverse sweep)
+  // or, in fewer registers, after them
+  constexpr bool kAhead = NQ == 6 && sizeof(R) == 8 && NT == 1 && !kPiv;
   MfmaAcc<NT> acc;
   mfma_acc_zero(acc);
+  constexpr int KV = kPiv ? KS : 1;
+  cx<R> bl[KV];            // b at the lane's positions, and its sums of bbar there
+  double bx[KV], by[KV];
+#pragma unroll
+  for (int s = 0; s < KV; ++s) {
+    bl[s] = kPiv && 4 * s + kq < NPD ? ld(bi + NQ + 4 * s + kq) : czero<R>();
+    bx[s] = by[s] = 0.0;
+  }
   __syncthreads();
 
   for (int w = blockIdx.x; w < nwork * G.nchunks; w += gridDim.x) {
@@ -127,12 +159,15 @@ __global__ __launch_bounds__(64 * kVjpWaves, 2) void k_vjp_block(DevPlan P, VjpP
       const int ee = diag ? eb1 : eq1;                        // entries [e0, ee) of the targets
       const cx<R>* pv = V.fcur[diag ? 0 : fam_f1k(K)] + rB;   // the pivot's values
       // targets: pointer and scale of each of the lane's positions
+      int kv = kq, cv = c;
+      if (kTight) asm volatile("" : "+v"(kv), "+v"(cv));   // (what follows is not moved out of the loops)
+      // (kTight: scales as 8-bit indexes into the square-root tables)
       const cx<R>* hptr[KS];
       R hw[KS];
-      uint32_t hv = 0;
+      uint32_t hi = 0, hv = 0;
 #pragma unroll
       for (int s = 0; s < KS; ++s) {
-        const int p = 4 * s + kq, j = min(p >> 1, MD - 1), side = p & 1;
+        const int p = 4 * s + kv, j = min(p >> 1, MD - 1), side = p & 1;
         const int mj = m_of(j);
         const int two = p == 2 * K ? 1 : 0;
         const int room = cj[s] - 2 - mj - (diag && j == 0 ? side : two);
@@ -142,20 +177,22 @@ __global__ __launch_bounds__(64 * kVjpWaves, 2) void k_vjp_block(DevPlan P, VjpP
         t = bridge ? gpk + (size_t)j * nrow1 - e0 : t;
         hptr[s] = ok ? t : pv;
         hw[s] = isq[mj + 1 + two];
+        hi |= (uint32_t)(kMaxCut + 4 + mj + 1 + two) << (8 * s);
         hv |= (ok ? 1u : 0u) << s;
       }
       // read values: columns l = 16 t + c
       const cx<R>* xptr[NT];
       R xw[NT];
-      uint32_t xv = 0;
+      uint32_t xi = 0, xv = 0;
 #pragma unroll
       for (int t = 0; t < NT; ++t) {
-        const int l = 16 * t + c, p = l - NQ, pc = min(max(p, 0), NPD - 1), j = pc >> 1;
+        const int l = 16 * t + cv, p = l - NQ, pc = min(max(p, 0), NPD - 1), j = pc >> 1;
         const int mj = m_of(j), dn = down(j);
         const bool first = p == 2 * K, det = p >= 0 && p < NPD;
-        const bool ok = l < NR && (!det || first || ((diag || p > 2 * K) && mj > 0));
+        const bool ok = l < NM && (!det || first || ((diag || p > 2 * K) && mj > 0));
         xptr[t] = !ok || !det ? pv : global_at<const cx<R>>(xp[K * kPtPos + pc]) + (first ? rB : (size_t)dn * B);
-        xw[t] = det ? sq[mj + (first ? 1 : 0)] : R(1);
+        xw[t] = sq[det ? mj + (first ? 1 : 0) : 1];
+        xi |= (uint32_t)(det ? mj + (first ? 1 : 0) : 1) << (8 * t);
         xv |= (ok ? 1u : 0u) << t;
       }
       // where the rows of u go: the cotangents of the detected reads to their
@@ -163,28 +200,33 @@ __global__ __launch_bounds__(64 * kVjpWaves, 2) void k_vjp_block(DevPlan P, VjpP
       // (added to) to the unit's rows, at offset loff, entries below lend
       cx<R>* gptr[NT * 4];
       R gw[NT * 4];
+      uint32_t gi[NT] = {};
       int loff[NT * 4], lend[NT * 4];
       uint32_t gv = 0, lsum = 0;
 #pragma unroll
       for (int t = 0; t < NT * 4; ++t) {
-        const int l = 4 * t + kq, p = l - NQ, pc = min(max(p, 0), NPD - 1), j = pc >> 1;
+        const int l = 4 * t + kv, p = l - NQ, pc = min(max(p, 0), NPD - 1), j = pc >> 1;
         const int mj = m_of(j), dn = down(j);
         const bool det = p >= 0 && p < NPD, first = p == 2 * K;
         const bool ok = det && (diag || p > 2 * K) && mj > 0;
         gptr[t] = global_at<cx<R>>(gp[K * kPtPos + pc]) + (ok ? (size_t)dn * B : 0);
-        gw[t] = det ? sq[first ? mK + 1 : mj] : R(1);
+        gw[t] = sq[det ? first ? mK + 1 : mj : 1];
+        gi[t / 4] |= (uint32_t)(det ? first ? mK + 1 : mj : 1) << (8 * (t % 4));
         gv |= (ok ? 1u : 0u) << t;
         const bool nb = l < NQ, piv = l == NPOS;
         loff[t] = nb ? (2 * RC + 1) * R0 + l * nrow2 : piv && !diag ? 0 : nrow1;
         lend[t] = nb ? ee : piv && !diag ? eb1 : piv || (det && first) ? e1 : e0;
         lsum |= (piv ? diag : first) ? 1u << t : 0u;
       }
+      // the row of u that the F0 cotangent adds up, and whether this lane holds it
+      const int srow = diag ? NPOS : NQ + 2 * K;
+      const bool sums = kq == (srow & 3);
       // read column t of entry ex: neighbour columns read the entry one step
       // down in their coordinate, with its square root as weight
       auto xcol = [&](int t, int ex, int* at, R* wt) -> bool {
         bool ok = ex < e1 && ((xv >> t) & 1);
         *at = ex;
-        *wt = xw[t];
+        *wt = kTight ? sq[(xi >> (8 * t)) & 255] : xw[t];
         if (t == 0) {
           const int q = (int)(((float)ex + 0.5f) * ui);
           const int kc = q - ud * (int)(((float)q + 0.5f) * di);
@@ -198,26 +240,27 @@ __global__ __launch_bounds__(64 * kVjpWaves, 2) void k_vjp_block(DevPlan P, VjpP
         return ok;
       };
       // the tile's loads, unconditional and unscaled: issued one tile ahead
-      // (a load waited on within the tile's work would wait for them all)
-      auto issue = [&](int eb, cx<R>(&h)[KS], cx<R>(&x)[NT][4], cx<R>& d0) {
+      // (a load waited on within the tile's work would wait for them all), but
+      // for the few reads beyond column 16, which go out before the next tile's
+      auto load_x = [&](int t, int eb, cx<R>(&x)[4]) {
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+          int at;
+          R wt;
+          (void)xcol(t, eb + 4 * s + kq, &at, &wt);
+          x[s] = ld(xptr[t] + at);
+        }
+      };
+      auto issue = [&](int eb, cx<R>(&h)[KS], cx<R>(&x)[4], cx<R>& d0, cx<R>& pval) {
         const int e = eb + c;
+        if (kPiv) pval = ld(pv + min(e, e1 - 1));
         if (K == 0) d0 = ld(V.d0cur + rB + min(e, e1 - 1));
 #pragma unroll
         for (int s = 0; s < KS; ++s) h[s] = ld(hptr[s] + (e < ee ? e : e0));
-        if (eb < e1) {
-#pragma unroll
-          for (int t = 0; t < NT; ++t)
-#pragma unroll
-            for (int s = 0; s < 4; ++s) {
-              int at;
-              R wt;
-              (void)xcol(t, eb + 4 * s + kq, &at, &wt);
-              x[t][s] = ld(xptr[t] + at);
-            }
-        }
+        if (eb < e1) load_x(0, eb, x);
       };
-      cx<R> hn[KS], xn[NT][4], dn = czero<R>();
-      if (e0 + 16 * wave < ee) issue(e0 + 16 * wave, hn, xn, dn);
+      cx<R> hn[KS], xn[4], dn = czero<R>(), pn = czero<R>();
+      if (e0 + 16 * wave < ee) issue(e0 + 16 * wave, hn, xn, dn, pn);
 #pragma unroll 1
       for (int eb = e0 + 16 * wave; eb < ee; eb += 16 * WV) {
         const int e = eb + c, le = e - e0;
@@ -227,15 +270,19 @@ __global__ __launch_bounds__(64 * kVjpWaves, 2) void k_vjp_block(DevPlan P, VjpP
 #pragma unroll
         for (int s = 0; s < KS; ++s) h[s] = hn[s];
 #pragma unroll
-        for (int t = 0; t < NT; ++t)
+        for (int s = 0; s < 4; ++s) x[0][s] = xn[s];
+        if (any_own) {
 #pragma unroll
-          for (int s = 0; s < 4; ++s) x[t][s] = xn[t][s];
-        const cx<R> d0 = dn;
-        if (eb + 16 * WV < ee) issue(eb + 16 * WV, hn, xn, dn);
+          for (int t = 1; t < NT; ++t) load_x(t, eb, x[t]);
+        }
+        const cx<R> d0 = dn, pval = pn;
+        if (eb + 16 * WV < ee) issue(eb + 16 * WV, hn, xn, dn, pn);
+        cx<R> was = czero<R>();
+        if (kAhead && sums && own) was = K == 0 ? d0 : g0a[le];
 #pragma unroll
         for (int s = 0; s < KS; ++s) {
           const bool ok = live && ((hv >> s) & 1);
-          h[s] = cscale(csel(ok, h[s], czero<R>()), hw[s]);
+          h[s] = cscale(csel(ok, h[s], czero<R>()), kTight ? sq[(hi >> (8 * s)) & 255] : hw[s]);
         }
 #pragma unroll
         for (int t = 0; t < NT; ++t) {
@@ -252,15 +299,37 @@ __global__ __launch_bounds__(64 * kVjpWaves, 2) void k_vjp_block(DevPlan P, VjpP
 #pragma unroll
           for (int s = 0; s < 4; ++s) {
             const int i = 4 * t + s;
-            if (4 * i >= NR) continue;   // no such rows
-            const cx<R> u = cscale(cmake<R>(re[s], im[s]), gw[i]);
+            if (4 * i >= NM) continue;   // no such rows
+            const cx<R> u = cscale(cmake<R>(re[s], im[s]), kTight ? sq[(gi[t] >> (8 * s)) & 255] : gw[i]);
             cx<R>* slot = gbv + loff[i] + le;
             if (e < lend[i]) {
-              cx<R> was = *slot;
-              was = csel(K == 0, d0, was);
-              *slot = cadd(u, csel((lsum >> i) & 1, was, czero<R>()));
+              if (kAhead) {
+                *slot = i == (srow >> 2) ? cadd(u, was) : u;
+              } else {
+                was = *slot;
+                was = csel(K == 0, d0, was);
+                *slot = cadd(u, csel((lsum >> i) & 1, was, czero<R>()));
+              }
             }
             if (own && ((gv >> i) & 1)) st(gptr[i] + e, u);
+          }
+        }
+        if (kPiv) {
+          // the pivot's row, b^H h, in the four lanes of an entry, and its column of D
+          cx<R> g = czero<R>();
+#pragma unroll
+          for (int s = 0; s < KV; ++s) {
+            cfma_conj(g, bl[s], h[s]);
+            const cx<R> ho = csel(own, h[s], czero<R>());
+            const double hx = ho.x, hy = ho.y, px = pval.x, py = pval.y;
+            bx[s] += px * hx + py * hy;
+            by[s] += px * hy - py * hx;
+          }
+          g = cadd(g, cmake<R>(__shfl_xor(g.x, 16), __shfl_xor(g.y, 16)));
+          g = cadd(g, cmake<R>(__shfl_xor(g.x, 32), __shfl_xor(g.y, 32)));
+          if (kq == 0) {
+            if (diag && own) g0a[le] = cadd(g, g0a[le]);
+            if (!diag && e < eb1) gbv[le] = g;
           }
         }
         if (any_own) {
@@ -302,7 +371,20 @@ __global__ __launch_bounds__(64 * kVjpWaves, 2) void k_vjp_block(DevPlan P, VjpP
   // fold the waves' pair tables (in wave order) into this block's slot
   cx<double>* red = reinterpret_cast<cx<double>*>(smem_raw);
   __syncthreads();
-  mfma_acc_store<NPD, NR, NR>(acc, red + (size_t)wave * NPAIR);
+  mfma_acc_store<NPD, NR, NM>(acc, red + (size_t)wave * NPAIR);
+  if (kPiv) {
+#pragma unroll
+    for (int s = 0; s < KV; ++s) {
+      double vx = bx[s], vy = by[s];
+#pragma unroll
+      for (int o = 8; o > 0; o >>= 1) {
+        vx += __shfl_xor(vx, o);
+        vy += __shfl_xor(vy, o);
+      }
+      const int p = 4 * s + kq;
+      if (c == 0 && p < NPD) red[(size_t)wave * NPAIR + p * NR + NPOS] = cmake<double>(vx, vy);
+    }
+  }
   __syncthreads();
   double2* slot = partial + (size_t)blockIdx.x * (NPOS * NR);
   for (int p = threadIdx.x; p < NPAIR; p += blockDim.x) {
@@ -325,7 +407,7 @@ static void launch_vjp_block_k(size_t shm, int grid, hipStream_t st, const DevPl
   if (shm > 65536)
     (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&k_vjp_block<MD, NQ, R, ST>),
                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)shm);
-  hipLaunchKernelGGL((k_vjp_block<MD, NQ, R, ST>), dim3(grid), dim3(64 * kVjpWaves), shm, st, P, Vp, Ai, bi, S, nwork,
+  hipLaunchKernelGGL((k_vjp_block<MD, NQ, R, ST>), dim3(grid), dim3(64 * vjp_waves(MD, NQ)), shm, st, P, Vp, Ai, bi, S, nwork,
                      G, partial);
 }
 
