@@ -408,8 +408,11 @@ constexpr int kSmallLevelUnits = 4096;   // below: the forward level halves its 
 // LDS tile of the permutations between rho's C order and node order:
 // consecutive lattice points x consecutive undetected-block entries
 constexpr int kOutTN = 64, kOutTK = 16;
-constexpr int kOutEPT = 4;                // elements of a thread of the permutations without undetected modes
-                                          // (16.8 M entries: 109 us, one element each 156)
+// Elements of a thread of the permutations without undetected modes: several in
+// flight where there are enough for the device (16.8 M entries: 109 us, one each 156),
+// one below (65 thousand: 2 us less, a million the same)
+constexpr int kOutEPT = 4;
+constexpr int64_t kOutEPTMin = 1 << 20;
 hipError_t launch_prep(const Plan& P, const void* A, const void* b, const void* c, void* Ai, void* f0node0,
                        hipStream_t st);
 // F0 in node order (level-major, prod_D C_j x B entries) -> rho in C order.

@@ -32,7 +32,7 @@ __global__ __launch_bounds__(64) void k_ufill(DevPlan P, const cx<R>* __restrict
 }
 
 // F0 (level-major nodes of B entries) -> rho, C order [kappa][n_D].
-template <typename R>
+template <typename R, int EPT>
 __global__ __launch_bounds__(kThreads) void k_out_perm(DevPlan P, const cx<R>* __restrict__ f0,
                                                        cx<R>* __restrict__ rho, int64_t N, int64_t total,
                                                        int* status) {
@@ -49,14 +49,14 @@ __global__ __launch_bounds__(kThreads) void k_out_perm(DevPlan P, const cx<R>* _
     const int64_t tiles = ((N + kOutTN - 1) / kOutTN) * ((P.B + kOutTK - 1) / kOutTK);
     for (int64_t t = blockIdx.x; t < tiles; t += gridDim.x) bad |= out_perm_tile<R>(P, spn, slv, f0, rho, N, t, tl);
   } else {
-    for (int64_t i0 = (int64_t)blockIdx.x * kThreads * kOutEPT; i0 < total;
-         i0 += (int64_t)gridDim.x * kThreads * kOutEPT) {
-      cx<R> v[kOutEPT];
+    for (int64_t i0 = (int64_t)blockIdx.x * kThreads * EPT; i0 < total;
+         i0 += (int64_t)gridDim.x * kThreads * EPT) {
+      cx<R> v[EPT];
 #pragma unroll
-      for (int e = 0; e < kOutEPT; ++e)
+      for (int e = 0; e < EPT; ++e)
         v[e] = out_perm_elem<R>(P, spn, slv, f0, N, min(i0 + e * kThreads + threadIdx.x, total - 1));
 #pragma unroll
-      for (int e = 0; e < kOutEPT; ++e) {
+      for (int e = 0; e < EPT; ++e) {
         const int64_t idx = i0 + e * kThreads + threadIdx.x;
         if (idx >= total) break;
         if (!isfinite(v[e].x) || !isfinite(v[e].y)) bad = 1;
@@ -266,12 +266,13 @@ static hipError_t launch_out_perm_t(const Plan& Pl, const DevPlan& P, const cx<R
   }
   const int64_t total = Pl.out_elems;
   const int64_t tiles = ((Pl.nodes_total + kOutTN - 1) / kOutTN) * ((Pl.B + kOutTK - 1) / kOutTK);
-  const int64_t grid =
-      std::min<int64_t>(Pl.B > 1 ? tiles : (total + kThreads * kOutEPT - 1) / (kThreads * kOutEPT), 65536);
+  const int ept = total >= kOutEPTMin ? kOutEPT : 1;
+  const int64_t grid = std::min<int64_t>(Pl.B > 1 ? tiles : (total + kThreads * ept - 1) / (kThreads * ept), 65536);
   const size_t shm = 16 * ((((size_t)(Pl.MD + 1) * (Pl.smax + 3)) * 4 + 15) / 16) +
                      16 * (((size_t)(Pl.smax + 2) * 8 + 15) / 16) + (size_t)kOutTN * (kOutTK + 1) * sizeof(cx<R>);
   KTimer kt(Pl, KK_OUT_PERM, st);
-  hipLaunchKernelGGL((k_out_perm<R>), dim3(grid), dim3(kThreads), shm, st, P, f0, reinterpret_cast<cx<R>*>(rho),
+  auto* kfn = ept == 1 ? &k_out_perm<R, 1> : &k_out_perm<R, kOutEPT>;
+  hipLaunchKernelGGL(kfn, dim3(grid), dim3(kThreads), shm, st, P, f0, reinterpret_cast<cx<R>*>(rho),
                      (int64_t)Pl.nodes_total, total, Pl.d_status);
   return hipGetLastError();
 }

@@ -38,7 +38,7 @@ __global__ void k_zero_d2(double2* p, int64_t n) {
 }
 
 // rho-shaped cotangent (C order [kappa][n_D]) -> node order (level-major)
-template <typename R>
+template <typename R, int EPT>
 __global__ __launch_bounds__(kThreads) void k_perm_in(DevPlan P, const cx<R>* __restrict__ drho, cx<R>* __restrict__ g0,
                                                       int64_t N, int64_t total) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
@@ -77,13 +77,13 @@ __global__ __launch_bounds__(kThreads) void k_perm_in(DevPlan P, const cx<R>* __
     return;
   }
   // one entry per node (no undetected modes): C-order index -> node order
-  for (int64_t i0 = (int64_t)blockIdx.x * kThreads * kOutEPT; i0 < total;
-       i0 += (int64_t)gridDim.x * kThreads * kOutEPT) {
-    cx<R> v[kOutEPT];
+  for (int64_t i0 = (int64_t)blockIdx.x * kThreads * EPT; i0 < total;
+       i0 += (int64_t)gridDim.x * kThreads * EPT) {
+    cx<R> v[EPT];
 #pragma unroll
-    for (int e = 0; e < kOutEPT; ++e) v[e] = ld(drho + min(i0 + e * kThreads + threadIdx.x, total - 1));
+    for (int e = 0; e < EPT; ++e) v[e] = ld(drho + min(i0 + e * kThreads + threadIdx.x, total - 1));
 #pragma unroll
-    for (int e = 0; e < kOutEPT; ++e) {
+    for (int e = 0; e < EPT; ++e) {
       const int64_t idx = i0 + e * kThreads + threadIdx.x;
       if (idx < total) st(g0 + node_of_cindex(P, spn, slv, (int)idx), v[e]);
     }
@@ -539,13 +539,14 @@ static hipError_t run_vjp_t(const Plan& Pl, bool odd, const void* A, const void*
   } else {
     const int64_t total = Pl.out_elems;
     const int64_t tiles = ((Pl.nodes_total + kOutTN - 1) / kOutTN) * ((Pl.B + kOutTK - 1) / kOutTK);
-    const int64_t grid =
-        std::min<int64_t>(Pl.B > 1 ? tiles : (total + kThreads * kOutEPT - 1) / (kThreads * kOutEPT), 65536);
+    const int ept = total >= kOutEPTMin ? kOutEPT : 1;
+    const int64_t grid = std::min<int64_t>(Pl.B > 1 ? tiles : (total + kThreads * ept - 1) / (kThreads * ept), 65536);
     const size_t shm = 16 * ((((size_t)(Pl.MD + 1) * (Pl.smax + 3)) * 4 + 15) / 16) +
                        16 * (((size_t)(Pl.smax + 2) * 8 + 15) / 16) +
                        (Pl.B > 1 ? (size_t)kOutTN * (kOutTK + 1) * sizeof(cx<R>) : 0);
     KTimer kt(Pl, KK_PERM_IN, st);
-    hipLaunchKernelGGL((k_perm_in<R>), dim3(grid), dim3(kThreads), shm, st, P,
+    auto* kfn = ept == 1 ? &k_perm_in<R, 1> : &k_perm_in<R, kOutEPT>;
+    hipLaunchKernelGGL(kfn, dim3(grid), dim3(kThreads), shm, st, P,
                        reinterpret_cast<const cx<R>*>(drho), g0, (int64_t)Pl.nodes_total, total);
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }
