@@ -76,7 +76,7 @@ constexpr int kWideTiles = 2048;         // tiles of a level up to which its fir
 // in a graph: two modes of cutoff 10 (1 tile) 148 against 200 us, three of cutoff
 // 9 (8 items) 261 against 324, four of cutoff 8 (27 items) 488 against 413.
 constexpr int kSmallFwdItems = 32, kSmallVjpItems = 16;
-constexpr int kVjpSlots = 16384;         // reduction slots of the state-vector cotangents
+constexpr int kVjpSlots = 512;           // reduction slots (and workgroups) of the state-vector reverse mode
 
 enum FamType { F_F0 = 0, F_F1K, F_F1B, F_F2, F_1010, F_1001 };
 

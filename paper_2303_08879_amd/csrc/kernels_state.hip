@@ -164,7 +164,7 @@ constexpr int kJvpTile = 4096, kJvpEPT = 4, kJvpThreads = kJvpTile / kJvpEPT;
 // The reverse mode stages no amplitudes: its tiles only number the entries (and
 // at most 2048 of them leave 33 lanes of 64 busy at the worst cutoffs), two
 // workgroups of four wavefronts on each CU.
-constexpr int kVjpTile = 2048, kVjpGrid = 512, kVjpChunk = 8, kVjpUw = kMaxCut;
+constexpr int kVjpTile = 2048, kVjpGrid = kVjpSlots, kVjpChunk = 8, kVjpUw = kMaxCut;
 // Items of a wavefront between two folds of its sums over the lanes (even): a
 // lane adds that many terms in a row and the folds go into a compensated sum.  One
 // chain over all 256 items of 8 modes cutoff 8 made the gradient's error 6.0e-16 and
@@ -811,8 +811,8 @@ static hipError_t run_state_vjp_t(const Plan& Pl, const void* c, const void* psi
   const int MD = Pl.MD, ncol = MD + MD * (MD + 1) / 2 + 1;
   double2* slots = static_cast<double2*>(ws);
   const StateTiles G = state_tiles(Pl, kVjpTile);
-  // at most kVjpGrid <= kVjpSlots workgroups (a multiple of 8), one slot each
-  static_assert(kVjpGrid <= kVjpSlots && kVjpGrid % 8 == 0, "reduction slots");
+  // at most kVjpGrid workgroups (a multiple of 8), one slot each
+  static_assert(kVjpGrid % 8 == 0, "one share of the items per XCD");
   const int64_t items = (int64_t)G.ntiles * ((G.T + 63) / 64);
   const int grid = (int)std::min<int64_t>((items + 8 * kVjpChunk - 1) / (8 * kVjpChunk) * 8, kVjpGrid);
   {

@@ -602,8 +602,8 @@ VjpLayout vjp_layout(const Plan& P, bool odd, size_t base) {
 size_t vjp_private_entries(const Plan& P) {
   if (P.B == 1 || P.MD == 0) return 0;
   const ChunkGeo G = chunk_geo(P, vjp_chunking(P).target);   // the taller of the launcher's two chunk heights
-  return (size_t)(P.MD + 1) * (G.RC + 1) * G.R0 + (size_t)G.RC * G.R0 +
-         (P.st_vjp ? (size_t)P.nq * (G.RC + 2) * G.R0 : 0);
+  return (size_t)P.MD * (G.RC + 1) * G.R0 +
+         (P.st_vjp ? ((size_t)(G.RC + 1) + G.RC + (size_t)P.nq * (G.RC + 2)) * G.R0 : 0);
 }
 
 
