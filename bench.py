@@ -28,6 +28,7 @@ import hashlib
 import json
 import math
 import os
+import re
 import sys
 import time
 
@@ -52,24 +53,38 @@ def workload(name):
     raise SystemExit(f"unknown workload {name}")
 
 
-# Sources each level kernel is compiled from: a counter summary applies to a
-# kernel only while these hash to the value recorded with it.
+# The file each level kernel is defined in: a counter summary applies to a kernel
+# only while that file and every library file that it includes hash to the value
+# recorded with the summary.
 KERNEL_SOURCES = {
-    "k_vjp_point": ["kernels_vjp_point.hip", "vjp_point_units.h", "vjp_common.h", "pt_units.h", "fd_device.h"],
-    "k_vjp_block": ["vjp_block.h", "vjp_common.h", "fd_device.h"],
-    "k_fwd_point": ["kernels_point.hip", "pt_units.h", "fd_device.h"],
-    "k_fwd_block": ["fwd_block.h", "fwd_units.h", "fd_device.h"],
-    "k_state_level": ["kernels_state.hip", "fd_device.h"],
-    "k_state_jvp": ["kernels_state.hip", "fd_device.h"],
-    "k_state_vjp": ["kernels_state.hip", "fd_device.h"],
+    "k_vjp_point": "kernels_vjp_point.hip",
+    "k_vjp_block": "vjp_block.h",
+    "k_fwd_point": "kernels_point.hip",
+    "k_fwd_block": "fwd_block.h",
+    "k_state_level": "kernels_state.hip",
+    "k_state_jvp": "kernels_state.hip",
+    "k_state_vjp": "kernels_state.hip",
 }
+
+
+def kernel_source_files(kernel):
+    csrc = os.path.join(HERE, "paper_2303_08879_amd", "csrc")
+    todo, files = [KERNEL_SOURCES[kernel]], {}
+    while todo:
+        f = todo.pop()
+        path = os.path.join(csrc, f)
+        if f in files or not os.path.exists(path):   # (the public header: declarations only)
+            continue
+        with open(path, "rb") as fh:
+            files[f] = fh.read()
+        todo += re.findall(r'^#include "(\w+\.h)"', files[f].decode(), flags=re.M)
+    return files
 
 
 def kernel_source_hash(kernel):
     h = hashlib.sha256()
-    for f in KERNEL_SOURCES[kernel]:
-        with open(os.path.join(HERE, "paper_2303_08879_amd", "csrc", f), "rb") as fh:
-            h.update(fh.read())
+    for f, text in sorted(kernel_source_files(kernel).items()):
+        h.update(f.encode() + b"\0" + text)
     return h.hexdigest()[:16]
 
 
