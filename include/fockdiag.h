@@ -371,7 +371,7 @@ const char* fd_last_error(void);
 
 /* Reads and clears the plan's device status word (synchronises `stream`):
  * FD_OK, or FD_ERR_NONFINITE if a non-finite input or output was seen, or
- * or FD_ERR_INVALID_ARG if a plan made with FD_B_ZERO received a non-zero b. */
+ * FD_ERR_INVALID_ARG if a plan made with FD_B_ZERO received a non-zero b. */
 fd_status fd_device_status(fd_plan p, hipStream_t stream);
 
 /* ---- Total photon cutoff and probability-sum stopping -----------------

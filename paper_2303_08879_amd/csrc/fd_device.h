@@ -160,7 +160,7 @@ struct LevelPtrs {
 // != 0: with tangents, dT bytes after the values (odd levels swept).
 template <typename R>
 hipError_t launch_fwd_point_level(const Plan& Pl, const DevPlan& P, bool odd, int S, const LevelPtrs<R>& L,
-                                  const cx<R>* A, const cx<R>* b, int nwork, hipStream_t st, int64_t dT = 0);
+                                  const cx<R>* A, const cx<R>* b, hipStream_t st, int64_t dT = 0);
 
 // Whole sweeps of small plans (Plan::small_fwd, small_vjp) in one workgroup
 // (kernels_point_small.hip); fam / gfam: node-0 pointers per family, [0] = F0.

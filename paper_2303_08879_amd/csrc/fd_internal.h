@@ -68,13 +68,25 @@ constexpr size_t kDigitTableBudget = size_t(1) << 30;   // bytes of all digit ta
 // wavefronts).  Eight modes: 71 thousand points 30 against 28 us, 143 thousand 41
 // against 48, a million 218 against 236.
 constexpr int kPointTileMin = 1 << 17;
-constexpr int kWideTiles = 2048;         // tiles of a level up to which its first ones get a workgroup each
+// Tiles of a level up to which its first ones get a workgroup each (reverse sweeps,
+// complex128, general b, graph: 0 / 256 / 2048 / 8192: five modes of cutoff 8 422 / 312 /
+// 312 / 312 us, seven of cutoff 5 469 / 372 / 328 / 327, eight of cutoff 5 697 / 589 / 544 /
+// 561, eight of cutoff 8 7920 / 7806 / 7780 / 7837).
+constexpr int kWideTiles = 2048;
 // Plans with every mode detected whose levels have at most this many (bridge,
 // 16-point tile) items run the sweep in one workgroup: about as many as it runs
 // at once, past which it falls behind level launches replayed from a graph.
-// Forward + reverse, complex128, displaced, one workgroup against level launches
-// in a graph: two modes of cutoff 10 (1 tile) 148 against 200 us, three of cutoff
-// 9 (8 items) 261 against 324, four of cutoff 8 (27 items) 488 against 413.
+// One workgroup against level launches, us, complex128 displaced replayed from a
+// graph / launched one by one / complex64 launched one by one:
+//   forward  two modes of cutoff 10 (1 tile) 43 : 67 / 38 : 67 / 37 : 64, four of
+//            cutoff 8 (27 items) 129 : 130 / 124 : 137 / 107 : 130, five of cutoff 5
+//            (32) 135 : 110 / 130 : 114 / 105 : 115, b = 0 90 : 89 / 85 : 95 / 74 : 95
+//   reverse  two of cutoff 10 97 : 120 / 94 : 127 / 91 : 124, three of cutoff 9 (8 items)
+//            174 : 180 / 170 : 190 / 160 : 191, three of cutoff 16 (16) 392 : 327 / 389 :
+//            350 / 361 : 348, four of cutoff 8 311 : 210 / 307 : 228 / 286 : 221.
+// Between, the reverse of five and more modes is up to a fifth slower in one
+// workgroup (eight of cutoff 2 136 : 105), where a level's first tiles take many
+// bridges that level launches spread over a workgroup each.
 constexpr int kSmallFwdItems = 32, kSmallVjpItems = 16;
 constexpr int kVjpSlots = 512;           // reduction slots (and workgroups) of the state-vector reverse mode
 

@@ -1,6 +1,7 @@
-// Forward level kernels of the selective Fock-amplitude sweep (gfx950): one
-// launch per sweep step S (all targets of one step are independent, Sec. 2.2).
-// The per-point and per-(node, chunk) work lives in fwd_units.h.
+// Driver of the forward sweep (gfx950): one launch per step S (all targets of
+// one step are independent, Sec. 2.2) around the prep, the undetected-block fill
+// and the output permutation, which are here.  The level kernels are in
+// kernels_point.hip (pt_units.h) and fwd_block.h (fwd_units.h).
 #include <algorithm>
 #include <cstring>
 #include <type_traits>
@@ -105,7 +106,7 @@ static hipError_t launch_fwd_level_t(const Plan& Pl, const DevPlan& P, bool odd,
   const cx<R>* A = reinterpret_cast<const cx<R>*>(Ai);
   const cx<R>* b = reinterpret_cast<const cx<R>*>(bi);
   if (Pl.B == 1) {
-    return launch_fwd_point_level<R>(Pl, P, odd, S, L, A, b, nwork, st);
+    return launch_fwd_point_level<R>(Pl, P, odd, S, L, A, b, st);
   }
   return MD <= 4 ? launch_fwd_block_range<R, 1>(Pl, P, S, L, A, b, nwork, st)
                  : launch_fwd_block_range<R, 5>(Pl, P, S, L, A, b, nwork, st);
@@ -500,7 +501,7 @@ static hipError_t run_jvp_t(const Plan& Pl, const void* A, const void* b, const 
       if (e != hipSuccess) return e;
       continue;
     }
-    if ((e = launch_fwd_point_level<R>(Pl, P, true, S, L, Ai, bi, nwork, st, half)) != hipSuccess) return e;
+    if ((e = launch_fwd_point_level<R>(Pl, P, true, S, L, Ai, bi, st, half)) != hipSuccess) return e;
   }
   if ((e = launch_out_perm_t<R>(Pl, P, f0, rho, st)) != hipSuccess) return e;
   return launch_out_perm_t<R>(Pl, P, tf0, drho, st);

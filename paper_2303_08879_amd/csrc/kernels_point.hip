@@ -1,6 +1,6 @@
 // Forward level kernels of plans with every mode detected (Algorithm 1), values
-// or values and tangents (forward mode, DUAL): one launch per sweep step, the points of the level in tiles of 16 columns on the
-// matrix cores (pt_units.h).
+// or values and tangents (forward mode, DUAL): one launch per sweep step, the
+// points of the level in tiles of 16 columns on the matrix cores (pt_units.h).
 #include <algorithm>
 
 #include "pt_units.h"
@@ -88,7 +88,7 @@ hipError_t fill_digit_table(const Plan& Pl) {
 
 template <typename R>
 hipError_t launch_fwd_point_level(const Plan& Pl, const DevPlan& P, bool odd, int S, const LevelPtrs<R>& L,
-                                  const cx<R>* A, const cx<R>* b, int nwork, hipStream_t st, int64_t dT) {
+                                  const cx<R>* A, const cx<R>* b, hipStream_t st, int64_t dT) {
   const PtItems I = pt_items(Pl, S);
   int units = 0;
   for (int K = 0; K < Pl.MD; ++K) units += I.tiles(K);
@@ -124,8 +124,8 @@ hipError_t launch_fwd_point_level(const Plan& Pl, const DevPlan& P, bool odd, in
   return hipGetLastError();
 }
 template hipError_t launch_fwd_point_level<float>(const Plan&, const DevPlan&, bool, int, const LevelPtrs<float>&,
-                                                  const cx<float>*, const cx<float>*, int, hipStream_t, int64_t);
+                                                  const cx<float>*, const cx<float>*, hipStream_t, int64_t);
 template hipError_t launch_fwd_point_level<double>(const Plan&, const DevPlan&, bool, int, const LevelPtrs<double>&,
-                                                   const cx<double>*, const cx<double>*, int, hipStream_t, int64_t);
+                                                   const cx<double>*, const cx<double>*, hipStream_t, int64_t);
 
 }  // namespace fd

@@ -12,19 +12,18 @@
 // of its only reader: no atomics, and two-level rings suffice for the
 // cotangents.  Diagonal amplitudes F0(m) are read only by pivots that sit at
 // the same lattice point m, so their cotangents are summed locally.
-// Abar / bbar are sums over every target: each workgroup stages its
-// per-pivot vectors (h, G-reads) in LDS and a fixed set of threads forms the
-// outer products in a fixed order, then adds them to its own partial slot;
-// one final kernel sums the slots in order.  The result is bitwise
-// reproducible for a given plan.
+// Abar / bbar are sums over every target: products h conj(x)^T on the matrix
+// cores, summed in registers; each workgroup adds its wavefronts' sums in order to
+// its own partial slot, and one final kernel sums the slots in order.  The result
+// is bitwise reproducible for a given plan.  This file: the cotangent permutation,
+// the reverse of the block fill, the final sums and the driver (level kernels:
+// vjp_point_units.h, vjp_block.h).
 #include <algorithm>
 #include <cstring>
 
 #include "vjp_common.h"
 
 namespace fd {
-
-
 
 template <typename R>
 __global__ void k_zero_cx(cx<R>* p, int64_t n) {

@@ -1,6 +1,6 @@
-// Shared by the reverse point kernels (kernels_vjp.hip) and the reverse
-// block kernels (kernels_vjp_block.hip): the per-level pointer table of the
-// reverse sweep and the matrix-core reduction of the Abar / bbar records.
+// Shared by the reverse point kernels (vjp_point_units.h) and the reverse block
+// kernel (vjp_block.h): the per-level pointer table of the reverse sweep and the
+// matrix-core reduction of Abar / bbar.
 #pragma once
 
 #include "pt_units.h"
@@ -20,9 +20,8 @@ struct VjpPtrs {
   int64_t priv_stride;          // entries per slot
 };
 
-// Abar / bbar: every reverse step reduces outer products of per-target
-// records (the target cotangents h and the read values x of one pivot
-// application) over all targets: D[i][l] = sum h_i conj(x_l), a dense
+// Abar / bbar: every reverse step reduces outer products of the target
+// cotangents h and the read values x of a pivot application over all of them: D[i][l] = sum h_i conj(x_l), a dense
 // contraction over points or block entries, on FP64 MFMA 16x16x4 steps of four
 // of them: lane t feeds value t % 16 of number 4 s + t / 16 to both operands and
 // keeps D[4 j + t / 16][t % 16], j = 0..3 (the gfx950 output layout, checked on
