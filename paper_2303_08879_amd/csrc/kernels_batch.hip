@@ -606,7 +606,8 @@ fd_status run_forward_batch(int n, Plan* const* plans, const bool* odd, const vo
     w2[k] = ws[i];
   }
   hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-  const bool captured_by_caller = hipStreamIsCapturing(st, &cap) == hipSuccess && cap != hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(st, &cap) != hipSuccess) (void)hipGetLastError();   // not left for the launches' checks
+  const bool captured_by_caller = cap != hipStreamCaptureStatusNone;
   auto fail_hip = [&](hipError_t e) {
     *err = std::string("kernel launch failed: ") + hipGetErrorString(e);
     return FD_ERR_HIP;
