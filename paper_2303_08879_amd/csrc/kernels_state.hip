@@ -379,11 +379,12 @@ __host__ __device__ constexpr int vjp_cols(int MD) { return MD + MD * (MD + 1) /
 // complex sums) are shared by two wavefronts: each has half of the modes as rows i and
 // takes every other pair (i, l) between the halves, as u_i v_l or u_l v_i.
 //
-// What bounds it (8 modes, cutoff 8, c128: 480 us): the shifts along the slower
-// modes miss the L2, so 3.2 GB leave it for 537 MB of psi and g (6.7 TB/s, the rate
-// of the cache behind it), with two wavefronts per SIMD to hide the loads; the f64
-// FMAs take 257 us.  Loading an item only after the products of the one before: 574
-// us; all loads of an item ahead: 28 registers spilled, 827.
+// What bounds it (8 modes, cutoff 8, c128: 455 us): instructions.  The vector unit
+// issues two thirds of the time, 87 M wave instructions in double precision and as
+// many others, with two wavefronts per SIMD, which wait a fifth of theirs; the shifts
+// along the slower modes miss the L2s, which 1.74 GB leave for 537 MB of psi and g (3.8
+// TB/s).  Loading an item only after the products of the one before: 574 us against
+// 480; all loads of an item ahead: 28 registers spilled, 827.
 // The order of the items does not matter (chunks of 2 to 512: 1045 to 1081 us for the
 // call).  The version before staged tiles of psi in LDS and folded each of the
 // 45 sums of every tile over the lanes: 620 us.
