@@ -285,6 +285,7 @@ struct VjpLayout {
 // the own F0 cotangent rows and the undetected-neighbour terms.
 size_t vjp_private_entries(const Plan& P);
 size_t vjp_lds_bytes(const Plan& P);   // dynamic LDS of the block reverse kernel (largest geometry used)
+bool vjp_takes_block(const Plan& P);   // whether the reverse mode takes the plan's undetected block
 // Dynamic LDS of the forward block kernel for one chunk geometry: F0 rows
 // [k0-2, k1), MD bridge pivot blocks of rows [k0-1, k1), A and b, the
 // square-root tables.

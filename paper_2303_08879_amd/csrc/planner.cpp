@@ -489,6 +489,21 @@ size_t vjp_lds_bytes(const Plan& Pl) {
   return std::max(vjp_lds_bytes_for(Pl, chunk_geo(Pl, t.target)), vjp_lds_bytes_for(Pl, chunk_geo(Pl, t.small)));
 }
 
+// With a detected mode, rows that do not fit the LDS are streamed: every block is
+// taken.  Without one only the block's fill runs, and what is taken is a limit of
+// the interface that no kernel's LDS moves: a chunk of 128 entries, F0 and its
+// undetected neighbours with their halo rows, 66 entries per position and the
+// pair table, together with the square-root tables, in 160 KB.
+bool vjp_takes_block(const Plan& Pl) {
+  if (Pl.B == 1) return true;
+  if (Pl.MD > 0) return vjp_lds_bytes(Pl) <= kMaxLds && ufill_launch_lds_bytes(Pl, true) <= kMaxLds;
+  const size_t eb = elem_bytes(Pl.dt);
+  const ChunkGeo G = chunk_geo(Pl, 128);
+  const size_t entries = ((size_t)(G.RC + 1) + (size_t)Pl.nq * (G.RC + 2)) * G.R0 + (size_t)66 * (Pl.npos + 1) +
+                         (size_t)Pl.npos * (Pl.npos + 1);
+  return entries * eb + (kMaxCut + 4) * eb <= kMaxLds && ufill_launch_lds_bytes(Pl, true) <= kMaxLds;
+}
+
 size_t jvp_half_bytes(const Plan& Pl) { return (fwd_layout(Pl, true, false, 0).total + 255) / 256 * 256; }
 
 // State vectors: the amplitudes in level order plus A and b of the kept modes.
